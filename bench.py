@@ -48,7 +48,8 @@ TRAFFIC = {
 
 # the sources that build the solver kernel and the mesh layout it reads (not the server's host code)
 KERNEL_SOURCES = ["include/pfc.h"] + [f"paper_1501_06852_amd/csrc/{f}" for f in
-                                      ("device.h", "host.h", "mesh.hip", "pfc_internal.h", "solver.h", "solver.hip")]
+                                      ("device.h", "host.h", "mesh.hip", "pfc_internal.h", "solver.h", "solver.hip", "tick.h",
+                                       "tick_f32.hip", "tick_f64.hip")]
 
 
 def kernel_source_digest():

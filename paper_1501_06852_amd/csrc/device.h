@@ -9,6 +9,8 @@
 // partials in fixed order.  Results are therefore bitwise reproducible and
 // independent of what else runs in the same launch.
 #pragma once
+#include <type_traits>
+
 #include "pfc_internal.h"
 
 namespace pfc {
@@ -27,6 +29,11 @@ struct Team {
 #define PFC_LCOL_W 16
 #define PFC_LCOL (PFC_WAVES * 64 * PFC_LCOL_W)
 __shared__ int pfc_lcol[PFC_LCOL];
+
+// Frames of the two-iterations-per-launch phases, and the row sums of the
+// reassembly of N (8 per thread).
+#define PFC_SS_LDS 8192
+__shared__ double pfc_ss[PFC_SS_LDS];
 
 // Where a launch takes the columns of the P1 pattern from: memory, the LDS
 // staging buffer, or computed from the row (periodic grid meshes, grid_col).
@@ -209,141 +216,244 @@ template <> struct TV<float> {
 // with S_k = sum over the vertices of psi^k and c_m = m!/(m+4)!.
 __device__ __forceinline__ double cm_of(int dim) { return dim == 2 ? (1.0 / 360.0) : (1.0 / 840.0); }
 
-// P2 (Section 3, p = 2; integrands of degree 8, exact through the reference
-// table C4[a][b][c][d] = int phi_a phi_b phi_c phi_d / |T|):
-//   Mpsi2^T_ab             = |T| sum_{c,d} psi_c psi_d C4[a][b][c][d]
-//   int_T psi_h^3 phi_a    = |T| sum_b psi_b sum_{c,d} psi_c psi_d C4[a][b][c][d]
-template <int Q, typename PsiF>
-__device__ __forceinline__ double entry_Mpsi2_p2(const MeshDev& m, long long e, PsiF psi) {
-  double acc = 0.0;
-  for (int t = m.sl_el_ptr[e]; t < m.sl_el_ptr[e + 1]; ++t) {
-    const int pk = m.sl_el[t];
-    const int el = pk >> 8, a = (pk >> 4) & 15, b = pk & 15;
-    const int* en = m.elem_nodes + (long long)el * Q;
-    double p[Q];
-#pragma unroll
-    for (int c = 0; c < Q; ++c) p[c] = psi(en[c]);
-    const double* C = m.p2_C4 + (a * Q + b) * Q * Q;
-    double s = 0.0;
-#pragma unroll 1
-    for (int c = 0; c < Q; ++c) {  // one row of the table at a time keeps the register use low
-      double r = 0.0;
-#pragma unroll
-      for (int d = 0; d < Q; ++d) r += C[c * Q + d] * p[d];
-      s += p[c] * r;
-    }
-    acc += m.elem_vol[el] * s;
-  }
-  return acc;
-}
+// P2 (Section 3, p = 2; integrands of degree 8, exact through reference tables
+// of the basis' fourfold products over |T|, packed by their symmetry in c, d
+// and in b, c, d):
+//   Mpsi2^T_ab          = |T| sum_{c <= d} psi_c psi_d C2[a][b][c, d]
+//   int_T psi_h^3 phi_a = |T| sum_{b <= c <= d} psi_b psi_c psi_d C3[a][b, c, d]
+//
+// Element sums are formed row by row: a thread walks the simplices around its
+// node once and adds each simplex's terms to the entries of its row, whose
+// positions the mesh stores with the visit.  Against walking the simplices of
+// every stored entry (dim + 1 times as many visits, each with its own gathers
+// of the element's nodes and of psi there) the visit lists are coalesced
+// streams and psi is gathered once per neighbour or once per visit.  Bound by
+// those gathers' latency, so the loads of several visits are issued together;
+// the terms of an entry are added in element order, one at a time.
+// Measured per call, launch and wait (19 us) included: pfc_assemble_N on 3D 64^3
+// 429 -> 67 us, pfc_apply_AR on 2D 512^2 65 -> 31 us, pfc_stage_rhs on 3D 48^3
+// 128 -> 49 us, pfc_load_psi3 on P2 200^2 68 -> 33 us; inside the solver's
+// launches (psi through the element's nodes, eight entries a round) a 3D 64^3
+// step 25.8 -> 25.3 ms.
 
-template <int Q, typename PsiF>
-__device__ __forceinline__ double node_psi3_p2(const MeshDev& m, int i, PsiF psi) {
-  double acc = 0.0;
-  for (int t = m.nd_el_ptr[i]; t < m.nd_el_ptr[i + 1]; ++t) {
-    const int pk = m.nd_el[t];
-    const int el = pk >> 4, a = pk & 15;
-    const int* en = m.elem_nodes + (long long)el * Q;
-    double p[Q];
+// one visit: the simplex, its volume, the node's local index a, psi at the
+// simplex's Q nodes; slot(c): position of its local node c in the row
+template <int Q>
+struct Visit {
+  static constexpr int W = (Q + 3) / 4;
+  int el, a;
+  double vol, p[Q];
+  unsigned word[W];        // narrow rows: the positions, a byte each
+  const unsigned* wide;    // long rows: the lane's first position, and the visit; or null
+  int t;
+  __device__ __forceinline__ int slot(int c) const {
+    if (wide) return (int)wide[64LL * ((long long)Q * t + c)];
+    unsigned w = word[0];
 #pragma unroll
-    for (int c = 0; c < Q; ++c) p[c] = psi(en[c]);
-    double s = 0.0;
-#pragma unroll 1
-    for (int b = 0; b < Q; ++b) {
-      const double* C = m.p2_C4 + (a * Q + b) * Q * Q;
-      double r2 = 0.0;
-#pragma unroll 1
-      for (int c = 0; c < Q; ++c) {
-        double r = 0.0;
+    for (int q = 1; q < W; ++q) w = c >= 4 * q ? word[q] : w;
+    return (int)((w >> (8 * (c & 3))) & 255u);
+  }
+};
+
+// visit(v) for every simplex around the row of (slice, lane), in element order;
+// psi(v, c): the value at local node c of the visit's simplex.  Q: nodes per
+// simplex (3, 4: P1; 6, 10: P2).  U visits' list entries and volumes are loaded
+// together; AHEAD: their psi as well (gathers from memory), else each visit's psi
+// (read from LDS) just before the visit.  WIDE: the mesh may have long rows.
+template <int Q, int U, bool AHEAD, bool WIDE, typename PsiF, typename F>
+__device__ __forceinline__ void for_visits(const MeshDev& m, int sl, int lane, PsiF psi, F visit) {
+  constexpr int BITS = Q <= 4 ? 2 : 4, W = Visit<Q>::W;
+  const long long vb = m.nv_ptr[sl];
+  const int vw = (int)((m.nv_ptr[sl + 1] - vb) >> 6);
+  const int* el_l = m.nv_el + vb + lane;
+  const unsigned* slot_l = m.nv_slot + vb * m.nv_words + lane;
+  const bool wide = WIDE && m.nv_wide != 0;
+  for (int t = 0; t < vw; t += U) {
+    Visit<Q> v[U];
+    int pk[U];
 #pragma unroll
-        for (int d = 0; d < Q; ++d) r += C[c * Q + d] * p[d];
-        r2 += p[c] * r;
+    for (int u = 0; u < U; ++u) {
+      const int tu = min(t + u, vw - 1);
+      pk[u] = el_l[64LL * tu];
+      v[u].wide = wide ? slot_l : nullptr;
+      v[u].t = tu;
+#pragma unroll
+      for (int q = 0; q < W; ++q) v[u].word[q] = wide ? 0u : slot_l[64LL * ((long long)W * tu + q)];
+      if (t + u >= vw) pk[u] = -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u].el = max(pk[u], 0) >> BITS;
+      v[u].a = pk[u] & ((1 << BITS) - 1);
+      v[u].vol = m.elem_vol[v[u].el];
+      if constexpr (AHEAD) {
+#pragma unroll
+        for (int c = 0; c < Q; ++c) v[u].p[c] = psi(v[u], c);
       }
-      s += psi(en[b]) * r2;
-    }
-    acc += m.elem_vol[el] * s;
-  }
-  return acc;
-}
-
-// The P1 element sums below visit an element list in groups of PFC_EV: the
-// loads of a group (list entries, then the elements' nodes, then psi there)
-// are issued together instead of one dependent chain per visit, and the
-// visits' terms are then added in list order as one visit at a time would.
-#define PFC_EV 4  // entry sums
-#define PFC_EVN 3  // node sums: psi there is a stage combination (up to three loads)
-// psi at the vertices of element el, psi(node) supplied by a functor (p[3] = 0
-// on triangles)
-template <typename PsiF>
-__device__ __forceinline__ void elem_psi4(const MeshDev& m, int el, PsiF psi, double* p) {
-  const int k = m.dim + 1;
-  const int* en = m.elem_nodes + (long long)el * k;
-  const int n0 = en[0], n1 = en[1], n2 = en[2];
-  const int n3 = k == 4 ? en[3] : n2;
-  p[0] = psi(n0);
-  p[1] = psi(n1);
-  p[2] = psi(n2);
-  p[3] = k == 4 ? psi(n3) : 0.0;
-}
-
-template <typename PsiF>
-__device__ __forceinline__ double entry_Mpsi2(const MeshDev& m, long long e, PsiF psi) {
-  if (m.degree == 2) return m.dim == 2 ? entry_Mpsi2_p2<6>(m, e, psi) : entry_Mpsi2_p2<10>(m, e, psi);
-  double acc = 0.0;
-  const double cm = cm_of(m.dim);
-  const int t0 = m.sl_el_ptr[e], t1 = m.sl_el_ptr[e + 1];
-  for (int t = t0; t < t1; t += PFC_EV) {
-    int pk[PFC_EV];
-#pragma unroll
-    for (int u = 0; u < PFC_EV; ++u) pk[u] = m.sl_el[min(t + u, t1 - 1)];
-    double p[PFC_EV][4], vol[PFC_EV];
-#pragma unroll
-    for (int u = 0; u < PFC_EV; ++u) {
-      elem_psi4(m, pk[u] >> 4, psi, p[u]);
-      vol[u] = m.elem_vol[pk[u] >> 4];
     }
 #pragma unroll
-    for (int u = 0; u < PFC_EV; ++u) {
-      if (t + u >= t1) break;
-      const int a = (pk[u] >> 2) & 3, b = pk[u] & 3;
-      double S1 = 0.0, S2 = 0.0;
-      for (int v = 0; v <= m.dim; ++v) { S1 += p[u][v]; S2 += p[u][v] * p[u][v]; }
-      const double pa = p[u][a], pb = p[u][b];
-      const double s = S1 * S1 + S2 + 2.0 * S1 * (pa + pb) + 2.0 * (pa * pa + pb * pb + pa * pb);
-      acc += vol[u] * cm * (a == b ? 2.0 : 1.0) * s;
+    for (int u = 0; u < U; ++u) {
+      if (pk[u] < 0) continue;
+      if constexpr (!AHEAD) {
+#pragma unroll
+        for (int c = 0; c < Q; ++c) v[u].p[c] = psi(v[u], c);
+      }
+      visit(v[u]);
     }
   }
-  return acc;
+}
+// visits per group: with psi gathered from memory, and with psi in LDS
+template <int Q> struct VisitU { static constexpr int mem = Q <= 4 ? 2 : 1, lds = Q <= 4 ? (Q == 3 ? 6 : 8) : 2; };
+
+// psi read from a vector over the nodes through the element's node list
+template <int Q, typename NodeF>
+struct NodePsi {
+  const int* en;
+  NodeF f;
+  __device__ __forceinline__ double operator()(const Visit<Q>& v, int c) const { return f(en[(long long)v.el * Q + c]); }
+};
+template <int Q, typename NodeF>
+__device__ __forceinline__ NodePsi<Q, NodeF> node_psi(const MeshDev& m, NodeF f) {
+  return NodePsi<Q, NodeF>{m.elem_nodes, f};
 }
 
-template <typename PsiF>
-__device__ __forceinline__ double node_psi3(const MeshDev& m, int i, PsiF psi) {
-  if (m.degree == 2) return m.dim == 2 ? node_psi3_p2<6>(m, i, psi) : node_psi3_p2<10>(m, i, psi);
-  double acc = 0.0;
-  const double cm = cm_of(m.dim);
-  const int t0 = m.nd_el_ptr[i], t1 = m.nd_el_ptr[i + 1];
-  for (int t = t0; t < t1; t += PFC_EVN) {
-    int pk[PFC_EVN];
+// f(table) once per local index a present among the lanes, on the lanes that
+// have it, with the table of that index at a wave-uniform address (the tables
+// are then read through the scalar cache; on the meshes met in practice the rows
+// of a slice have the same local index at the same visit)
+template <typename F>
+__device__ __forceinline__ void per_local_index(const double* tab, int stride, int a, F f) {
+  unsigned long long todo = __ballot(1);
+  while (todo) {
+    const int au = __builtin_amdgcn_readlane(a, __ffsll((long long)todo) - 1);
+    const bool mine = a == au;
+    const unsigned long long base = (unsigned long long)(tab + au * stride);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)base);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(base >> 32));
+    if (mine) f((const __attribute__((address_space(4))) double*)(((unsigned long long)hi << 32) | lo));
+    todo &= ~__ballot(mine);
+  }
+}
+
+// Sums of a row's entries in LDS: entry k of entries [s0, s0 + c) at acc[(k - s0) st]
+// (ALL: of all entries, s0 = 0); add: entry of local node b += x[b] y[b].  The positions of a simplex's nodes differ, so
+// its Q sums are read together before any is written.
+template <bool ALL>
+struct RowAcc {
+  double* acc;
+  int st, s0, c;
+  template <int Q>
+  __device__ __forceinline__ void add(const Visit<Q>& v, const double* x, const double* y) const {
+    if constexpr (ALL) {
+      double t[Q];
+      int s[Q];
 #pragma unroll
-    for (int u = 0; u < PFC_EVN; ++u) pk[u] = m.nd_el[min(t + u, t1 - 1)];
-    double p[PFC_EVN][4], vol[PFC_EVN];
+      for (int b = 0; b < Q; ++b) { s[b] = v.slot(b) * st; t[b] = acc[s[b]]; }
 #pragma unroll
-    for (int u = 0; u < PFC_EVN; ++u) {
-      elem_psi4(m, pk[u] >> 2, psi, p[u]);
-      vol[u] = m.elem_vol[pk[u] >> 2];
-    }
+      for (int b = 0; b < Q; ++b) acc[s[b]] = fma(x[b], y[b], t[b]);
+    } else {
 #pragma unroll
-    for (int u = 0; u < PFC_EVN; ++u) {
-      if (t + u >= t1) break;
-      const int a = pk[u] & 3;
-      double S1 = 0.0, S2 = 0.0, S3 = 0.0;
-      for (int v = 0; v <= m.dim; ++v) { S1 += p[u][v]; S2 += p[u][v] * p[u][v]; S3 += p[u][v] * p[u][v] * p[u][v]; }
-      const double pa = p[u][a];
-      const double s = S1 * S1 * S1 + 3.0 * S1 * S2 + 2.0 * S3 + 3.0 * pa * (S1 * S1 + S2) + 6.0 * pa * pa * S1 + 6.0 * pa * pa * pa;
-      acc += vol[u] * cm * s;
+      for (int b = 0; b < Q; ++b) add1(v.slot(b), x[b], y[b]);
     }
   }
-  return acc;
+  __device__ __forceinline__ void add1(int pos, double x, double y) const {
+    const int k = pos - s0;
+    if (ALL || (unsigned)k < (unsigned)c) acc[k * st] = fma(x, y, acc[k * st]);
+  }
+};
+
+// the simplex's contributions to Mpsi2 between the node and each of its nodes
+template <int Q, typename Acc>
+__device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v, const Acc& acc) {
+  if constexpr (Q <= 4) {
+    const double cm = cm_of(Q - 1);
+    double S1 = 0.0, S2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 += v.p[c] * v.p[c]; }
+    double pa = v.p[0];
+#pragma unroll
+    for (int c = 1; c < Q; ++c) pa = v.a == c ? v.p[c] : pa;
+    double x[Q], y[Q];
+#pragma unroll
+    for (int b = 0; b < Q; ++b) {
+      const double pb = v.p[b];
+      x[b] = v.vol * cm * (v.a == b ? 2.0 : 1.0);
+      y[b] = S1 * S1 + S2 + 2.0 * S1 * (pa + pb) + 2.0 * (pa * pa + pb * pb + pa * pb);
+    }
+    acc.add(v, x, y);
+  } else {
+    constexpr int NP = Q * (Q + 1) / 2, W = Visit<Q>::W;
+    per_local_index(m.p2_C2, Q * NP, v.a, [&](auto C) {
+      unsigned pos[W];  // the positions, shifted by a byte per node (an index that varies would put them in memory)
+#pragma unroll
+      for (int w = 0; w < W; ++w) pos[w] = v.word[w];
+#pragma unroll 1
+      for (int b = 0; b < Q; ++b) {
+        double s = 0.0;
+        int q = b * NP;
+#pragma unroll
+        for (int c = 0; c < Q; ++c) {
+          double r = 0.0;
+#pragma unroll
+          for (int d = c; d < Q; ++d) r += C[q++] * v.p[d];
+          s += v.p[c] * r;
+        }
+        const int k = v.wide ? v.slot(b) : (int)(pos[0] & 255u);
+#pragma unroll
+        for (int w = 0; w < W; ++w) pos[w] = (pos[w] >> 8) | (w + 1 < W ? pos[w + 1] << 24 : 0u);
+        acc.add1(k, v.vol, s);
+      }
+    });
+  }
+}
+
+// the simplex's contribution to the cubic load of the node
+template <int Q>
+__device__ __forceinline__ double visit_psi3(const MeshDev& m, const Visit<Q>& v) {
+  if constexpr (Q <= 4) {
+    const double cm = cm_of(Q - 1);
+    double S1 = 0.0, S2 = 0.0, S3 = 0.0;
+#pragma unroll
+    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 += v.p[c] * v.p[c]; S3 += v.p[c] * v.p[c] * v.p[c]; }
+    double pa = v.p[0];
+#pragma unroll
+    for (int c = 1; c < Q; ++c) pa = v.a == c ? v.p[c] : pa;
+    const double s = S1 * S1 * S1 + 3.0 * S1 * S2 + 2.0 * S3 + 3.0 * pa * (S1 * S1 + S2) + 6.0 * pa * pa * S1 + 6.0 * pa * pa * pa;
+    return v.vol * cm * s;
+  } else {
+    constexpr int NT = Q * (Q + 1) * (Q + 2) / 6;
+    double s = 0.0;
+    per_local_index(m.p2_C3, NT, v.a, [&](auto C) {
+      int q = 0;
+#pragma unroll
+      for (int b = 0; b < Q; ++b) {
+        double r2 = 0.0;
+#pragma unroll
+        for (int c = b; c < Q; ++c) {
+          double r = 0.0;
+#pragma unroll
+          for (int d = c; d < Q; ++d) r += C[q++] * v.p[d];
+          r2 += v.p[c] * r;
+        }
+        s += v.p[b] * r2;
+      }
+    });
+    return v.vol * s;
+  }
+}
+
+// Row of a matrix of element sums: term(sums) visits the simplices of the row and
+// adds to its entries; the sums are held in LDS (acc[k * st], k < cap), in as many
+// rounds as the row needs (ALL: in one), and written by put(position, value).
+template <bool ALL, typename TermF, typename PutF>
+__device__ __forceinline__ void row_sums(double* acc, int st, int cap, int w, TermF term, PutF put) {
+  for (int s0 = 0; s0 < w; s0 += cap) {
+    const int c = min(cap, w - s0);
+    for (int k = 0; k < c; ++k) acc[k * st] = 0.0;
+    term(RowAcc<ALL>{acc, st, s0, c});
+    for (int k = 0; k < c; ++k) put(s0 + k, acc[k * st]);
+    if (ALL) break;
+  }
 }
 
 // ---- mobility matrices of the PFC1 model (Section 3) ---------------------------
@@ -357,57 +467,130 @@ __device__ __forceinline__ double elem_k(const MeshDev& m, int el, int a, int b)
   return m.elem_K[(long long)el * (k * (k + 1) / 2) + a * k - a * (a - 1) / 2 + (b - a)];
 }
 
-template <typename PsiF>
-__device__ __forceinline__ double entry_Kplus(const MeshDev& m, long long e, PsiF psi, double psi_min) {
-  double acc = 0.0;
-  const int k = m.dim + 1;
-  const double ik = 1.0 / k;
-  for (int t = m.sl_el_ptr[e]; t < m.sl_el_ptr[e + 1]; ++t) {
-    const int pk = m.sl_el[t];
-    const int el = pk >> 4, a = (pk >> 2) & 3, b = pk & 3;
-    const int* en = m.elem_nodes + (long long)el * k;
-    double s = 0.0;
-    for (int c = 0; c < k; ++c) s += psi(en[c]) - psi_min;
-    acc += s * ik * elem_k(m, el, a, b);
-  }
-  return acc;
+template <int Q, typename Acc>
+__device__ __forceinline__ void visit_Kplus(const MeshDev& m, const Visit<Q>& v, double psi_min, const Acc& acc) {
+  const double ik = 1.0 / Q;
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < Q; ++c) s += v.p[c] - psi_min;
+  double x[Q], y[Q];
+#pragma unroll
+  for (int b = 0; b < Q; ++b) { x[b] = s * ik; y[b] = elem_k(m, v.el, v.a, b); }
+  acc.add(v, x, y);
 }
 
-template <typename MuF>
-__device__ __forceinline__ double entry_F(const MeshDev& m, long long e, MuF mu) {
-  double acc = 0.0;
-  const int k = m.dim + 1;
-  const double ik = 1.0 / k;
-  for (int t = m.sl_el_ptr[e]; t < m.sl_el_ptr[e + 1]; ++t) {
-    const int pk = m.sl_el[t];
-    const int el = pk >> 4, a = (pk >> 2) & 3;
-    const int* en = m.elem_nodes + (long long)el * k;
-    double s = 0.0;
-    for (int c = 0; c < k; ++c) s += mu(en[c]) * elem_k(m, el, c, a);
-    acc += s * ik;
-  }
-  return acc;
+// v.p: mu at the simplex's nodes
+template <int Q, typename Acc>
+__device__ __forceinline__ void visit_F(const MeshDev& m, const Visit<Q>& v, const Acc& acc) {
+  const double ik = 1.0 / Q;
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < Q; ++c) s += v.p[c] * elem_k(m, v.el, c, v.a);
+  double x[Q], y[Q];
+#pragma unroll
+  for (int b = 0; b < Q; ++b) { x[b] = s; y[b] = ik; }
+  acc.add(v, x, y);
 }
 
-// (K_+(psi) mu)_i at node i, element by element (the stage right-hand side
-// needs it at the stage state, where no assembled K_+ exists)
-template <typename PsiF, typename MuF>
-__device__ __forceinline__ double node_Kplus_mu(const MeshDev& m, int i, PsiF psi, MuF mu, double psi_min) {
-  double acc = 0.0;
-  const int k = m.dim + 1;
-  const double ik = 1.0 / k;
-  for (int t = m.nd_el_ptr[i]; t < m.nd_el_ptr[i + 1]; ++t) {
-    const int pk = m.nd_el[t];
-    const int el = pk >> 2, a = pk & 3;
-    const int* en = m.elem_nodes + (long long)el * k;
-    double sp = 0.0, km = 0.0;
-    for (int c = 0; c < k; ++c) {
-      const int j = en[c];
-      sp += psi(j) - psi_min;
-      km += elem_k(m, el, a, c) * mu(j);
-    }
-    acc += sp * ik * km;
+// contribution to (K_+(psi) mu)_i of a simplex around node i (the stage
+// right-hand side needs it at the stage state, where no assembled K_+ exists);
+// mu(v, c): mu at its local node c
+template <int Q, typename MuF>
+__device__ __forceinline__ double visit_Kplus_mu(const MeshDev& m, const Visit<Q>& v, MuF mu, double psi_min) {
+  const double ik = 1.0 / Q;
+  double sp = 0.0, km = 0.0;
+#pragma unroll
+  for (int c = 0; c < Q; ++c) {
+    sp += v.p[c] - psi_min;
+    km += elem_k(m, v.el, v.a, c) * mu(v, c);
   }
+  return sp * ik * km;
+}
+
+// Columns of the rows of one slice for the mesh-level kernels: where every row
+// of the slice lies inside a periodic grid (no edge row), entry k's column is the
+// row plus one offset for the whole wave, so its index is not read and x at the
+// neighbours is a coalesced load; elsewhere the stored columns are read.
+// (pfc_spmv, 2D 1000^2: 35.1 -> 29.8 us per call)
+struct WaveCols {
+  const int* col;  // stored columns from the lane's first entry, or null
+  const int* off;  // offsets of the interior row class
+  int i;
+  __device__ __forceinline__ int at(int k) const { return col ? col[64LL * k] : i + off[k]; }
+};
+__device__ __forceinline__ WaveCols wave_cols(const MeshDev& m, int sl, int lane, long long e0) {
+  const int i = sl * 64 + lane, inner = m.dim == 2 ? 4 : 13;
+  const bool in = m.gN > 0 && i < m.n && grid_class(i, m.gN, m.gInv) == inner;
+  return WaveCols{__all(in) ? nullptr : m.col + e0, m.glin + inner * PFC_GRID_W, i};
+}
+
+// LDS of the mesh-level kernels with element sums (RowPlan)
+extern __shared__ double pfc_row_lds[];
+
+// f(integral_constant<Q>) for the mesh's nodes per simplex (ANY: the mesh may be P2, and have
+// long rows; else it is a P1 grid)
+template <bool ANY, typename F>
+__device__ __forceinline__ void with_nloc(const MeshDev& m, F f) {
+  if constexpr (ANY) {
+    if (m.nloc == 6) { f(std::integral_constant<int, 6>()); return; }
+    if (m.nloc == 10) { f(std::integral_constant<int, 10>()); return; }
+  }
+  if (m.dim == 2) f(std::integral_constant<int, 3>());
+  else f(std::integral_constant<int, 4>());
+}
+
+// int psi_h^3 phi_i at the row of (slice, lane), psi(node) from a functor
+template <bool ANY, typename PsiF>
+__device__ __forceinline__ double node_psi3(const MeshDev& m, int sl, int lane, PsiF psi) {
+  double g = 0.0;
+  with_nloc<ANY>(m, [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi),
+                                        [&](const Visit<Q>& v) { g += visit_psi3<Q>(m, v); });
+  });
+  return g;
+}
+
+// N(psi) = -3 Mpsi2 on the row of (slice, lane), put(position, value)
+template <bool ANY, typename PsiF, typename PutF>
+__device__ __forceinline__ void row_N(const MeshDev& m, int sl, int lane, double* acc, int st, int cap, int w,
+                                      PsiF psi, PutF put) {
+  with_nloc<ANY>(m, [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+      for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi),
+                                          [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
+    }, [&](int k, double x) { put(k, -3.0 * x); });
+  });
+}
+
+// K_+(psi) and F(mu) on the row of (slice, lane) (PFC1: P1 meshes)
+template <bool ANY, typename PsiF, typename MuF, typename PutF, typename PutG>
+__device__ __forceinline__ void row_mob(const MeshDev& m, int sl, int lane, double* acc, int st, int cap, int w,
+                                        PsiF psi, MuF mu, double psi_min, PutF put_k, PutG put_f) {
+  with_nloc<false>(m, [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+      for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi),
+                                          [&](const Visit<Q>& v) { visit_Kplus<Q>(m, v, psi_min, sums); });
+    }, put_k);
+    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+      for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, mu),
+                                          [&](const Visit<Q>& v) { visit_F<Q>(m, v, sums); });
+    }, put_f);
+  });
+}
+
+// (K_+(psi) mu)_i at the row of (slice, lane) (PFC1: P1 meshes)
+template <bool ANY, typename PsiF, typename MuF>
+__device__ __forceinline__ double node_Kplus_mu(const MeshDev& m, int sl, int lane, PsiF psi, MuF mu, double psi_min) {
+  double acc = 0.0;
+  with_nloc<false>(m, [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi), [&](const Visit<Q>& v) {
+      acc += visit_Kplus_mu<Q>(m, v, node_psi<Q>(m, mu), psi_min);
+    });
+  });
   return acc;
 }
 
@@ -422,17 +605,14 @@ __device__ __forceinline__ Red3 ph_rb_begin(const InstDev& I, const Team& tm) {
   auto psi = [&](int j) { return xk[n + j]; };
   const PatView<L> pv = p1_pat<L>(I, tm);
   PFC_SLICES(I, tm) {
-    const int base = pv.base(sl);
-    const int w = pv.width(sl);
-    const int lane = tm.lane;
-    for (int k = 0; k < w; ++k) {
-      const long long e = (long long)base + k * 64 + lane;
-      I.N[e] = -3.0 * entry_Mpsi2(I.m, e, psi);
-      if (I.model == PFC_MODEL_PFC1) {
-        I.Kp[e] = entry_Kplus(I.m, e, psi, I.psi_min);
-        I.Fm[e] = entry_F(I.m, e, [&](int j) { return xk[j]; });
-      }
-    }
+    const int lane = tm.lane, w = pv.width(sl);
+    const long long e0 = (long long)pv.base(sl) + lane;
+    double* acc = pfc_ss + threadIdx.x;
+    constexpr int cap = PFC_SS_LDS / PFC_WG;
+    row_N<L != PFC_COL_GRID>(I.m, sl, lane, acc, PFC_WG, cap, w, psi, [&](int k, double x) { I.N[e0 + 64LL * k] = x; });
+    if (I.model == PFC_MODEL_PFC1)
+      row_mob<L != PFC_COL_GRID>(I.m, sl, lane, acc, PFC_WG, cap, w, psi, [&](int j) { return xk[j]; }, I.psi_min,
+              [&](int k, double x) { I.Kp[e0 + 64LL * k] = x; }, [&](int k, double x) { I.Fm[e0 + 64LL * k] = x; });
   }
   return red3(0.0, 0.0);
 }
@@ -446,45 +626,57 @@ __device__ __forceinline__ double stage_comb(const InstDev& I, int stage, int bl
   return v;
 }
 
-// Stage right-hand side at the row of (slice, lane) (Section 3.1): F(x_i) with
-// block 1 multiplied by tau, plus sum_j c_ij M y_j^psi on block 1, with the
-// stage state x_i = x_k + sum_j a_ij y_j formed on the fly.
-template <int L>
-__device__ __forceinline__ void stage_rhs_row(const InstDev& I, const PatView<L>& pv, int sl, int lane, int stage,
-                                              double& b0, double& b1, double& b2) {
+// Stage right-hand side at a row (Section 3.1): F(x_i) with block 1 multiplied by
+// tau, plus sum_j c_ij M y_j^psi on block 1, with the stage state
+// x_i = x_k + sum_j a_ij y_j formed on the fly.  The products with M and K over
+// the row's w entries (entry k at position pos(k) of the values, column col(k));
+// seen(k, mu, psi) is told the stage state there.
+template <typename PosF, typename ColF, typename SeenF>
+__device__ __forceinline__ void stage_rhs_products(const InstDev& I, int w, int stage, PosF pos, ColF col, SeenF seen,
+                                                   double& b0, double& b1, double& b2) {
   const int n = I.n;
-  const int i = sl * 64 + lane;
-  const int base = pv.base(sl);
-  const int w = pv.width(sl);
   double sMmu = 0, sMps = 0, sMom = 0, sKmu = 0, sKps = 0, sKom = 0, sMy1 = 0, sMy2 = 0;
   const long long n3 = 3LL * n;
   for (int k = 0; k < w; ++k) {
-    const long long e = (long long)base + k * 64 + lane;
-    const int j = pv.at(e, i);
+    const long long e = pos(k);
+    const int j = col(k);
     const double Mv = I.m.M[e], Kv = I.m.K[e];
     const double mu = stage_comb(I, stage, 0, j);
     const double ps = stage_comb(I, stage, 1, j);
     const double om = stage_comb(I, stage, 2, j);
+    seen(k, mu, ps);
     sMmu += Mv * mu; sMps += Mv * ps; sMom += Mv * om;
     sKmu += Kv * mu; sKps += Kv * ps; sKom += Kv * om;
     if (stage >= 2) sMy1 += Mv * I.ys[n + j];
     if (stage >= 3) sMy2 += Mv * I.ys[n3 + n + j];
   }
-  double g = 0.0;
-  if (i < n) g = node_psi3(I.m, i, [&](int j) { return stage_comb(I, stage, 1, j); });
-  b0 = -sMmu + (1.0 + I.r) * sMps - 2.0 * sKps - sKom + g;
-  if (I.model == PFC_MODEL_PFC1) {  // -tau K_+(psi_i) mu_i
-    double kpm = 0.0;
-    if (i < n)
-      kpm = node_Kplus_mu(I.m, i, [&](int j) { return stage_comb(I, stage, 1, j); },
-                          [&](int j) { return stage_comb(I, stage, 0, j); }, I.psi_min);
-    b1 = I.tau * (-kpm);
-  } else {
-    b1 = I.tau * (-sKmu);
-  }
+  b0 = -sMmu + (1.0 + I.r) * sMps - 2.0 * sKps - sKom;
+  // block 1 up to its mobility term: the products' part, and for PFC2 -tau K mu
+  b1 = I.model == PFC_MODEL_PFC1 ? 0.0 : I.tau * (-sKmu);
   if (stage == 2) b1 += ROS_C21 * sMy1;
   if (stage == 3) b1 += ROS_C31 * sMy1 + ROS_C32 * sMy2;
   b2 = -sMom - sKps;
+}
+
+// ... and the element sums: the cubic load g and, for PFC1, -tau K_+(psi_i) mu_i
+__device__ __forceinline__ void stage_rhs_finish(const InstDev& I, double g, double kpm, double& b0, double& b1) {
+  b0 += g;
+  if (I.model == PFC_MODEL_PFC1) b1 += I.tau * (-kpm);
+}
+
+template <int L>
+__device__ __forceinline__ void stage_rhs_row(const InstDev& I, const PatView<L>& pv, int sl, int lane, int stage,
+                                              double& b0, double& b1, double& b2) {
+  const long long e0 = (long long)pv.base(sl) + lane;
+  const int i = sl * 64 + lane;
+  stage_rhs_products(I, pv.width(sl), stage, [&](int k) { return e0 + 64LL * k; },
+                     [&](int k) { return pv.at(e0 + 64LL * k, i); }, [](int, double, double) {}, b0, b1, b2);
+  auto psi = [&](int j) { return stage_comb(I, stage, 1, j); };
+  const double g = node_psi3<L != PFC_COL_GRID>(I.m, sl, lane, psi);
+  double kpm = 0.0;
+  if (I.model == PFC_MODEL_PFC1)
+    kpm = node_Kplus_mu<L != PFC_COL_GRID>(I.m, sl, lane, psi, [&](int j) { return stage_comb(I, stage, 0, j); }, I.psi_min);
+  stage_rhs_finish(I, g, kpm, b0, b1);
 }
 
 // Right-hand side of the solve: stage rhs b_i^R for job RB, the caller's rhs
@@ -685,10 +877,8 @@ __device__ __forceinline__ Red3 ph_pcg_setup(const InstDev& I, const State& S, c
           sKp += I.m.K[e] * I.xk[n + j];
           sKo += I.m.K[e] * I.xk[2 * n + j];
         }
-        if (i < n) {
-          auto psi = [&](int j) { return I.xk[n + j]; };
-          rhs = (1.0 + I.r) * sMp - 2.0 * sKp - sKo + node_psi3(I.m, i, psi);
-        }
+        rhs = (1.0 + I.r) * sMp - 2.0 * sKp - sKo +
+              node_psi3<L != PFC_COL_GRID>(I.m, sl, lane, [&](int j) { return I.xk[n + j]; });
       } break;
     }
     if (i < n) {
@@ -957,11 +1147,9 @@ __device__ __forceinline__ Red3 ph_cg_iter(const InstDev& I, const State& S, con
 // steps around them, keeps them in LDS, and applies T there: Tp on the rows one
 // step around, T^2 p and Tu on its own rows.  The halo is a contiguous range of
 // rows (mod n) on 2D periodic grids, whose neighbours lie within N + 1 rows.
-#define PFC_SS_LDS 8192
 #define PFC_SS_NG 26  // 15 entries of G, 10 of H, and ||b||^2 in the first launch of a solve
 #define PFC_SS_NA 4   // passes of a workgroup over the two-step halo (R + 4H <= 4096 rows)
 #define PFC_SS_NB 3   // passes over the one-step halo (R + 2H <= 3072 rows); 7 entries per row
-__shared__ double pfc_ss[PFC_SS_LDS];
 __shared__ double pfc_ssred[64 * 32];
 #ifdef PFC_TICK_TIMING
 __shared__ unsigned long long pfc_sst[6];  // optional instrumentation (separate build only)

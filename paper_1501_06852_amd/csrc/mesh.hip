@@ -74,53 +74,63 @@ __global__ void k_elem_geom(int dim, int n_elem, const double* __restrict__ X, d
     for (int c = 0; c < dim; ++c) grad[((long long)e * k + a) * dim + c] = g[a][c];
 }
 
+// Simplices around each row of a slice, with what the set-up assembly needs of them
+template <int Q, typename F>
+__device__ __forceinline__ void set_up_visits(const MeshDev& m, int sl, int lane, F f) {
+  for_visits<Q, 1, true, true>(m, sl, lane, [](const Visit<Q>&, int) { return 0.0; }, f);
+}
+
 // M_ij = sum_T |T| (1 + [a==b]) / ((m+1)(m+2)),  K_ij = sum_T |T| grad lambda_a . grad lambda_b,
-// gathered per stored entry over its element list (deterministic, no atomics).
-__global__ void k_assemble_MK(MeshDev m, const double* __restrict__ grad, double* __restrict__ M,
-                              double* __restrict__ K) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= m.nnz_sell) return;
-  const int k = m.dim + 1;
+// summed per row over the simplices around its node (deterministic, no atomics).
+template <int Q>
+__global__ void k_assemble_MK(MeshDev m, const double* __restrict__ grad, double* M, double* K) {
+  const int sl = blockIdx.x * PFC_WAVES + (threadIdx.x >> 6);
+  if (sl >= m.n_slices) return;
+  const int lane = threadIdx.x & 63;
+  const long long e0 = (long long)m.slice_ptr[sl] + lane;
+  const int w = (m.slice_ptr[sl + 1] - m.slice_ptr[sl]) >> 6;
+  for (int k = 0; k < w; ++k) M[e0 + 64LL * k] = K[e0 + 64LL * k] = 0.0;
   const double cmass = 1.0 / ((m.dim + 1.0) * (m.dim + 2.0));
-  double mv = 0.0, kv = 0.0;
-  for (int t = m.sl_el_ptr[e]; t < m.sl_el_ptr[e + 1]; ++t) {
-    const int pk = m.sl_el[t];
-    const int el = pk >> 4, a = (pk >> 2) & 3, b = pk & 3;
-    const double v = m.elem_vol[el];
-    mv += v * cmass * (a == b ? 2.0 : 1.0);
-    double d = 0.0;
-    for (int c = 0; c < m.dim; ++c) d += grad[((long long)el * k + a) * m.dim + c] * grad[((long long)el * k + b) * m.dim + c];
-    kv += v * d;
-  }
-  M[e] = mv;
-  K[e] = kv;
+  set_up_visits<Q>(m, sl, lane, [&](const Visit<Q>& v) {
+#pragma unroll
+    for (int b = 0; b < Q; ++b) {
+      double d = 0.0;
+      for (int c = 0; c < m.dim; ++c)
+        d += grad[((long long)v.el * Q + v.a) * m.dim + c] * grad[((long long)v.el * Q + b) * m.dim + c];
+      const long long e = e0 + 64LL * v.slot(b);
+      M[e] += v.vol * cmass * (v.a == b ? 2.0 : 1.0);
+      K[e] += v.vol * d;
+    }
+  });
 }
 
 // P2: M_ij = sum_T |T| M2[a][b],  K_ij = sum_T |T| sum_{s,t} (grad l_s . grad l_t) D[s][t][a][b]
 // with the reference tables of the quadratic basis (Section 3, p = 2).
-__global__ void k_assemble_MK_p2(MeshDev m, const double* __restrict__ grad, double* __restrict__ M,
-                                 double* __restrict__ K) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= m.nnz_sell) return;
-  const int k = m.dim + 1, q = m.nloc;
-  double mv = 0.0, kv = 0.0;
-  for (int t = m.sl_el_ptr[e]; t < m.sl_el_ptr[e + 1]; ++t) {
-    const int pk = m.sl_el[t];
-    const int el = pk >> 8, a = (pk >> 4) & 15, b = pk & 15;
-    const double v = m.elem_vol[el];
-    mv += v * m.p2_M2[a * q + b];
-    double kk = 0.0;
-    for (int s = 0; s < k; ++s)
-      for (int u = 0; u < k; ++u) {
-        double g = 0.0;
-        for (int c = 0; c < m.dim; ++c)
-          g += grad[((long long)el * k + s) * m.dim + c] * grad[((long long)el * k + u) * m.dim + c];
-        kk += g * m.p2_D[((s * k + u) * q + a) * q + b];
-      }
-    kv += v * kk;
-  }
-  M[e] = mv;
-  K[e] = kv;
+template <int Q>
+__global__ void k_assemble_MK_p2(MeshDev m, const double* __restrict__ grad, double* M, double* K) {
+  const int sl = blockIdx.x * PFC_WAVES + (threadIdx.x >> 6);
+  if (sl >= m.n_slices) return;
+  const int lane = threadIdx.x & 63;
+  const long long e0 = (long long)m.slice_ptr[sl] + lane;
+  const int w = (m.slice_ptr[sl + 1] - m.slice_ptr[sl]) >> 6;
+  for (int k = 0; k < w; ++k) M[e0 + 64LL * k] = K[e0 + 64LL * k] = 0.0;
+  const int kv = m.dim + 1;
+  set_up_visits<Q>(m, sl, lane, [&](const Visit<Q>& v) {
+#pragma unroll
+    for (int b = 0; b < Q; ++b) {
+      double kk = 0.0;
+      for (int s = 0; s < kv; ++s)
+        for (int u = 0; u < kv; ++u) {
+          double g = 0.0;
+          for (int c = 0; c < m.dim; ++c)
+            g += grad[((long long)v.el * kv + s) * m.dim + c] * grad[((long long)v.el * kv + u) * m.dim + c];
+          kk += g * m.p2_D[((s * kv + u) * Q + v.a) * Q + b];
+        }
+      const long long e = e0 + 64LL * v.slot(b);
+      M[e] += v.vol * m.p2_M2[v.a * Q + b];
+      K[e] += v.vol * kk;
+    }
+  });
 }
 
 // Element stiffness |T| grad lambda_a . grad lambda_b, upper triangle a <= b in
@@ -161,32 +171,170 @@ __global__ void k_mesh_derived(MeshDev m, const double* __restrict__ M, const do
   }
 }
 
-__global__ void k_spmv(MeshDev m, const double* __restrict__ A, const double* __restrict__ x, double* __restrict__ y) {
-  const int sl = blockIdx.x * PFC_WAVES + (threadIdx.x >> 6);
+__global__ __launch_bounds__(PFC_ROW_T) void k_spmv(MeshDev m, const double* __restrict__ A,
+                                                    const double* __restrict__ x, double* __restrict__ y) {
+  const int sl = xcd_rank(blockIdx.x, gridDim.x) * (PFC_ROW_T / 64) + (threadIdx.x >> 6);
   if (sl >= m.n_slices) return;
   const int lane = threadIdx.x & 63;
   const int i = sl * 64 + lane;
   const int base = m.slice_ptr[sl];
   const int w = (m.slice_ptr[sl + 1] - base) >> 6;
+  const long long e0 = (long long)base + lane;
+  const WaveCols wc = wave_cols(m, sl, lane, e0);
   double acc = 0.0;
-  for (int k = 0; k < w; ++k) {
-    const long long e = (long long)base + k * 64 + lane;
-    acc += A[e] * x[m.col[e]];
-  }
+  for_width(w, [&](int k) { acc += A[e0 + 64LL * k] * x[wc.at(k)]; });
   if (i < m.n) y[i] = acc;
 }
 
-__global__ void k_assemble_N_csr(MeshDev m, const long long* __restrict__ csr2sell, int nnz,
-                                 const double* __restrict__ psi, double* __restrict__ N) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nnz) return;
-  N[s] = -3.0 * entry_Mpsi2(m, csr2sell[s], [&](int j) { return psi[j]; });
+// Element sums on their own (N(psi), the cubic load, and below the operator apply
+// and the stage right-hand side that contain them).  STAGE: psi at the row's
+// neighbours is gathered once into LDS (sp[k * st], position k of the row), and
+// every visit reads it there; otherwise (rows too long for that) each visit
+// gathers it through the element's nodes.  st = threads + 1, so that reading a
+// row's sums back along the row has no bank conflicts.
+
+template <int Q, bool STAGE, typename F>
+__device__ __forceinline__ void row_visits(const MeshDev& m, int sl, int lane, const double* psi, const double* sp, int st,
+                                           F f) {
+  if constexpr (STAGE)
+    for_visits<Q, VisitU<Q>::lds, false, false>(m, sl, lane, [=](const Visit<Q>& v, int c) { return sp[v.slot(c) * st]; }, f);
+  else
+    for_visits<Q, VisitU<Q>::mem, true, true>(m, sl, lane, node_psi<Q>(m, [=](int j) { return psi[j]; }), f);
 }
 
-__global__ void k_load_psi3(MeshDev m, const double* __restrict__ psi, double* __restrict__ g) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m.n) return;
-  g[i] = node_psi3(m, i, [&](int j) { return psi[j]; });
+// N(psi) = -3 Mpsi2, in the mesh's layout (row_ptr null) or in CSR order.
+template <int Q, bool STAGE>
+__global__ __launch_bounds__(PFC_ROW_T) void k_row_N(MeshDev m, const double* __restrict__ psi, double* __restrict__ out,
+                                                     const int* __restrict__ row_ptr, int cap) {
+  const int T = blockDim.x, tid = threadIdx.x, st = T + 1;
+  const int rank = xcd_rank(blockIdx.x, gridDim.x);
+  const int sl = rank * (T >> 6) + (tid >> 6), lane = tid & 63, i = sl * 64 + lane;
+  double* acc = pfc_row_lds + tid;
+  double* sp = acc + cap * st;
+  if (sl < m.n_slices) {
+    const int base = m.slice_ptr[sl], w = (m.slice_ptr[sl + 1] - base) >> 6;
+    const long long e0 = (long long)base + lane;
+    if constexpr (STAGE) {
+      const WaveCols wc = wave_cols(m, sl, lane, e0);
+      for_width(w, [&](int k) { sp[k * st] = psi[wc.at(k)]; });
+    }
+    const int o = row_ptr && i < m.n ? row_ptr[i] : 0, len = row_ptr ? (i < m.n ? row_ptr[i + 1] - o : 0) : w;
+    row_sums<STAGE>(acc, st, cap, w, [&](auto sums) {
+      row_visits<Q, STAGE>(m, sl, lane, psi, sp, st, [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
+    }, [&](int k, double x) {
+      x *= -3.0;
+      if (!row_ptr) out[e0 + 64LL * k] = x;
+      else if (STAGE) acc[k * st] = x;  // stored along the rows below
+      else if (k < len) out[o + k] = x;
+    });
+  }
+  if (!STAGE || !row_ptr) return;
+  __syncthreads();
+  const int r0 = rank * T, r1 = min(r0 + T, m.n);
+  if (r0 >= r1) return;
+  const int b0 = row_ptr[r0], nb = row_ptr[r1] - b0;
+  const float iz = m.zrow ? 1.0f / (float)m.zrow : 0.0f;
+  for (int q = tid; q < nb; q += T) {
+    int r;
+    if (m.zrow) {
+      r = grid_div(q, iz);
+    } else {  // the last row that begins at or before q
+      int hi = r1 - r0;
+      r = 0;
+      while (hi - r > 1) {
+        const int mid = (r + hi) >> 1;
+        if (row_ptr[r0 + mid] - b0 <= q) r = mid;
+        else hi = mid;
+      }
+    }
+    const int k = m.zrow ? q - r * m.zrow : q - (row_ptr[r0 + r] - b0);
+    out[b0 + q] = pfc_row_lds[k * st + r];
+  }
+}
+
+template <int Q, bool STAGE>
+__global__ __launch_bounds__(PFC_ROW_T) void k_row_psi3(MeshDev m, const double* __restrict__ psi, double* __restrict__ g) {
+  const int T = blockDim.x, tid = threadIdx.x, st = T + 1;
+  const int sl = xcd_rank(blockIdx.x, gridDim.x) * (T >> 6) + (tid >> 6), lane = tid & 63, i = sl * 64 + lane;
+  if (sl >= m.n_slices) return;
+  double* sp = pfc_row_lds + tid;
+  if constexpr (STAGE) {
+    const int base = m.slice_ptr[sl], w = (m.slice_ptr[sl + 1] - base) >> 6;
+    const long long e0 = (long long)base + lane;
+    const WaveCols wc = wave_cols(m, sl, lane, e0);
+    for_width(w, [&](int k) { sp[k * st] = psi[wc.at(k)]; });
+  }
+  double s = 0.0;
+  row_visits<Q, STAGE>(m, sl, lane, psi, sp, st, [&](const Visit<Q>& v) { s += visit_psi3<Q>(m, v); });
+  if (i < m.n) g[i] = s;
+}
+
+// A^R y (PFC2) with N(psi_k) formed row by row in LDS instead of in memory.
+template <int Q>
+__global__ __launch_bounds__(PFC_ROW_T) void k_row_AR(MeshDev m, const double* __restrict__ psi, double r, double t,
+                                                      double s, const double* __restrict__ y, double* __restrict__ out,
+                                                      int cap) {
+  const int T = blockDim.x, tid = threadIdx.x, st = T + 1, n = m.n;
+  const int sl = xcd_rank(blockIdx.x, gridDim.x) * (T >> 6) + (tid >> 6), lane = tid & 63, i = sl * 64 + lane;
+  if (sl >= m.n_slices) return;
+  double* acc = pfc_row_lds + tid;
+  double* sp = acc + cap * st;
+  const int base = m.slice_ptr[sl], w = (m.slice_ptr[sl + 1] - base) >> 6;
+  const long long e0 = (long long)base + lane;
+  const WaveCols wc = wave_cols(m, sl, lane, e0);
+  for_width(w, [&](int k) { sp[k * st] = psi[wc.at(k)]; });
+  row_sums<true>(acc, st, cap, w, [&](auto sums) {
+    row_visits<Q, true>(m, sl, lane, psi, sp, st, [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
+  }, [](int, double) {});
+  const double c1 = -(1.0 + r);
+  double w0 = 0.0, w1 = 0.0, w2 = 0.0;
+  for_width(w, [&](int k) {
+    const int j = wc.at(k);
+    const double Mv = m.M[e0 + 64LL * k], Kv = m.K[e0 + 64LL * k], Nv = -3.0 * acc[k * st];
+    const double mu = y[j], ps = y[n + j], om = y[2 * n + j];
+    w0 += Mv * mu + (c1 * Mv + 2.0 * Kv + Nv) * ps + Kv * om;
+    w1 += t * Kv * mu + s * Mv * ps;
+    w2 += Kv * ps + Mv * om;
+  });
+  if (i < n) { out[i] = w0; out[n + i] = w1; out[2 * n + i] = w2; }
+}
+
+int launch_row_N(const pfc_mesh* m, const double* psi, double* out, bool csr, hipStream_t s) {
+  const RowPlan p = row_plan(m, 2);
+  const int* rp = csr ? m->d_row_ptr : nullptr;
+#define PFC_X(Q)                                                                                                      \
+  if (p.stage) hipLaunchKernelGGL((k_row_N<Q, true>), row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, out, rp, \
+                                  p.cap);                                                                             \
+  else hipLaunchKernelGGL((k_row_N<Q, false>), row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, out, rp, p.cap)
+  PFC_FOR_NLOC(m, PFC_X)
+#undef PFC_X
+  PFC_HIP(hipGetLastError());
+  return PFC_OK;
+}
+
+static int launch_row_psi3(const pfc_mesh* m, const double* psi, double* g, hipStream_t s) {
+  const RowPlan p = row_plan(m, 1);
+  const size_t lds = p.stage ? p.lds(1) : 0;
+#define PFC_X(Q)                                                                                                   \
+  if (p.stage) hipLaunchKernelGGL((k_row_psi3<Q, true>), row_grid(m, p.T), dim3(p.T), lds, s, m->dev, psi, g);     \
+  else hipLaunchKernelGGL((k_row_psi3<Q, false>), row_grid(m, p.T), dim3(p.T), lds, s, m->dev, psi, g)
+  PFC_FOR_NLOC(m, PFC_X)
+#undef PFC_X
+  PFC_HIP(hipGetLastError());
+  return PFC_OK;
+}
+
+bool row_AR_applies(const pfc_mesh* m) { return !m->dev.nv_wide; }
+
+int launch_row_AR(const pfc_mesh* m, const double* psi, double r, double tau, double m11, const double* y, double* out,
+                  hipStream_t s) {
+  const RowPlan p = row_plan(m, 2);
+#define PFC_X(Q) \
+  hipLaunchKernelGGL((k_row_AR<Q>), row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, r, tau, m11, y, out, p.cap)
+  PFC_FOR_NLOC(m, PFC_X)
+#undef PFC_X
+  PFC_HIP(hipGetLastError());
+  return PFC_OK;
 }
 
 // ---- host construction ---------------------------------------------------------
@@ -203,7 +351,7 @@ static int upload(T** dst, const T* src, size_t count) {
 static void mesh_free(pfc_mesh* m) {
   if (!m) return;
   void* ptrs[] = {m->d_slice_ptr, m->d_col, m->d_M, m->d_K, m->d_Mf, m->d_Kf, m->d_dinvM, m->d_dinvMf,
-                  m->d_sl_el_ptr, m->d_sl_el, m->d_nd_el_ptr, m->d_nd_el, m->d_elem_nodes, m->d_vol, m->d_csr2sell,
+                  m->d_nv_ptr, m->d_nv_el, m->d_nv_slot, m->d_row_ptr, m->d_elem_nodes, m->d_vol,
                   m->d_w_slice_ptr, m->d_w_col, m->d_w_p1pos, m->d_w_tri_ptr, m->d_w_tri, m->d_elemK, m->d_p2tab};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -348,7 +496,7 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
   int gN = 0;
   std::vector<int> glin;
 #ifndef PFC_NO_GRID_COLUMNS
-  if (m->uniform_width > 0 && !detect_grid(m, m->uniform_width, gN, glin)) gN = 0;
+  if (m->degree == 1 && m->uniform_width > 0 && !detect_grid(m, m->uniform_width, gN, glin)) gN = 0;
 #endif
   std::vector<int> scol((size_t)m->nnz_sell);
   m->csr2sell.assign(m->nnz, 0);
@@ -368,41 +516,56 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
       }
     }
   }
-  // element contributions of each stored entry, in element order
-  std::vector<int> cnt((size_t)m->nnz_sell + 1, 0);
-  std::vector<long long> pos_of_pair((size_t)m->n_elem * k * k);
-  for (long long e = 0; e < m->n_elem; ++e)
-    for (int a = 0; a < k; ++a)
-      for (int b = 0; b < k; ++b) {
-        const int s = slot_of(m, en[e * k + a], en[e * k + b]);
-        if (s < 0) {
+  // simplices around each node, in element order, and the positions of their
+  // nodes in the node's row
+  int zmax = 0, zrow = m->row_ptr[1] - m->row_ptr[0];
+  for (int i = 0; i < n; ++i) {
+    const int z = m->row_ptr[i + 1] - m->row_ptr[i];
+    zmax = std::max(zmax, z);
+    if (z != zrow) zrow = 0;
+  }
+  const bool wide = zmax > PFC_ROW_MAX;
+  const int words = wide ? k : (k + 3) / 4;
+  std::vector<long long> vptr((size_t)m->n_slices + 1, 0);
+  for (int s = 0; s < m->n_slices; ++s) {
+    int w = 0;
+    for (int i = s * 64; i < std::min(n, s * 64 + 64); ++i) w = std::max(w, ndp[i + 1] - ndp[i]);
+    vptr[s + 1] = vptr[s] + 64LL * w;
+  }
+  const size_t nv = (size_t)vptr[m->n_slices];
+  std::vector<int> vel(nv, -1);
+  std::vector<unsigned> vslot(nv * words, 0u);
+  std::vector<int> at(n, -1), of(n, -1);  // position of a column in the row `of`
+  for (int i = 0; i < n; ++i) {
+    for (int t = m->row_ptr[i]; t < m->row_ptr[i + 1]; ++t) {
+      at[m->col_idx[t]] = t - m->row_ptr[i];
+      of[m->col_idx[t]] = i;
+    }
+    const long long vb = vptr[i / 64];
+    const int lane = i & 63;
+    for (int t = ndp[i]; t < ndp[i + 1]; ++t) {
+      const int q = t - ndp[i], e = ndl[t] >> bits;
+      vel[vb + 64LL * q + lane] = ndl[t];
+      unsigned* sw = vslot.data() + vb * words + lane;
+      for (int c = 0; c < k; ++c) {
+        const int j = en[(long long)e * k + c];
+        if (of[j] != i) {
           set_error("element " + std::to_string(e) + " has a node pair missing from the pattern");
           return PFC_ERR_ARG;
         }
-        const long long p = m->csr2sell[s];
-        pos_of_pair[(e * k + a) * k + b] = p;
-        cnt[p + 1]++;
+        if (wide) sw[64LL * ((long long)words * q + c)] = (unsigned)at[j];
+        else sw[64LL * ((long long)words * q + c / 4)] |= (unsigned)at[j] << (8 * (c & 3));
       }
-  for (long long p = 0; p < m->nnz_sell; ++p) cnt[p + 1] += cnt[p];
-  if ((long long)cnt[m->nnz_sell] != (long long)m->n_elem * k * k) {
-    set_error("internal: element list size mismatch");
-    return PFC_ERR_STATE;
+    }
   }
-  std::vector<int> lst((size_t)m->n_elem * k * k);
-  std::vector<int> fill(cnt.begin(), cnt.end() - 1);
-  for (long long e = 0; e < m->n_elem; ++e)
-    for (int a = 0; a < k; ++a)
-      for (int b = 0; b < k; ++b)
-        lst[fill[pos_of_pair[(e * k + a) * k + b]]++] = (int)((e << (2 * bits)) | (a << bits) | b);
   int rc;
   if ((rc = upload(&m->d_slice_ptr, sptr.data(), sptr.size()))) return rc;
   if ((rc = upload(&m->d_col, scol.data(), scol.size()))) return rc;
-  if ((rc = upload(&m->d_sl_el_ptr, cnt.data(), cnt.size()))) return rc;
-  if ((rc = upload(&m->d_sl_el, lst.data(), lst.size()))) return rc;
-  if ((rc = upload(&m->d_nd_el_ptr, ndp.data(), ndp.size()))) return rc;
-  if ((rc = upload(&m->d_nd_el, ndl.data(), ndl.size()))) return rc;
+  if ((rc = upload(&m->d_nv_ptr, vptr.data(), vptr.size()))) return rc;
+  if ((rc = upload(&m->d_nv_el, vel.data(), vel.size()))) return rc;
+  if ((rc = upload(&m->d_nv_slot, vslot.data(), vslot.size()))) return rc;
+  if ((rc = upload(&m->d_row_ptr, m->row_ptr.data(), m->row_ptr.size()))) return rc;
   if ((rc = upload(&m->d_elem_nodes, en, (size_t)m->n_elem * k))) return rc;
-  if ((rc = upload(&m->d_csr2sell, m->csr2sell.data(), m->csr2sell.size()))) return rc;
   if ((rc = upload<double>(&m->d_M, nullptr, m->nnz_sell))) return rc;
   if ((rc = upload<double>(&m->d_K, nullptr, m->nnz_sell))) return rc;
   if ((rc = upload<float>(&m->d_Mf, nullptr, m->nnz_sell))) return rc;
@@ -413,7 +576,9 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
   d.n = n; d.dim = m->dim; d.n_slices = m->n_slices; d.n_elem = m->n_elem; d.nnz_sell = m->nnz_sell;
   d.uw = m->uniform_width;
   d.slice_ptr = m->d_slice_ptr; d.col = m->d_col; d.M = m->d_M; d.K = m->d_K; d.Mf = m->d_Mf; d.Kf = m->d_Kf;
-  d.dinvM = m->d_dinvM; d.dinvMf = m->d_dinvMf; d.sl_el_ptr = m->d_sl_el_ptr; d.sl_el = m->d_sl_el;
+  d.dinvM = m->d_dinvM; d.dinvMf = m->d_dinvMf;
+  d.nv_ptr = m->d_nv_ptr; d.nv_el = m->d_nv_el; d.nv_slot = m->d_nv_slot; d.nv_words = words; d.nv_wide = wide ? 1 : 0;
+  d.zmax = zmax; d.zrow = zrow;
   d.degree = m->degree; d.nloc = m->nloc;
   d.gN = gN;
   d.gInv = gN ? 1.0f / (float)gN : 0.0f;
@@ -423,7 +588,7 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
   d.gdir_ok = gN && detect_grid_dirs(m, m->uniform_width, gN, gdir) ? 1 : 0;
   std::memset(d.gdir, 13, sizeof(d.gdir));
   if (d.gdir_ok) std::memcpy(d.gdir, gdir.data(), sizeof(d.gdir));
-  d.nd_el_ptr = m->d_nd_el_ptr; d.nd_el = m->d_nd_el; d.elem_nodes = m->d_elem_nodes; d.elem_vol = m->d_vol;
+  d.elem_nodes = m->d_elem_nodes; d.elem_vol = m->d_vol;
   return PFC_OK;
 }
 
@@ -618,14 +783,16 @@ std::vector<Poly> p2_basis(int m) {
 }
 }  // namespace
 
-// M2 [q*q], D [k*k*q*q], C4 [q^4] concatenated
+// M2 [q*q], D [k*k*q*q], C2 [q*q][c <= d], C3 [q][b <= c <= d] concatenated
 static std::vector<double> p2_tables(int m) {
   const std::vector<Poly> B = p2_basis(m);
   const int q = (int)B.size(), k = m + 1;
-  std::vector<double> t((size_t)q * q + (size_t)k * k * q * q + (size_t)q * q * q * q, 0.0);
+  const int np = q * (q + 1) / 2, nt = q * (q + 1) * (q + 2) / 6;
+  std::vector<double> t((size_t)q * q + (size_t)k * k * q * q + (size_t)q * q * np + (size_t)q * nt, 0.0);
   double* M2 = t.data();
   double* D = M2 + q * q;
-  double* C4 = D + k * k * q * q;
+  double* C2 = D + k * k * q * q;
+  double* C3 = C2 + (size_t)q * q * np;
   std::vector<Poly> P2((size_t)q * q);
   for (int a = 0; a < q; ++a)
     for (int b = 0; b < q; ++b) {
@@ -638,12 +805,16 @@ static std::vector<double> p2_tables(int m) {
         for (int b = 0; b < q; ++b) D[((i * k + j) * q + a) * q + b] = integral(mul(dl(B[a], i), dl(B[b], j)), m);
   for (int a = 0; a < q; ++a)
     for (int b = a; b < q; ++b)
-      for (int c = 0; c < q; ++c)
-        for (int d = c; d < q; ++d) {
-          const double v = integral(mul(P2[a * q + b], P2[c * q + d]), m);
-          C4[((a * q + b) * q + c) * q + d] = C4[((b * q + a) * q + c) * q + d] = v;
-          C4[((a * q + b) * q + d) * q + c] = C4[((b * q + a) * q + d) * q + c] = v;
-        }
+      for (int c = 0, p = 0; c < q; ++c)
+        for (int d = c; d < q; ++d, ++p)
+          C2[(a * q + b) * np + p] = C2[(b * q + a) * np + p] =
+              (c == d ? 1.0 : 2.0) * integral(mul(P2[a * q + b], P2[c * q + d]), m);
+  for (int a = 0; a < q; ++a)
+    for (int b = 0, p = 0; b < q; ++b)
+      for (int c = b; c < q; ++c)
+        for (int d = c; d < q; ++d, ++p)  // C2 holds each product of c != d twice already
+          C3[a * nt + p] = (c == d ? (b == c ? 1.0 : 3.0) : (b == c ? 1.5 : 3.0)) *
+                           C2[(a * q + b) * np + c * q - c * (c - 1) / 2 + d - c];
   return t;
 }
 
@@ -728,7 +899,8 @@ static int create_lagrange(const char* who, int dim, int degree, int n, int n_el
     if ((rc = upload(&m->d_p2tab, tab.data(), tab.size()))) { mesh_free(m); return rc; }
     m->dev.p2_M2 = m->d_p2tab;
     m->dev.p2_D = m->d_p2tab + k * k;
-    m->dev.p2_C4 = m->dev.p2_D + kv * kv * k * k;
+    m->dev.p2_C2 = m->dev.p2_D + kv * kv * k * k;
+    m->dev.p2_C3 = m->dev.p2_C2 + k * k * (k * (k + 1) / 2);
   }
   // element geometry and assembly on the GPU
   double* d_X = nullptr;
@@ -749,16 +921,18 @@ static int create_lagrange(const char* who, int dim, int degree, int n, int n_el
   if (hipMemset(d_bad, 0, sizeof(int)) != hipSuccess) return fail(hip_fail(hipErrorUnknown, "hipMemset"));
   hipLaunchKernelGGL(k_elem_geom, dim3((n_elem + 255) / 256), dim3(256), 0, 0, dim, n_elem, d_X, m->d_vol, d_grad, d_bad);
   if (degree == 1) {
-    hipLaunchKernelGGL(k_assemble_MK, dim3((unsigned)((m->nnz_sell + 255) / 256)), dim3(256), 0, 0, m->dev, d_grad,
-                       m->d_M, m->d_K);
+    const dim3 nb(slice_blocks(m->n_slices));
+    if (dim == 2) hipLaunchKernelGGL(k_assemble_MK<3>, nb, dim3(PFC_WG), 0, 0, m->dev, d_grad, m->d_M, m->d_K);
+    else hipLaunchKernelGGL(k_assemble_MK<4>, nb, dim3(PFC_WG), 0, 0, m->dev, d_grad, m->d_M, m->d_K);
     // element stiffness for the mobility matrices of the PFC1 model
     if ((rc = upload<double>(&m->d_elemK, nullptr, (size_t)n_elem * (kv * (kv + 1) / 2)))) return fail(rc);
     m->dev.elem_K = m->d_elemK;
     hipLaunchKernelGGL(k_elem_stiff, dim3((n_elem + 255) / 256), dim3(256), 0, 0, dim, n_elem, m->d_vol, d_grad,
                        m->d_elemK);
   } else {
-    hipLaunchKernelGGL(k_assemble_MK_p2, dim3((unsigned)((m->nnz_sell + 255) / 256)), dim3(256), 0, 0, m->dev,
-                       d_grad, m->d_M, m->d_K);
+    const dim3 nb(slice_blocks(m->n_slices));
+    if (dim == 2) hipLaunchKernelGGL(k_assemble_MK_p2<6>, nb, dim3(PFC_WG), 0, 0, m->dev, d_grad, m->d_M, m->d_K);
+    else hipLaunchKernelGGL(k_assemble_MK_p2<10>, nb, dim3(PFC_WG), 0, 0, m->dev, d_grad, m->d_M, m->d_K);
   }
   hipError_t he = hipGetLastError();
   if (he == hipSuccess) he = hipDeviceSynchronize();
@@ -943,7 +1117,7 @@ int pfc_spmv(const pfc_mesh* m, int which, const double* x, double* y, void* str
     return PFC_ERR_ARG;
   }
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_spmv, dim3(slice_blocks(m->n_slices)), dim3(PFC_WG), 0, s, m->dev,
+  hipLaunchKernelGGL(k_spmv, row_grid(m, PFC_ROW_T), dim3(PFC_ROW_T), 0, s, m->dev,
                      which == PFC_OP_M ? m->d_M : m->d_K, x, y);
   PFC_HIP(hipGetLastError());
   PFC_HIP(hipStreamSynchronize(s));
@@ -953,9 +1127,8 @@ int pfc_spmv(const pfc_mesh* m, int which, const double* x, double* y, void* str
 int pfc_assemble_N(const pfc_mesh* m, const double* psi, double* N_csr, void* stream) {
   if (!m || !psi || !N_csr) { set_error("pfc_assemble_N: invalid arguments"); return PFC_ERR_ARG; }
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_assemble_N_csr, dim3((m->nnz + 255) / 256), dim3(256), 0, s, m->dev, m->d_csr2sell, m->nnz,
-                     psi, N_csr);
-  PFC_HIP(hipGetLastError());
+  const int rc = launch_row_N(m, psi, N_csr, true, s);
+  if (rc) return rc;
   PFC_HIP(hipStreamSynchronize(s));
   return PFC_OK;
 }
@@ -963,8 +1136,8 @@ int pfc_assemble_N(const pfc_mesh* m, const double* psi, double* N_csr, void* st
 int pfc_load_psi3(const pfc_mesh* m, const double* psi, double* g, void* stream) {
   if (!m || !psi || !g) { set_error("pfc_load_psi3: invalid arguments"); return PFC_ERR_ARG; }
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_load_psi3, dim3((m->n + 255) / 256), dim3(256), 0, s, m->dev, psi, g);
-  PFC_HIP(hipGetLastError());
+  const int rc = launch_row_psi3(m, psi, g, s);
+  if (rc) return rc;
   PFC_HIP(hipStreamSynchronize(s));
   return PFC_OK;
 }

@@ -21,6 +21,9 @@
 #define PFC_SLICE 64
 #define PFC_MAXM 32
 #define PFC_NSTEPS_P 5
+// rows of at most this many entries have byte-wide positions in the visit lists
+// and are staged whole in LDS by the mesh-level element sums
+#define PFC_ROW_MAX 96
 
 // Solver phases.  A phase is the work done by one launch of the solver
 // kernel for one instance; the next phase is chosen from the reductions of
@@ -94,7 +97,8 @@ struct MeshDev {
   int gdir_ok;
   const double* p2_M2;    // P2 reference tables (divided by |T|): M2[a][b],
   const double* p2_D;     //   D[i][j][a][b] = int d_i phi_a d_j phi_b (i, j barycentric),
-  const double* p2_C4;    //   C4[a][b][c][d] = int phi_a phi_b phi_c phi_d
+  const double* p2_C2;    //   C2[a][b][c <= d] = (2 - [c==d]) int phi_a phi_b phi_c phi_d,
+  const double* p2_C3;    //   C3[a][b <= c <= d] = multiplicity(b, c, d) int phi_a phi_b phi_c phi_d
   const int* slice_ptr;   // [n_slices+1] entry offset of each slice (multiple of 64)
   const int* col;         // [nnz_sell]
   const double* M;        // [nnz_sell]
@@ -103,10 +107,15 @@ struct MeshDev {
   const float* Kf;
   const double* dinvM;    // [n] 1/diag(M)
   const float* dinvMf;
-  const int* sl_el_ptr;   // [nnz_sell+1] element contributions of each stored entry
-  const int* sl_el;       // packed (elem << 4) | (a << 2) | b; P2: (elem << 8) | (a << 4) | b
-  const int* nd_el_ptr;   // [n+1] simplices containing each node
-  const int* nd_el;       // packed (elem << 2) | local index; P2: (elem << 4) | local index
+  // simplices containing each node, in element order, laid out as the matrices:
+  // visit t of the rows of slice s at [nv_ptr[s] + 64 t + lane]
+  const long long* nv_ptr;  // [n_slices+1]
+  const int* nv_el;         // (elem << 2) | local index; P2: (elem << 4) | local index; -1: padding
+  const unsigned* nv_slot;  // position within the node's row of each node of the simplex, words
+                            // [nv_words nv_ptr[s] + 64 (nv_words t + w) + lane]: a byte per node
+                            // (narrow rows), or a word per node where nv_wide
+  int nv_words, nv_wide;
+  int zmax, zrow;           // longest row; common length of all rows, or 0
   const int* elem_nodes;  // [n_elem*nloc]
   const double* elem_vol; // [n_elem]
   const double* elem_K;   // [n_elem * k(k+1)/2] |T| grad l_a . grad l_b for a <= b (P1 meshes; else null)

@@ -9,6 +9,25 @@ struct pfc_instance;
 
 namespace pfc {
 
+// One launch of the solver kernel (k_tick).
+struct TickLaunch {
+  const TeamEntry* teams;
+  const InstDev* insts;
+  // launches that serve one instance: its state and partial sums, and its mesh pattern
+  const State* st_in;
+  State* st_out;
+  const double* part_in;
+  double* part_out;
+  const double* gram_in;
+  int parity;
+  const int* col;
+  int uw, n_slices;
+  int n_wg, cols;       // workgroups; where the columns come from (PFC_COL_*)
+  bool single, b2;      // serves one instance; has the 2D block form
+};
+void launch_tick_f64(const TickLaunch& q, hipStream_t stream);
+void launch_tick_f32(const TickLaunch& q, hipStream_t stream);
+
 struct Group {
   int count = 0, n_wg = 0, graph_ticks = 0;
   TeamEntry* d_teams = nullptr;
