@@ -75,10 +75,46 @@ __device__ __forceinline__ PatView<L> p1_pat(const InstDev& I, const Team& tm) {
                     L == PFC_COL_GRID ? I.m.glin : nullptr};
 }
 
+// Cross-lane moves of a double through DPP (register to register, no LDS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// Halving exchange between the lanes of a pair: the lane that keeps the lower
+// half gets a + (partner's a), the other b + (partner's b).  Partners: lanes
+// l and l ^ 32 (permlane32 swap), rows 2k and 2k + 1 (permlane16 swap), or the
+// DPP pairs of CTRL within a row.  A swap of (a, b) leaves the lower lanes with
+// their a and the partner's a, the upper lanes with the partner's b and their b:
+// the sum of its two results is the wanted one in every lane.
+__device__ __forceinline__ double ss_pair(unsigned hi, unsigned lo) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <bool ROWS16>
+__device__ __forceinline__ double ss_swap(double a, double b) {
+  const unsigned long long ia = (unsigned long long)__double_as_longlong(a), ib = (unsigned long long)__double_as_longlong(b);
+  if constexpr (ROWS16) {
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)ia, (unsigned)ib, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
+    return ss_pair(h[0], l[0]) + ss_pair(h[1], l[1]);
+  } else {
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)ia, (unsigned)ib, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
+    return ss_pair(h[0], l[0]) + ss_pair(h[1], l[1]);
+  }
+}
+// Sum over the wave, in every lane: the butterfly over lane distances 32, 16, 8,
+// 4, 2, 1 without LDS (within a row of 16 a rotation by 8 or 4 meets the lane at
+// that distance, or one that holds the same partial sum).
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = ss_swap<false>(v, v);
+  v = ss_swap<true>(v, v);
+  v += dpp_f64<0x128, 0xf>(v);  // row_ror:8
+  v += dpp_f64<0x124, 0xf>(v);  // row_ror:4
+  v += dpp_f64<0x4e, 0xf>(v);   // quad_perm [2,3,0,1]
+  return v + dpp_f64<0xb1, 0xf>(v);  // quad_perm [1,0,3,2]
 }
 
 struct Red3 {
@@ -165,6 +201,21 @@ __device__ __forceinline__ T gld(const T* p) {
   return *(const __attribute__((address_space(1))) T*)p;
 }
 
+// A pointer that is the same in all lanes, in scalar registers, and accesses at a
+// byte offset of 32 bits from it: the address needs no 64-bit arithmetic per lane,
+// and constant steps of up to 4 KB from the offset are free.
+template <typename T>
+__device__ __forceinline__ T* uni(T* p) {
+  const unsigned long long a = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return (T*)(((unsigned long long)hi << 32) | lo);
+}
+template <typename T>
+__device__ __forceinline__ T gldo(const T* base, unsigned off, unsigned step = 0) {
+  typedef const __attribute__((address_space(1))) char* P;
+  return *(const __attribute__((address_space(1))) T*)((P)base + off + step);
+}
+
 template <typename T>
 __device__ __forceinline__ void vst(T* p, T v) {
 #if PFC_STORE_POLICY == 1
@@ -174,6 +225,12 @@ __device__ __forceinline__ void vst(T* p, T v) {
 #else
   *gp(p) = v;
 #endif
+}
+
+template <typename T>
+__device__ __forceinline__ void vsto(T* base, unsigned off, T v) {
+  typedef __attribute__((address_space(1))) char* P;
+  vst((T*)((P)base + off), v);
 }
 
 // Workgroup placement.  The dispatcher deals the workgroups of a launch to the
@@ -742,6 +799,7 @@ __device__ __forceinline__ bool is_ci(int kind) { return kind == KIND_CI_OMEGA |
 template <typename T>
 __device__ __forceinline__ PcgOps<T> pcg_ops(const InstDev& I, int kind) {
   PcgOps<T> o;
+  kind = __builtin_amdgcn_readfirstlane(kind);
   o.Mv = TV<T>::M(I);
   o.Kv = TV<T>::K(I);
   o.cK = T(0);
@@ -775,6 +833,13 @@ __device__ __forceinline__ PcgOps<T> pcg_ops(const InstDev& I, int kind) {
     case KIND_CI_OMEGA: o.x = (T*)(I.xk + 2LL * n); break;
     case KIND_CI_MU: o.x = (T*)(I.xk); break;
   }
+  o.C = uni(o.C);
+  o.Mv = uni(o.Mv);
+  o.Kv = uni(o.Kv);
+  o.dinv = uni(o.dinv);
+  o.x = uni(o.x);
+  o.sp = uni(o.sp);
+  o.colp = uni(o.colp);
   return o;
 }
 
@@ -1159,14 +1224,6 @@ __shared__ unsigned long long pfc_sst[6];  // optional instrumentation (separate
 #define PFC_SS_STAMP(k)
 #endif
 
-// Cross-lane moves of a double through DPP (register to register, no LDS).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 // Workgroup barrier that orders LDS only: the global loads and stores of the
 // two-iterations-per-launch phase are never read back within the launch, so
 // loads issued ahead stay in flight across it (a full __syncthreads would wait
@@ -1177,26 +1234,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Halving exchange between the lanes of a pair: the lane that keeps the lower
-// half returns a + (partner's a), the other b + (partner's b).  Partners: lanes
-// l and l ^ 32 (permlane32 swap), rows 2k and 2k + 1 (permlane16 swap), or the
-// DPP pairs of CTRL within a row.
-__device__ __forceinline__ double ss_pair(unsigned hi, unsigned lo) {
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <bool ROWS16>
-__device__ __forceinline__ double ss_swap(double a, double b, bool upper) {
-  const unsigned long long ia = (unsigned long long)__double_as_longlong(a), ib = (unsigned long long)__double_as_longlong(b);
-  if constexpr (ROWS16) {
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)ia, (unsigned)ib, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-    return upper ? b + ss_pair(h[0], l[0]) : a + ss_pair(h[1], l[1]);
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)ia, (unsigned)ib, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-    return upper ? b + ss_pair(h[0], l[0]) : a + ss_pair(h[1], l[1]);
-  }
-}
 template <int CTRL>
 __device__ __forceinline__ double ss_dppx(double a, double b, bool upper) {
   return (upper ? b : a) + dpp_f64<CTRL, 0xf>(upper ? a : b);
@@ -1208,9 +1245,9 @@ __device__ __forceinline__ double ss_dppx(double a, double b, bool upper) {
 __device__ __forceinline__ double ss_wave_sums32(const double* v, int lane) {
   double w16[16], w8[8], w4[4], w2[2];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) w16[k] = ss_swap<false>(v[k], v[k + 16], lane >= 32);
+  for (int k = 0; k < 16; ++k) w16[k] = ss_swap<false>(v[k], v[k + 16]);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) w8[k] = ss_swap<true>(w16[k], w16[k + 8], (lane >> 4) & 1);
+  for (int k = 0; k < 8; ++k) w8[k] = ss_swap<true>(w16[k], w16[k + 8]);
 #pragma unroll
   for (int k = 0; k < 4; ++k) w4[k] = ss_dppx<0x140>(w8[k], w8[k + 4], (lane & 15) >= 8);  // row_mirror
 #pragma unroll
@@ -1521,7 +1558,7 @@ __device__ __forceinline__ void ss_gram(const double* part, int size, const doub
     double t = 0.0;
 #pragma unroll
     for (int q = 0; q < 16; ++q) t += pfc_ssred[(half * 16 + q) * 32 + v];
-    t = ss_swap<false>(t, t, half != 0);
+    t = ss_swap<false>(t, t);
     if (tid < PFC_SS_NG) g[tid] = t;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_wave_barrier();
@@ -1671,7 +1708,7 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
   // T p on the one-step frame
   auto tprow = [&](int q1, const T* a, T di) {
     const int x = q1 & 63, t1 = q1 >> 6, yl = t1 % 6 - 1, zl = t1 / 6 - 1;
-    const unsigned char* gd = gdir + s3_class(G, x, yl, zl) * PFC_GRID_W;
+    const unsigned char* gd = gdir;
     const int rb = PFC_S3_N * ((yl + 2) + 8 * (zl + 2));
     T acc = T(0);
 #pragma unroll
@@ -1700,7 +1737,7 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
   const T odi = gld(o.dinv + og);
   lds_barrier();
   // own row: T u, T^2 p, the stores and the Gram products
-  const unsigned char* gd = gdir + s3_class(G, ox, oyl, ozl) * PFC_GRID_W;
+  const unsigned char* gd = gdir;
   const int rb1 = PFC_S3_N * ((oyl + 1) + 6 * (ozl + 1));
   T au = T(0), att = T(0), dg = T(0);
 #pragma unroll
@@ -1778,23 +1815,70 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
   }
 }
 
+// Row of a stored operator (or of M + cK), W entries from byte offset off.
+template <int W, typename T>
+__device__ __forceinline__ void op_row(const PcgOps<T>& o, unsigned off, T* a) {
+  if (o.C) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) a[k] = gldo(o.C, off, k * 64 * (unsigned)sizeof(T));
+  } else {
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+      a[k] = gldo(o.Mv, off, k * 64 * (unsigned)sizeof(T)) + o.cK * gldo(o.Kv, off, k * 64 * (unsigned)sizeof(T));
+  }
+}
+// frame steps of the W entries of a grid row (MeshDev::goff[f]), in scalar registers
+template <int W>
+struct GridOff {
+  int d[W];
+};
+template <int W>
+__device__ __forceinline__ GridOff<W> grid_off(const MeshDev& m, int f) {
+  GridOff<W> r;
+  const int* p = (const int*)m.goff[f];
+#pragma unroll
+  for (int q = 0; q < (W + 1) / 2; ++q) {
+    const int w = __builtin_amdgcn_readfirstlane(p[q]);
+    r.d[2 * q] = (short)w;
+    if (2 * q + 1 < W) r.d[2 * q + 1] = w >> 16;
+  }
+  return r;
+}
+
 // ---- two Jacobi-PCG iterations per launch on blocks of 2D periodic grids -------
 // The iteration of ph_scg3 on a 2D grid of side N, a multiple of 64: rank r
 // owns the block of 64 x 16 rows x0 .. x0 + 63, y0 .. y0 + 15 with
 // x0 = 64 (r mod N/64), y0 = 16 (r div N/64).  The two-step frame is the
 // 68 x 20 rows x0 - 2 .. x0 + 65, y0 - 2 .. y0 + 17, the one-step frame the
 // 66 x 18 rows x0 - 1 .. x0 + 64, y0 - 1 .. y0 + 16 (periodic), so a row's
-// neighbour in a frame is the row's frame position plus the entry's direction
-// (MeshDev::gdir).  Against a range of whole grid lines per workgroup (ph_scg)
-// the frames hold 1360 and 1188 rows instead of 3076 and 2050 at N = 512: the
-// basis is read, and p and T p are formed, on fewer rows.  Thread t's own row
-// is x0 + t mod 64, y0 + t / 64, so a wave's own rows are one SELL slice.
+// neighbour in a frame is the row's frame position plus the entry's step, the
+// same for every row (MeshDev::goff).  Against a range of whole grid lines per
+// workgroup (ph_scg) the frames hold 1360 and 1188 rows instead of 3076 and 2050
+// at N = 512: the basis is read, and p and T p are formed, on fewer rows.
+// Thread t owns row x0 + t mod 64, y0 + t / 64 (a wave's own rows are one SELL
+// slice), whose basis values and operator row stay in its registers through the
+// launch; the rings around the block (336 rows of the two-step frame, 164 of the
+// one-step frame, 180 of the three-step frame of a set-up) are second rows of
+// waves 0-5, 6-8 and 9-11.  The launch is bound by the instructions its waves
+// issue (four waves a SIMD) and by its chain of round trips, not by bytes: frame
+// passes over all rows in thread order, with the own row's operator and basis read
+// again, division-built coordinates, a direction table in LDS and 64-bit address
+// arithmetic per load took 1097 vector instructions a wave, this form 699 (2D
+// 512^2 float64: stage solve 13.2 -> 10.1 ms, 128^2 mixed x 64 90.7 -> 72.4 ms a step).
 #define PFC_B2_W2 68
 #define PFC_B2_N2 (PFC_B2_W2 * 20)  // two-step frame
 #define PFC_B2_W1 66
 #define PFC_B2_N1 (PFC_B2_W1 * 18)  // one-step frame
 #define PFC_B2_W3 70
 #define PFC_B2_N3 (PFC_B2_W3 * 22)  // three-step frame (a set-up that also ends the previous solve)
+#define PFC_B2_R2 336               // two-step frame rows outside the block: waves 0-5
+#define PFC_B2_R1 164               // one-step frame rows outside the block: waves 6-8
+#define PFC_B2_R3 180               // three-step frame rows outside the two-step frame: waves 9-11
+#define PFC_B2_T2 384
+#define PFC_B2_T1 576
+#define PFC_B2_T3 768
+static_assert(PFC_B2_R2 <= PFC_B2_T2 && PFC_B2_R1 <= PFC_B2_T1 - PFC_B2_T2 && PFC_B2_R3 <= PFC_B2_T3 - PFC_B2_T1 &&
+              PFC_B2_T3 <= PFC_WG, "the rings of a 2D block exceed their waves");
 struct B2Geo {
   int x0, y0, N;
 };
@@ -1803,34 +1887,47 @@ __device__ __forceinline__ B2Geo b2_geo(int rank, int N) {
   return B2Geo{(rank % bx) * 64, (rank / bx) * 16, N};
 }
 __device__ __forceinline__ int b2_wrap(int v, int N) { return v < 0 ? v + N : (v >= N ? v - N : v); }
-// row at block coordinates (fx, fy), -2 <= fx < 66, -2 <= fy < 18
+// row at block coordinates (fx, fy), -3 <= fx < 67, -3 <= fy < 19
 __device__ __forceinline__ int b2_row(const B2Geo& G, int fx, int fy) {
   return b2_wrap(G.x0 + fx, G.N) + G.N * b2_wrap(G.y0 + fy, G.N);
 }
-__device__ __forceinline__ int b2_class(const B2Geo& G, int fx, int fy) {
-  return grid_edge(b2_wrap(G.x0 + fx, G.N), G.N) + 3 * grid_edge(b2_wrap(G.y0 + fy, G.N), G.N);
+// block coordinates of row r of the ring of width d (rows 64 + 2 k wide) around
+// the frame k - d steps out: d full lines below, d above, then the sides
+template <int K, int D>
+__device__ __forceinline__ void b2_ring(int r, int& fx, int& fy) {
+  constexpr int W = 64 + 2 * K, L = 2 * D * W;
+  if (r < L) {
+    const int q = r / W;
+    fx = r - W * q - K;
+    fy = q < D ? q - K : q - D + 16 + K - D;
+  } else {
+    const int s = r - L, c = s % (2 * D);
+    fy = s / (2 * D) - (K - D);
+    fx = c < D ? c - K : 64 + K - 2 * D + c;
+  }
 }
-// frame offset of an entry's direction code in a frame of width w
-__device__ __forceinline__ int b2_doff(int code, int w) { return code % 3 - 1 + w * ((code / 3) % 3 - 1); }
 
 template <typename T>
 struct B2Pre {
-  T bv[2][5];
+  T own[5], ring[5];
 };
-// the current basis on the two-step frame (the second pass covers 336
-// positions; the others load a clamped position), issued before the reductions
+// the current basis on the own row and on the ring of the two-step frame, issued
+// before the reductions
 template <typename T>
 __device__ __forceinline__ void b2_load(const InstDev& I, int rank, B2Pre<T>& P, int par) {
   const long long nn = I.n;
   const int tid = threadIdx.x;
   const B2Geo G = b2_geo(rank, I.m.gN);
-  const T* bin = (const T*)I.sbas + (long long)par * 5 * nn;
+  const T* bin = uni((const T*)I.sbas + (long long)par * 5 * nn);
+  const unsigned og = (unsigned)(G.x0 + (tid & 63) + G.N * (G.y0 + (tid >> 6))) * (unsigned)sizeof(T);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int q = min(tid + c * PFC_WG, PFC_B2_N2 - 1);
-    const int g = b2_row(G, q % PFC_B2_W2 - 2, q / PFC_B2_W2 - 2);
+  for (int k = 0; k < 5; ++k) P.own[k] = gldo(uni(bin + k * nn), og);
+  if (tid < PFC_B2_T2) {
+    int fx, fy;
+    b2_ring<2, 2>(min(tid, PFC_B2_R2 - 1), fx, fy);
+    const unsigned g = (unsigned)b2_row(G, fx, fy) * (unsigned)sizeof(T);
 #pragma unroll
-    for (int k = 0; k < 5; ++k) P.bv[c][k] = gld(bin + k * nn + g);
+    for (int k = 0; k < 5; ++k) P.ring[k] = gldo(uni(bin + k * nn), g);
   }
 }
 
@@ -1845,194 +1942,201 @@ __device__ __forceinline__ void b2_end_store(const InstDev& I, int rank, int kin
   const long long nn = I.n;
   const int tid = threadIdx.x;
   const B2Geo G = b2_geo(rank, I.m.gN);
-  const int og = b2_row(G, tid & 63, tid >> 6);
+  const unsigned og = (unsigned)(G.x0 + (tid & 63) + G.N * (G.y0 + (tid >> 6))) * (unsigned)sizeof(T);
   T* x = pcg_ops<T>(I, kind).x;
-  const T* bas = (const T*)I.sbas + (long long)(1 - par) * 5 * nn;
-  const T xo = gld(x + og);
-  const double p = gld(bas + og), tp = gld(bas + nn + og), u = gld(bas + 3 * nn + og);
-  vst(x + og, T((double)xo + (c0 * p + c1 * tp + c3 * u)));
+  const T* bas = uni((const T*)I.sbas + (long long)(1 - par) * 5 * nn);
+  const T xo = gldo(x, og);
+  const double p = gldo(bas, og), tp = gldo(uni(bas + nn), og), u = gldo(uni(bas + 3 * nn), og);
+  vsto(x, og, T((double)xo + (c0 * p + c1 * tp + c3 * u)));
 }
 
 template <typename T>
 __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const Team& tm, const double* coef, bool init,
                                          double* spart_out, B2Pre<T>& P, int par) {
   constexpr int W7 = 7;
+  constexpr unsigned TS = sizeof(T);
   const int n = I.n, tid = threadIdx.x;
   const long long nn = n;
   const B2Geo G = b2_geo(tm.rank, I.m.gN);
-  PcgOps<T> o = pcg_ops<T>(I, S.kind);
-  const PatView<PFC_COL_GRID> pv = op_pat<PFC_COL_GRID>(I, o, tm);
-  T* bout = (T*)I.sbas + (long long)(1 - par) * 5 * nn;
-  const T* bold = (const T*)I.sbas + (long long)par * 5 * nn;
-  const unsigned char* gdir = I.m.gdir;
+  const PcgOps<T> o = pcg_ops<T>(I, S.kind);
+  T* bout = uni((T*)I.sbas + (long long)(1 - par) * 5 * nn);
   T* sp = (T*)pfc_ss;          // new p on the two-step frame
   T* su = sp + PFC_B2_N2;      // new u on the one-step frame
   T* stp = su + PFC_B2_N1;     // T p on the one-step frame
-  T* sb = stp + PFC_B2_N1;     // right-hand side on the two-step frame (first launch of a solve)
-  T* sv = sb + PFC_B2_N2;      // v on the three-step frame (a set-up that also ends the previous solve)
-  static_assert((2 * PFC_B2_N2 + 2 * PFC_B2_N1 + PFC_B2_N3) * sizeof(double) <= sizeof(pfc_ss),
+  T* sv = stp + PFC_B2_N1;     // v on the three-step frame (a set-up that also ends the previous solve)
+  static_assert((PFC_B2_N2 + 2 * PFC_B2_N1 + PFC_B2_N3) * sizeof(double) <= sizeof(pfc_ss),
                 "the frames of ph_scg2b exceed the s-step LDS");
+  // own row: its index, its byte offsets in a vector and in the values, its frame positions
   const int ox = tid & 63, oy = tid >> 6;
-  const int og = b2_row(G, ox, oy);
+  const int gi = G.x0 + ox + G.N * (G.y0 + oy);
+  const unsigned og = (unsigned)gi * TS, oe = (unsigned)((gi >> 6) * 64 * W7 + (gi & 63)) * TS;
+  const int o1 = (ox + 1) + PFC_B2_W1 * (oy + 1), o2 = (ox + 2) + PFC_B2_W2 * (oy + 2);
+  const int o3 = (ox + 3) + PFC_B2_W3 * (oy + 3);
+  // the rings' rows
+  const bool w2 = tid < PFC_B2_T2, in2 = tid < PFC_B2_R2;
+  const bool w1 = tid >= PFC_B2_T2 && tid < PFC_B2_T1, in1 = w1 && tid < PFC_B2_T2 + PFC_B2_R1;
+  int rx = 0, ry = 0, rg = 0;
+  if (w2) {
+    b2_ring<2, 2>(min(tid, PFC_B2_R2 - 1), rx, ry);
+    rg = b2_row(G, rx, ry);
+  } else if (w1) {
+    b2_ring<1, 1>(min(tid - PFC_B2_T2, PFC_B2_R1 - 1), rx, ry);
+    rg = b2_row(G, rx, ry);
+  }
+  const unsigned rge = (unsigned)((rg >> 6) * 64 * W7 + (rg & 63)) * TS;
+  const int r1 = (rx + 1) + PFC_B2_W1 * (ry + 1), r2 = (rx + 2) + PFC_B2_W2 * (ry + 2);
+  T x1f = T(0);  // x1 on the own row where this launch ends its solve
+  T bo = T(0), dio = T(0), br = T(0), dir = T(0);
   if (init) {
     // the solve's right-hand side b on the two-step frame and u_0 = p_0 = D^{-1} b;
     // as ph_scg: b = t - s (A v) by solve kind
     const long long n3 = 3 * nn;
-    const double* Vj = I.V + (long long)S.j * n3;
-    const int kind = S.kind;
+    const double* Vj = uni(I.V + (long long)S.j * n3);
+    const int kind = __builtin_amdgcn_readfirstlane(S.kind);
     const T* A = (kind == KIND_Y1 || kind == KIND_X2) ? o.Kv : (kind == KIND_Y0 ? nullptr : o.Mv);
-    const T* v = kind == KIND_Y1 ? (const T*)I.y0 : kind == KIND_Z ? (const T*)I.y1 : kind == KIND_X1 ? (const T*)I.zt
-                                                                                                      : (const T*)I.x1;
-    const double* t = kind == KIND_Y0 ? I.W : (kind == KIND_Y1 ? Vj + nn : (kind == KIND_X2 ? Vj + 2 * nn : nullptr));
+    const T* v = uni(kind == KIND_Y1 ? (const T*)I.y0 : kind == KIND_Z ? (const T*)I.y1 : kind == KIND_X1 ? (const T*)I.zt
+                                                                                                          : (const T*)I.x1);
+    const double* t = uni(kind == KIND_Y0 ? (const double*)I.W
+                                          : (kind == KIND_Y1 ? Vj + nn : (kind == KIND_X2 ? Vj + 2 * nn : nullptr)));
     const double ts = kind == KIND_Y0 ? S.vscale : 1.0, sa = kind == KIND_Y1 ? I.tau_p : 1.0;
-    const bool fz = S.fuse != 0;
+    const bool fz = __builtin_amdgcn_readfirstlane(S.fuse) != 0;
     if (fz) {
       // the previous solve (the P_CH step before, whose x is this solve's v) ends
       // in this launch: its x plus the last increment, formed on the three-step
       // frame; x itself stays unchanged here (other workgroups read it on their
       // halos) and is stored by the next launch (b2_end_store)
       const T* xp = pcg_ops<T>(I, S.fkind).x;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int q3 = tid + c * PFC_WG;
-        if (q3 < PFC_B2_N3) {
-          const int g = b2_row(G, q3 % PFC_B2_W3 - 3, q3 / PFC_B2_W3 - 3);
-          const T xo = gld(xp + g);
-          const double p = gld(bold + g), tp = gld(bold + nn + g), u = gld(bold + 3 * nn + g);
-          sv[q3] = T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u));
-        }
+      const double c0 = coef[0], c1 = coef[1], c3 = coef[3];
+      auto fin = [&](T xo, double p, double tp, double u) { return T((double)xo + (c0 * p + c1 * tp + c3 * u)); };
+      x1f = fin(gldo(xp, og), P.own[0], P.own[1], P.own[3]);
+      sv[o3] = x1f;
+      if (w2) {
+        const T xr = fin(gldo(xp, (unsigned)rg * TS), P.ring[0], P.ring[1], P.ring[3]);
+        if (in2) sv[(rx + 3) + PFC_B2_W3 * (ry + 3)] = xr;
+      } else if (tid >= PFC_B2_T1 && tid < PFC_B2_T3) {
+        int qx, qy;
+        b2_ring<3, 1>(min(tid - PFC_B2_T1, PFC_B2_R3 - 1), qx, qy);
+        const unsigned q = (unsigned)b2_row(G, qx, qy) * TS;
+        const T* bold = uni((const T*)I.sbas + (long long)par * 5 * nn);
+        const T xr = fin(gldo(xp, q), gldo(bold, q), gldo(uni(bold + nn), q), gldo(uni(bold + 3 * nn), q));
+        if (tid < PFC_B2_T1 + PFC_B2_R3) sv[(qx + 3) + PFC_B2_W3 * (qy + 3)] = xr;
       }
       lds_barrier();
     }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int q = tid + c * PFC_WG, qc = min(q, PFC_B2_N2 - 1);
-      const int fx = qc % PFC_B2_W2 - 2, fy = qc / PFC_B2_W2 - 2;
-      const int g = b2_row(G, fx, fy);
-      const int base = (g >> 6) * 64 * W7 + (g & 63);
+    const GridOff<W7> off3 = grid_off<W7>(I.m, 2);
+    const PatView<PFC_COL_GRID> pv = op_pat<PFC_COL_GRID>(I, o, tm);
+    auto rhs = [&](int g, unsigned e, int q3, T& b, T& di) {
       T d = T(0);
-      if (A && fz) {
-        const unsigned char* gd = gdir + b2_class(G, fx, fy) * PFC_GRID_W;
-        const int q3 = (fx + 3) + PFC_B2_W3 * (fy + 3);
+      if (A) {
+        T a[W7];
 #pragma unroll
-        for (int k = 0; k < W7; ++k) d += gld(A + (long long)base + k * 64) * sv[q3 + b2_doff(gd[k], PFC_B2_W3)];
-      } else if (A) {
+        for (int k = 0; k < W7; ++k) a[k] = gldo(A, e, k * 64 * TS);
+        if (fz) {
 #pragma unroll
-        for (int k = 0; k < W7; ++k) {
-          const long long e = (long long)base + k * 64;
-          d += gld(A + e) * gld(v + pv.at(e, g));
+          for (int k = 0; k < W7; ++k) d += a[k] * sv[q3 + off3.d[k]];
+        } else {
+          const int base = (g >> 6) * 64 * W7 + (g & 63);
+#pragma unroll
+          for (int k = 0; k < W7; ++k) d += a[k] * gldo(v, (unsigned)pv.at((long long)base + k * 64, g) * TS);
         }
       }
-      const double tt = t ? gld(t + g) * ts : 0.0;
-      const double b = !A ? tt : (t ? tt - sa * (double)d : (double)d);
-      P.bv[c][0] = gld(o.dinv + g);
-      P.bv[c][1] = T(b);
-      if (q < PFC_B2_N2) sb[q] = T(b);
-    }
+      const double tt = t ? gldo(t, (unsigned)g * 8u) * ts : 0.0;
+      b = T(!A ? tt : (t ? tt - sa * (double)d : (double)d));
+      di = gldo(o.dinv, (unsigned)g * TS);
+    };
+    rhs(gi, oe, o3, bo, dio);
+    if (w2) rhs(rg, rge, (rx + 3) + PFC_B2_W3 * (ry + 3), br, dir);
   } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
-    const T xo = gld(o.x + og);
-    const double p = gld(bold + og), tp = gld(bold + nn + og), u = gld(bold + 3 * nn + og);
-    vst(o.x + og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+    const double p = P.own[0], tp = P.own[1], u = P.own[3];
+    vsto(o.x, og, T((double)gldo(o.x, og) + (coef[0] * p + coef[1] * tp + coef[3] * u)));
     return;
   }
-  // operator rows of the one-step frame (the second pass covers 164 rows),
-  // issued before the new p and u are formed (whose basis loads they wait for)
-  // and in flight across the barrier
-  T av[2][W7], dv[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int q1 = min(tid + c * PFC_WG, PFC_B2_N1 - 1);
-    const int g = b2_row(G, q1 % PFC_B2_W1 - 1, q1 / PFC_B2_W1 - 1);
-    const int base = (g >> 6) * 64 * W7 + (g & 63);
-#pragma unroll
-    for (int k = 0; k < W7; ++k) av[c][k] = opval_g(o, (long long)base + k * 64);
-    dv[c] = gld(o.dinv + g);
+  // operator rows of the own row and of the one-step ring, issued before the new p
+  // and u are formed (whose basis loads they wait for) and in flight across the barrier
+  T ao[W7], ar[W7], odi, rdi = T(0);
+  op_row<W7>(o, oe, ao);
+  odi = init ? dio : gldo(o.dinv, og);
+  const T xo = init ? T(0) : gldo(o.x, og);
+  if (w1) {
+    op_row<W7>(o, rge, ar);
+    rdi = gldo(o.dinv, (unsigned)rg * TS);
   }
   // new p on the two-step frame, new u on the one-step frame
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int q = tid + c * PFC_WG;
-    if (q < PFC_B2_N2) {
-      const T* b = P.bv[c];
-      T pn, un;
-      if (init) {
-        pn = b[0] * b[1];
-        un = pn;
-      } else {
-        pn = T(coef[5] * b[0] + coef[6] * b[1] + coef[7] * b[2] + coef[8] * b[3] + coef[9] * b[4]);
-        un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
-      }
-      sp[q] = pn;
-      const int fx = q % PFC_B2_W2 - 2, fy = q / PFC_B2_W2 - 2;
-      if (fx >= -1 && fx < 65 && fy >= -1 && fy < 17) su[(fx + 1) + PFC_B2_W1 * (fy + 1)] = un;
+  auto pu = [&](const T* b, T& pn, T& un) {
+    pn = T(coef[5] * b[0] + coef[6] * b[1] + coef[7] * b[2] + coef[8] * b[3] + coef[9] * b[4]);
+    un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
+  };
+  T pn, un;
+  if (init) pn = un = dio * bo;
+  else pu(P.own, pn, un);
+  sp[o2] = pn;
+  su[o1] = un;
+  if (w2) {
+    T pr, ur;
+    if (init) pr = ur = dir * br;
+    else pu(P.ring, pr, ur);
+    if (in2) {
+      sp[r2] = pr;
+      if (rx >= -1 && rx < 65 && ry >= -1 && ry < 17) su[r1] = ur;
     }
   }
   lds_barrier();
   PFC_SS_STAMP(0);
   // T p on the one-step frame
+  const GridOff<W7> off2 = grid_off<W7>(I.m, 1);
+  auto tp_of = [&](const T* a, T di, int q2) {
+    T acc = T(0);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int q1 = tid + c * PFC_WG;
-    if (q1 < PFC_B2_N1) {
-      const int fx = q1 % PFC_B2_W1 - 1, fy = q1 / PFC_B2_W1 - 1;
-      const unsigned char* gd = gdir + b2_class(G, fx, fy) * PFC_GRID_W;
-      const int q2 = (fx + 2) + PFC_B2_W2 * (fy + 2);
-      T acc = T(0);
-#pragma unroll
-      for (int k = 0; k < W7; ++k) acc += av[c][k] * sp[q2 + b2_doff(gd[k], PFC_B2_W2)];
-      stp[q1] = dv[c] * acc;
-    }
+    for (int k = 0; k < W7; ++k) acc += a[k] * sp[q2 + off2.d[k]];
+    return T(di * acc);
+  };
+  const T tpo = tp_of(ao, odi, o2);
+  stp[o1] = tpo;
+  if (w1) {
+    const T tpr = tp_of(ar, rdi, r2);
+    if (in1) stp[r1] = tpr;
   }
-  // the own row's operator row (a cache hit: the frame pass read it)
-  T ao[W7];
-  const int obase = (og >> 6) * 64 * W7 + (og & 63);
-#pragma unroll
-  for (int k = 0; k < W7; ++k) ao[k] = opval_g(o, (long long)obase + k * 64);
-  const T odi = gld(o.dinv + og);
   lds_barrier();
   PFC_SS_STAMP(1);
   // own row: T u, T^2 p, the stores and the Gram products
-  const unsigned char* gd = gdir + b2_class(G, ox, oy) * PFC_GRID_W;
-  const int o1 = (ox + 1) + PFC_B2_W1 * (oy + 1), o2 = (ox + 2) + PFC_B2_W2 * (oy + 2);
-  T au = T(0), att = T(0), dg = T(0);
+  const GridOff<W7> off1 = grid_off<W7>(I.m, 0);
+  T au = T(0), att = T(0);
 #pragma unroll
   for (int k = 0; k < W7; ++k) {
-    const int code = gd[k];
-    const int i1 = o1 + b2_doff(code, PFC_B2_W1);
+    const int i1 = o1 + off1.d[k];
     au += ao[k] * su[i1];
     att += ao[k] * stp[i1];
-    dg += code == 13 ? ao[k] : T(0);
   }
-  const T pn = sp[o2], un = su[o1], tpo = stp[o1], tuo = odi * au, ttp = odi * att;
+  const T dg = ao[W7 / 2];
+  const T tuo = odi * au, ttp = odi * att;
   double bbo = 0.0;
   if (init) {
-    const double bo = (double)sb[o2];
-    bbo = bo * bo;
-    vst(o.x + og, T(0));
+    bbo = (double)bo * (double)bo;
+    vsto(o.x, og, T(0));
     const long long n3 = 3 * nn;
+    const unsigned od = (unsigned)gi * 8u;
     if (S.kind == KIND_Y0) {  // the Arnoldi vector v_j = w / ||w||
-      double* Vw = I.V + (long long)S.j * n3;
-      vst(Vw + og, gld(I.W + og) * S.vscale);
-      vst(Vw + nn + og, gld(I.W + nn + og) * S.vscale);
-      vst(Vw + 2 * nn + og, gld(I.W + 2 * nn + og) * S.vscale);
+      double* Vw = uni(I.V + (long long)S.j * n3);
+      const double* W = uni(I.W);
+#pragma unroll
+      for (int blk = 0; blk < 3; ++blk) vsto(uni(Vw + blk * nn), od, gldo(uni(W + blk * nn), od) * S.vscale);
     } else if (S.kind == KIND_X2) {  // (4): z_j = (y0 + (y1 - x1) / delta, x1, x2)
-      double* Zj = I.Z + (long long)S.j * n3;
-      const double y0i = (double)gld((const T*)I.y0 + og), y1i = (double)gld((const T*)I.y1 + og);
-      // x1 (the solve that ends in this launch when it fuses) from the frame
-      const double x1i = S.fuse ? (double)sv[(ox + 3) + PFC_B2_W3 * (oy + 3)] : (double)gld((const T*)I.x1 + og);
-      vst(Zj + og, y0i + (y1i - x1i) / I.delta);
-      vst(Zj + nn + og, x1i);
+      double* Zj = uni(I.Z + (long long)S.j * n3);
+      const double y0i = (double)gldo(uni((const T*)I.y0), og), y1i = (double)gldo(uni((const T*)I.y1), og);
+      // x1: formed above where its solve ends in this launch
+      const double x1i = S.fuse ? (double)x1f : (double)gldo(uni((const T*)I.x1), og);
+      vsto(Zj, od, y0i + (y1i - x1i) / I.delta);
+      vsto(uni(Zj + nn), od, x1i);
     }
   } else {
-    const T xo = gld(o.x + og);
-    const double p = gld(bold + og), tp = gld(bold + nn + og), u = gld(bold + 3 * nn + og);
-    vst(o.x + og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+    const double p = P.own[0], tp = P.own[1], u = P.own[3];
+    vsto(o.x, og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
   }
-  vst(bout + og, pn);
-  vst(bout + nn + og, tpo);
-  vst(bout + 2 * nn + og, ttp);
-  vst(bout + 3 * nn + og, un);
-  vst(bout + 4 * nn + og, tuo);
+  vsto(bout, og, pn);
+  vsto(uni(bout + nn), og, tpo);
+  vsto(uni(bout + 2 * nn), og, ttp);
+  vsto(uni(bout + 3 * nn), og, un);
+  vsto(uni(bout + 4 * nn), og, tuo);
   double gp[PFC_SS_NG];
   {
     const double dgo = (double)dg;
@@ -2093,9 +2197,9 @@ __shared__ double pfc_gsred[PFC_WAVES * PFC_GS_NV];
 __device__ __forceinline__ double gs_wave_sums16(const double* v, int lane) {
   double w8[8], w4[4], w2[2];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) w8[k] = ss_swap<false>(v[k], v[k + 8], lane >= 32);
+  for (int k = 0; k < 8; ++k) w8[k] = ss_swap<false>(v[k], v[k + 8]);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) w4[k] = ss_swap<true>(w8[k], w8[k + 4], (lane >> 4) & 1);
+  for (int k = 0; k < 4; ++k) w4[k] = ss_swap<true>(w8[k], w8[k + 4]);
 #pragma unroll
   for (int k = 0; k < 2; ++k) w2[k] = ss_dppx<0x140>(w4[k], w4[k + 2], (lane & 15) >= 8);  // row_mirror
   double w1 = ss_dppx<0x141>(w2[0], w2[1], (lane & 7) >= 4);                                // row_half_mirror
