@@ -424,9 +424,11 @@ template <int Q, typename Acc>
 __device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v, const Acc& acc) {
   if constexpr (Q <= 4) {
     const double cm = cm_of(Q - 1);
+    // (one rounding sequence, whatever the compiler could contract: with float32
+    // inner solves a last place here can move a result by far more)
     double S1 = 0.0, S2 = 0.0;
 #pragma unroll
-    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 += v.p[c] * v.p[c]; }
+    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 = fma(v.p[c], v.p[c], S2); }
     double pa = v.p[0];
 #pragma unroll
     for (int c = 1; c < Q; ++c) pa = v.a == c ? v.p[c] : pa;
@@ -435,7 +437,7 @@ __device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v,
     for (int b = 0; b < Q; ++b) {
       const double pb = v.p[b];
       x[b] = v.vol * cm * (v.a == b ? 2.0 : 1.0);
-      y[b] = S1 * S1 + S2 + 2.0 * S1 * (pa + pb) + 2.0 * (pa * pa + pb * pb + pa * pb);
+      y[b] = fma(2.0, fma(pa, pb, fma(pa, pa, pb * pb)), fma(pa + pb, S1 + S1, fma(S1, S1, S2)));
     }
     acc.add(v, x, y);
   } else {
@@ -471,7 +473,7 @@ __device__ __forceinline__ double visit_psi3(const MeshDev& m, const Visit<Q>& v
     const double cm = cm_of(Q - 1);
     double S1 = 0.0, S2 = 0.0, S3 = 0.0;
 #pragma unroll
-    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 += v.p[c] * v.p[c]; S3 += v.p[c] * v.p[c] * v.p[c]; }
+    for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 = fma(v.p[c], v.p[c], S2); S3 = fma(v.p[c], v.p[c] * v.p[c], S3); }
     double pa = v.p[0];
 #pragma unroll
     for (int c = 1; c < Q; ++c) pa = v.a == c ? v.p[c] : pa;
@@ -688,9 +690,11 @@ __device__ __forceinline__ double stage_comb(const InstDev& I, int stage, int bl
 // x_i = x_k + sum_j a_ij y_j formed on the fly.  The products with M and K over
 // the row's w entries (entry k at position pos(k) of the values, column col(k));
 // seen(k, mu, psi) is told the stage state there.
+struct StageSums {
+  double b0, b2, Kmu, My1, My2;
+};
 template <typename PosF, typename ColF, typename SeenF>
-__device__ __forceinline__ void stage_rhs_products(const InstDev& I, int w, int stage, PosF pos, ColF col, SeenF seen,
-                                                   double& b0, double& b1, double& b2) {
+__device__ __forceinline__ StageSums stage_rhs_products(const InstDev& I, int w, int stage, PosF pos, ColF col, SeenF seen) {
   const int n = I.n;
   double sMmu = 0, sMps = 0, sMom = 0, sKmu = 0, sKps = 0, sKom = 0, sMy1 = 0, sMy2 = 0;
   const long long n3 = 3LL * n;
@@ -707,18 +711,19 @@ __device__ __forceinline__ void stage_rhs_products(const InstDev& I, int w, int 
     if (stage >= 2) sMy1 += Mv * I.ys[n + j];
     if (stage >= 3) sMy2 += Mv * I.ys[n3 + n + j];
   }
-  b0 = -sMmu + (1.0 + I.r) * sMps - 2.0 * sKps - sKom;
-  // block 1 up to its mobility term: the products' part, and for PFC2 -tau K mu
-  b1 = I.model == PFC_MODEL_PFC1 ? 0.0 : I.tau * (-sKmu);
-  if (stage == 2) b1 += ROS_C21 * sMy1;
-  if (stage == 3) b1 += ROS_C31 * sMy1 + ROS_C32 * sMy2;
-  b2 = -sMom - sKps;
+  return StageSums{-sMmu + (1.0 + I.r) * sMps - 2.0 * sKps - sKom, -sMom - sKps, sKmu, sMy1, sMy2};
 }
 
-// ... and the element sums: the cubic load g and, for PFC1, -tau K_+(psi_i) mu_i
-__device__ __forceinline__ void stage_rhs_finish(const InstDev& I, double g, double kpm, double& b0, double& b1) {
-  b0 += g;
-  if (I.model == PFC_MODEL_PFC1) b1 += I.tau * (-kpm);
+// ... and the element sums: the cubic load g and, for PFC1, (K_+(psi_i) mu_i) = kpm
+__device__ __forceinline__ void stage_rhs_finish(const InstDev& I, const StageSums& q, int stage, double g, double kpm,
+                                                 double& b0, double& b1, double& b2) {
+  b0 = q.b0 + g;
+  // (roundings spelled out: the same in a solver launch and on its own)
+  const double k = -(I.model == PFC_MODEL_PFC1 ? kpm : q.Kmu);
+  b1 = I.tau * k;
+  if (stage == 2) b1 = fma(ROS_C21, q.My1, b1);
+  if (stage == 3) b1 = fma(I.tau, k, fma(ROS_C31, q.My1, ROS_C32 * q.My2));
+  b2 = q.b2;
 }
 
 template <int L>
@@ -726,14 +731,14 @@ __device__ __forceinline__ void stage_rhs_row(const InstDev& I, const PatView<L>
                                               double& b0, double& b1, double& b2) {
   const long long e0 = (long long)pv.base(sl) + lane;
   const int i = sl * 64 + lane;
-  stage_rhs_products(I, pv.width(sl), stage, [&](int k) { return e0 + 64LL * k; },
-                     [&](int k) { return pv.at(e0 + 64LL * k, i); }, [](int, double, double) {}, b0, b1, b2);
+  const StageSums q = stage_rhs_products(I, pv.width(sl), stage, [&](int k) { return e0 + 64LL * k; },
+                                         [&](int k) { return pv.at(e0 + 64LL * k, i); }, [](int, double, double) {});
   auto psi = [&](int j) { return stage_comb(I, stage, 1, j); };
   const double g = node_psi3<L != PFC_COL_GRID>(I.m, sl, lane, psi);
   double kpm = 0.0;
   if (I.model == PFC_MODEL_PFC1)
     kpm = node_Kplus_mu<L != PFC_COL_GRID>(I.m, sl, lane, psi, [&](int j) { return stage_comb(I, stage, 0, j); }, I.psi_min);
-  stage_rhs_finish(I, g, kpm, b0, b1);
+  stage_rhs_finish(I, q, stage, g, kpm, b0, b1, b2);
 }
 
 // Right-hand side of the solve: stage rhs b_i^R for job RB, the caller's rhs
@@ -1567,254 +1572,6 @@ __device__ __forceinline__ void ss_gram(const double* part, int size, const doub
 }
 
 
-// ---- two Jacobi-PCG iterations per launch on 3D periodic grids of side 64 -------
-// The s-step iteration of ph_scg with a workgroup's rows a block of the grid
-// instead of a range of rows: whole x-lines (64 rows, one SELL slice each) at
-// y0..y0+3, z0..z0+3, 1024 rows; rank r has y0 = 4 (r mod 16), z0 = 4 (r / 16).
-// The two-step frame is the 8 x 8 lines y0-2..y0+5, z0-2..z0+5, the one-step
-// frame the 6 x 6 lines y0-1..y0+4, z0-1..z0+4 (periodic in every direction),
-// so a row's neighbour in a frame follows from the entry's direction
-// (MeshDev::gdir).  Frame positions: q = x + 64 (ly + 8 lz) in the two-step
-// frame (4 passes of the workgroup), q1 = x + 64 (ly1 + 6 lz1) in the one-step
-// frame (3 passes, the third partial).  New p and u are formed on the frames,
-// T p on the one-step frame, and a last pass gives thread t the own row
-// x = t mod 64, y0 + (t / 64) mod 4, z0 + t / 256 for T u, T^2 p, the stores and
-// the Gram products.  T is the inner precision (float in PFC_MIXED); the Gram
-// sums and the coefficients stay float64.
-#define PFC_S3_N 64
-__device__ __forceinline__ int s3_wrap(int v) { return v & (PFC_S3_N - 1); }
-struct S3Geo {
-  int y0, z0;
-};
-__device__ __forceinline__ S3Geo s3_geo(int rank) { return S3Geo{(rank & 15) * 4, (rank >> 4) * 4}; }
-__device__ __forceinline__ int s3_row(const S3Geo& G, int x, int yl, int zl) {
-  return x + PFC_S3_N * (s3_wrap(G.y0 + yl) + PFC_S3_N * s3_wrap(G.z0 + zl));
-}
-// row class (grid_class) of the row at block coordinates (x, yl, zl)
-__device__ __forceinline__ int s3_class(const S3Geo& G, int x, int yl, int zl) {
-  return grid_edge(x, PFC_S3_N) + 3 * grid_edge(s3_wrap(G.y0 + yl), PFC_S3_N) + 9 * grid_edge(s3_wrap(G.z0 + zl), PFC_S3_N);
-}
-// offset of an entry's neighbour within a frame of f lines per direction:
-// (x + dx) mod 64 - x is applied separately
-__device__ __forceinline__ int s3_dline(int code, int f) { return PFC_S3_N * ((code / 3) % 3 - 1 + f * (code / 9 - 1)); }
-__device__ __forceinline__ int s3_nx(int x, int code) { return s3_wrap(x + code % 3 - 1); }
-
-template <typename T>
-struct S3Pre {
-  T bv[PFC_SS_NA][5];
-};
-// the current basis on the two-step frame, issued before the reductions
-template <typename T>
-__device__ __forceinline__ void s3_load(const InstDev& I, const State& S, int rank, S3Pre<T>& P, int par) {
-  const long long nn = I.n;
-  const int tid = threadIdx.x;
-  const S3Geo G = s3_geo(rank);
-  const T* bin = (const T*)I.sbas + (long long)par * 5 * nn;
-#pragma unroll
-  for (int c = 0; c < PFC_SS_NA; ++c) {
-    const int q = tid + c * PFC_WG;
-    const int g = s3_row(G, q & 63, ((q >> 6) & 7) - 2, (q >> 9) - 2);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) P.bv[c][k] = gld(bin + k * nn + g);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const Team& tm, const double* coef, bool init,
-                                        double* spart_out, S3Pre<T>& P, int par) {
-  constexpr int W15 = 15;
-  const int n = I.n, tid = threadIdx.x;
-  const long long nn = n;
-  const S3Geo G = s3_geo(tm.rank);
-  PcgOps<T> o = pcg_ops<T>(I, S.kind);
-  const PatView<PFC_COL_GRID> pv = op_pat<PFC_COL_GRID>(I, o, tm);
-  T* bout = (T*)I.sbas + (long long)(1 - par) * 5 * nn;
-  const T* bold = (const T*)I.sbas + (long long)par * 5 * nn;
-  const unsigned char* gdir = I.m.gdir;
-  T* sp = (T*)pfc_ss;          // new p on the two-step frame [4096]
-  T* su = sp + 4096;           // new u on the one-step frame [2304]
-  T* stp = su + 2304;          // T p on the one-step frame [2304]
-  T* sb = stp + 2304;          // right-hand side on the two-step frame (first launch of a solve) [4096]
-  static_assert(12800 * sizeof(T) <= sizeof(pfc_ss), "the frames of ph_scg3 exceed the s-step LDS");
-  // own row of this thread
-  const int ox = tid & 63, oyl = (tid >> 6) & 3, ozl = tid >> 8;
-  const int og = s3_row(G, ox, oyl, ozl);
-  if (init) {
-    // the solve's right-hand side b on the two-step frame and u_0 = p_0 = D^{-1} b;
-    // as ph_scg: b = t - s (A v) by solve kind
-    const long long n3 = 3 * nn;
-    const double* Vj = I.V + (long long)S.j * n3;
-    const int kind = S.kind;
-    const T* A = (kind == KIND_Y1 || kind == KIND_X2) ? o.Kv : (kind == KIND_Y0 ? nullptr : o.Mv);
-    const T* v = kind == KIND_Y1 ? (const T*)I.y0 : kind == KIND_Z ? (const T*)I.y1 : kind == KIND_X1 ? (const T*)I.zt
-                                                                                                      : (const T*)I.x1;
-    const double* t = kind == KIND_Y0 ? I.W : (kind == KIND_Y1 ? Vj + nn : (kind == KIND_X2 ? Vj + 2 * nn : nullptr));
-    const double ts = kind == KIND_Y0 ? S.vscale : 1.0, sa = kind == KIND_Y1 ? I.tau_p : 1.0;
-#pragma unroll
-    for (int c = 0; c < PFC_SS_NA; ++c) {
-      const int q = tid + c * PFC_WG;
-      const int g = s3_row(G, q & 63, ((q >> 6) & 7) - 2, (q >> 9) - 2);
-      const int base = (g >> 6) * 64 * W15 + (g & 63);
-      T d = T(0);
-      if (A) {
-#pragma unroll 5
-        for (int k = 0; k < W15; ++k) {
-          const long long e = (long long)base + k * 64;
-          d += gld(A + e) * gld(v + pv.at(e, g));
-        }
-      }
-      const double tt = t ? gld(t + g) * ts : 0.0;
-      const double b = !A ? tt : (t ? tt - sa * (double)d : (double)d);
-      P.bv[c][0] = gld(o.dinv + g);
-      P.bv[c][1] = T(b);
-      sb[q] = T(b);
-    }
-  } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
-    const T xo = gld(o.x + og);
-    const double p = gld(bold + og), tp = gld(bold + nn + og), u = gld(bold + 3 * nn + og);
-    vst(o.x + og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
-    return;
-  }
-  // operator rows of the one-step frame, issued before the new p and u are
-  // formed (whose basis loads they wait for) and in flight across the barrier
-  T av[2][W15], dv[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int q1 = tid + c * PFC_WG, t1 = q1 >> 6;
-    const int g = s3_row(G, q1 & 63, t1 % 6 - 1, t1 / 6 - 1);
-    const int base = (g >> 6) * 64 * W15 + (g & 63);
-#pragma unroll
-    for (int k = 0; k < W15; ++k) av[c][k] = opval_g(o, (long long)base + k * 64);
-    dv[c] = gld(o.dinv + g);
-  }
-  // new p on the two-step frame, new u on the one-step frame
-#pragma unroll
-  for (int c = 0; c < PFC_SS_NA; ++c) {
-    const int q = tid + c * PFC_WG;
-    const T* b = P.bv[c];
-    T pn, un;
-    if (init) {
-      pn = b[0] * b[1];
-      un = pn;
-    } else {
-      pn = T(coef[5] * b[0] + coef[6] * b[1] + coef[7] * b[2] + coef[8] * b[3] + coef[9] * b[4]);
-      un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
-    }
-    sp[q] = pn;
-    const int ly = (q >> 6) & 7, lz = q >> 9;
-    if (ly >= 1 && ly < 7 && lz >= 1 && lz < 7) su[(q & 63) + 64 * ((ly - 1) + 6 * (lz - 1))] = un;
-  }
-  lds_barrier();
-  // T p on the one-step frame
-  auto tprow = [&](int q1, const T* a, T di) {
-    const int x = q1 & 63, t1 = q1 >> 6, yl = t1 % 6 - 1, zl = t1 / 6 - 1;
-    const unsigned char* gd = gdir;
-    const int rb = PFC_S3_N * ((yl + 2) + 8 * (zl + 2));
-    T acc = T(0);
-#pragma unroll
-    for (int k = 0; k < W15; ++k) {
-      const int code = gd[k];
-      acc += a[k] * sp[s3_nx(x, code) + rb + s3_dline(code, 8)];
-    }
-    stp[q1] = di * acc;
-  };
-#pragma unroll
-  for (int c = 0; c < 2; ++c) tprow(tid + c * PFC_WG, av[c], dv[c]);
-  if (tid + 2 * PFC_WG < 2304) {  // the third pass: 256 rows
-    const int q1 = tid + 2 * PFC_WG, t1 = q1 >> 6;
-    const int g = s3_row(G, q1 & 63, t1 % 6 - 1, t1 / 6 - 1);
-    const int base = (g >> 6) * 64 * W15 + (g & 63);
-    T a3[W15];
-#pragma unroll
-    for (int k = 0; k < W15; ++k) a3[k] = opval_g(o, (long long)base + k * 64);
-    tprow(q1, a3, gld(o.dinv + g));
-  }
-  // the own row's operator row (a cache hit: the frame passes read it)
-  T ao[W15];
-  const int obase = (og >> 6) * 64 * W15 + (og & 63);
-#pragma unroll
-  for (int k = 0; k < W15; ++k) ao[k] = opval_g(o, (long long)obase + k * 64);
-  const T odi = gld(o.dinv + og);
-  lds_barrier();
-  // own row: T u, T^2 p, the stores and the Gram products
-  const unsigned char* gd = gdir;
-  const int rb1 = PFC_S3_N * ((oyl + 1) + 6 * (ozl + 1));
-  T au = T(0), att = T(0), dg = T(0);
-#pragma unroll
-  for (int k = 0; k < W15; ++k) {
-    const int code = gd[k];
-    const int i1 = s3_nx(ox, code) + rb1 + s3_dline(code, 6);
-    au += ao[k] * su[i1];
-    att += ao[k] * stp[i1];
-    dg += code == 13 ? ao[k] : T(0);
-  }
-  const int o2 = ox + PFC_S3_N * ((oyl + 2) + 8 * (ozl + 2)), o1 = ox + rb1;
-  const T pn = sp[o2], un = su[o1], tpo = stp[o1], tuo = odi * au, ttp = odi * att;
-  double bbo = 0.0;
-  if (init) {
-    const double bo = (double)sb[o2];
-    bbo = bo * bo;
-    vst(o.x + og, T(0));
-    const long long n3 = 3 * nn;
-    if (S.kind == KIND_Y0) {  // the Arnoldi vector v_j = w / ||w||
-      double* Vw = I.V + (long long)S.j * n3;
-      vst(Vw + og, gld(I.W + og) * S.vscale);
-      vst(Vw + nn + og, gld(I.W + nn + og) * S.vscale);
-      vst(Vw + 2 * nn + og, gld(I.W + 2 * nn + og) * S.vscale);
-    } else if (S.kind == KIND_X2) {  // (4): z_j = (y0 + (y1 - x1) / delta, x1, x2)
-      double* Zj = I.Z + (long long)S.j * n3;
-      const double y0i = (double)gld((const T*)I.y0 + og), y1i = (double)gld((const T*)I.y1 + og);
-      const double x1i = (double)gld((const T*)I.x1 + og);
-      vst(Zj + og, y0i + (y1i - x1i) / I.delta);
-      vst(Zj + nn + og, x1i);
-    }
-  } else {
-    const T xo = gld(o.x + og);
-    const double p = gld(bold + og), tp = gld(bold + nn + og), u = gld(bold + 3 * nn + og);
-    vst(o.x + og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
-  }
-  vst(bout + og, pn);
-  vst(bout + nn + og, tpo);
-  vst(bout + 2 * nn + og, ttp);
-  vst(bout + 3 * nn + og, un);
-  vst(bout + 4 * nn + og, tuo);
-  double gp[PFC_SS_NG];
-  {
-    const double dgo = (double)dg;
-    const double v[5] = {(double)pn, (double)tpo, (double)ttp, (double)un, (double)tuo};
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const double di = dgo * v[i];
-#pragma unroll
-      for (int j = i; j < 5; ++j) gp[ss_tri(i, j, 5)] = di * v[j];
-    }
-#pragma unroll
-    for (int i = 1; i < 5; ++i) {
-      const double di = dgo * dgo * v[i];
-#pragma unroll
-      for (int j = i; j < 5; ++j) gp[15 + ss_tri(i - 1, j - 1, 4)] = di * v[j];
-    }
-  }
-  gp[25] = bbo;
-  // workgroup sums as ph_scg: each wave by recursive halving, then over the waves
-  const int lane = tid & 63, wave = tid >> 6;
-  {
-    double v32[32];
-#pragma unroll
-    for (int m = 0; m < 32; ++m) v32[m] = m < PFC_SS_NG ? gp[m] : 0.0;
-    const double tot = ss_wave_sums32(v32, lane);
-    const int idx = ss_wave_sums32_index(lane);
-    if ((lane & 1) == 0) pfc_ssred[wave * 32 + idx] = tot;
-  }
-  lds_barrier();
-  if (tid < PFC_SS_NG) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < PFC_WAVES; ++w) t += pfc_ssred[w * 32 + tid];
-    vst(spart_out + (long long)tm.rank * 32 + tid, t);
-  }
-}
-
 // Row of a stored operator (or of M + cK), W entries from byte offset off.
 template <int W, typename T>
 __device__ __forceinline__ void op_row(const PcgOps<T>& o, unsigned off, T* a) {
@@ -1827,22 +1584,296 @@ __device__ __forceinline__ void op_row(const PcgOps<T>& o, unsigned off, T* a) {
       a[k] = gldo(o.Mv, off, k * 64 * (unsigned)sizeof(T)) + o.cK * gldo(o.Kv, off, k * 64 * (unsigned)sizeof(T));
   }
 }
-// frame steps of the W entries of a grid row (MeshDev::goff[f]), in scalar registers
-template <int W>
-struct GridOff {
-  int d[W];
+// the diagonal entry of such a row, at position k
+template <typename T>
+__device__ __forceinline__ T op_at(const PcgOps<T>& o, unsigned off, int k) {
+  const unsigned e = off + (unsigned)k * 64u * (unsigned)sizeof(T);
+  return o.C ? gldo(o.C, e) : gldo(o.Mv, e) + o.cK * gldo(o.Kv, e);
+}
+// frame steps of the entries of a row of class c: 2D (MeshDev::goff2), 3D (goff3)
+struct Steps2 {
+  unsigned long long w;
+  __device__ __forceinline__ int operator[](int k) const { return (int)(signed char)(w >> (8 * k)); }
 };
-template <int W>
-__device__ __forceinline__ GridOff<W> grid_off(const MeshDev& m, int f) {
-  GridOff<W> r;
-  const int* p = (const int*)m.goff[f];
-#pragma unroll
-  for (int q = 0; q < (W + 1) / 2; ++q) {
-    const int w = __builtin_amdgcn_readfirstlane(p[q]);
-    r.d[2 * q] = (short)w;
-    if (2 * q + 1 < W) r.d[2 * q + 1] = w >> 16;
+__device__ __forceinline__ Steps2 steps2(const MeshDev& m, int c, int f) { return Steps2{m.goff2[c][f]}; }
+typedef int Int4 __attribute__((ext_vector_type(4)));
+struct Steps3 {
+  Int4 a, b;
+  __device__ __forceinline__ int operator[](int k) const {
+    const int q = k >> 1;
+    const int w = q == 0 ? a.x : q == 1 ? a.y : q == 2 ? a.z : q == 3 ? a.w : q == 4 ? b.x : q == 5 ? b.y : q == 6 ? b.z : b.w;
+    return (k & 1) ? w >> 16 : (int)(short)w;
   }
-  return r;
+};
+__device__ __forceinline__ Steps3 steps3(const short* goff3, int c, int f) {
+  const unsigned o = (unsigned)(c * 2 + f) * 32u;
+  return Steps3{gldo((const Int4*)goff3, o), gldo((const Int4*)goff3, o, 16)};
+}
+
+// Gram products of a row's basis values with the diagonal entry dg, their sums over
+// the workgroup in fixed order (each wave by recursive halving, then over the waves)
+// and the workgroup's partial sums.  Every thread calls this.
+template <typename T>
+__device__ __forceinline__ void ss_gram_out(T dg, T p, T tp, T ttp, T u, T tu, double bb, double* out) {
+  double gp[32];
+  const double dgo = (double)dg;
+  const double v[5] = {(double)p, (double)tp, (double)ttp, (double)u, (double)tu};
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const double di = dgo * v[i];
+#pragma unroll
+    for (int j = i; j < 5; ++j) gp[ss_tri(i, j, 5)] = di * v[j];
+  }
+#pragma unroll
+  for (int i = 1; i < 5; ++i) {
+    const double di = dgo * dgo * v[i];
+#pragma unroll
+    for (int j = i; j < 5; ++j) gp[15 + ss_tri(i - 1, j - 1, 4)] = di * v[j];
+  }
+  gp[25] = bb;
+#pragma unroll
+  for (int m = PFC_SS_NG; m < 32; ++m) gp[m] = 0.0;
+  PFC_SS_STAMP(2);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double tot = ss_wave_sums32(gp, lane);
+  if ((lane & 1) == 0) pfc_ssred[wave * 32 + ss_wave_sums32_index(lane)] = tot;
+  lds_barrier();
+  if (tid < PFC_SS_NG) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < PFC_WAVES; ++w) t += pfc_ssred[w * 32 + tid];
+    vst(out + tid, t);
+  }
+  PFC_SS_STAMP(3);
+}
+
+// ---- two Jacobi-PCG iterations per launch on 3D periodic grids of side 64 -------
+// The s-step iteration of ph_scg with a workgroup's rows a block of the grid
+// instead of a range of rows: whole x-lines (64 rows, one SELL slice each) at
+// y0..y0+3, z0..z0+3, 1024 rows; rank r has y0 = 4 (r mod 16), z0 = 4 (r / 16).
+// The two-step frame is the 8 x 8 lines y0-2..y0+5, z0-2..z0+5, the one-step
+// frame the 6 x 6 lines y0-1..y0+4, z0-1..z0+4 (periodic in every direction).  A
+// line takes 66 places in LDS, with the row before its first and the one after its
+// last (periodic), so a neighbour's place is the row's plus the entry's step, the
+// same for every row of a class (MeshDev::goff3).  A wave owns one line, whose basis values
+// and operator rows stay in registers; of the 48 lines around the block in the
+// two-step frame it takes three, of the 20 in the one-step frame one (waves 0-3
+// two), each a whole line: a line's place and addresses are scalars.  New p and u
+// are formed on the frames, T p on the one-step frame, T u and T^2 p, the stores
+// and the Gram products on the own row.  T is the inner precision (float in
+// PFC_MIXED); the Gram sums and the coefficients stay float64.  Bound by the
+// instructions issued and the chain of round trips (as ph_scg2b): against passes
+// over the frames in thread order, wrapped neighbour places from a direction
+// table and a second read of the own rows, 1019 -> 793 vector instructions a wave
+// (3D 64^3 mixed step 20.7 -> 17.5 ms).
+#define PFC_S3_N 64
+#define PFC_S3_L 66  // places of a line
+__device__ __forceinline__ int s3_wrap(int v) { return v & (PFC_S3_N - 1); }
+struct S3Geo {
+  int y0, z0, wave, x;
+};
+__device__ __forceinline__ S3Geo s3_geo(int rank) {
+  return S3Geo{(rank & 15) * 4, (rank >> 4) * 4, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)),
+               (int)(threadIdx.x & 63)};
+}
+// a line at block coordinates (yl, zl); lb: its first row
+struct S3Line {
+  int yl, zl, lb;
+};
+__device__ __forceinline__ S3Line s3_line(const S3Geo& G, int yl, int zl) {
+  return S3Line{yl, zl, PFC_S3_N * (s3_wrap(G.y0 + yl) + PFC_S3_N * s3_wrap(G.z0 + zl))};
+}
+__device__ __forceinline__ S3Line s3_own(const S3Geo& G) { return s3_line(G, G.wave & 3, G.wave >> 2); }
+// line c (0..2) of the wave in the ring of the two-step frame
+__device__ __forceinline__ S3Line s3_ring2(const S3Geo& G, int c) {
+  const int w = G.wave;
+  if (c < 2) return s3_line(G, (w & 7) - 2, (w >> 3) + (c ? 4 : -2));
+  return s3_line(G, (w & 3) < 2 ? (w & 3) - 2 : (w & 3) + 2, w >> 2);
+}
+// line q (0..19) of the ring of the one-step frame
+__device__ __forceinline__ S3Line s3_ring1(const S3Geo& G, int q) {
+  if (q < 12) return s3_line(G, (q < 6 ? q : q - 6) - 1, q < 6 ? -1 : 4);
+  return s3_line(G, (q & 1) ? 4 : -1, (q - 12) >> 1);
+}
+// class (grid_class) of the lane's row of a line
+__device__ __forceinline__ int s3_class(const S3Geo& G, const S3Line& l) {
+  return grid_edge(G.x, PFC_S3_N) + 3 * grid_edge(s3_wrap(G.y0 + l.yl), PFC_S3_N) +
+         9 * grid_edge(s3_wrap(G.z0 + l.zl), PFC_S3_N);
+}
+// place of the lane's row of a line in the two-step and the one-step frame
+__device__ __forceinline__ int s3_p2(const S3Geo& G, const S3Line& l) { return G.x + 1 + PFC_S3_L * (l.yl + 2 + 8 * (l.zl + 2)); }
+__device__ __forceinline__ int s3_p1(const S3Geo& G, const S3Line& l) { return G.x + 1 + PFC_S3_L * (l.yl + 1 + 6 * (l.zl + 1)); }
+// store at place p and, from the line's ends, at the place beyond its other end
+template <typename T>
+__device__ __forceinline__ void s3_put(const S3Geo& G, T* f, int p, T v) {
+  f[p] = v;
+  if (G.x == 0 || G.x == PFC_S3_N - 1) f[G.x == 0 ? p + PFC_S3_N : p - PFC_S3_N] = v;
+}
+
+template <typename T>
+struct S3Pre {
+  T own[5], ring[3][5];
+};
+// the current basis on the two-step frame, issued before the reductions
+template <typename T>
+__device__ __forceinline__ void s3_load(const InstDev& I, const State& S, int rank, S3Pre<T>& P, int par) {
+  const long long nn = I.n;
+  const S3Geo G = s3_geo(rank);
+  const T* bin = uni((const T*)I.sbas + (long long)par * 5 * nn);
+  const unsigned xo = (unsigned)G.x * (unsigned)sizeof(T);
+  const int lo = s3_own(G).lb;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) P.own[k] = gldo(uni(bin + k * nn + lo), xo);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int lb = s3_ring2(G, c).lb;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) P.ring[c][k] = gldo(uni(bin + k * nn + lb), xo);
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const Team& tm, const double* coef, bool init,
+                                        double* spart_out, S3Pre<T>& P, int par) {
+  constexpr int W15 = 15;
+  constexpr unsigned TS = sizeof(T);
+  const int n = I.n, tid = threadIdx.x;
+  const long long nn = n;
+  const S3Geo G = s3_geo(tm.rank);
+  const PcgOps<T> o = pcg_ops<T>(I, S.kind);
+  T* bout = uni((T*)I.sbas + (long long)(1 - par) * 5 * nn);
+  T* sp = (T*)pfc_ss;                  // new p on the two-step frame
+  T* su = sp + 64 * PFC_S3_L;          // new u on the one-step frame
+  T* stp = su + 36 * PFC_S3_L;         // T p on the one-step frame
+  static_assert(136 * PFC_S3_L * sizeof(T) <= sizeof(pfc_ss), "the frames of ph_scg3 exceed the s-step LDS");
+  const S3Line lo = s3_own(G);
+  const unsigned xo = (unsigned)G.x * TS, xd = (unsigned)G.x * 8u;
+  T bo = T(0), dio = T(0), br[3], dir[3];
+  if (init) {
+    // the solve's right-hand side b on the two-step frame and u_0 = p_0 = D^{-1} b;
+    // as ph_scg: b = t - s (A v) by solve kind
+    const long long n3 = 3 * nn;
+    const double* Vj = uni(I.V + (long long)S.j * n3);
+    const int kind = __builtin_amdgcn_readfirstlane(S.kind);
+    const T* A = (kind == KIND_Y1 || kind == KIND_X2) ? o.Kv : (kind == KIND_Y0 ? nullptr : o.Mv);
+    const T* v = uni(kind == KIND_Y1 ? (const T*)I.y0 : kind == KIND_Z ? (const T*)I.y1 : kind == KIND_X1 ? (const T*)I.zt
+                                                                                                          : (const T*)I.x1);
+    const double* t = uni(kind == KIND_Y0 ? (const double*)I.W
+                                          : (kind == KIND_Y1 ? Vj + nn : (kind == KIND_X2 ? Vj + 2 * nn : nullptr)));
+    const double ts = kind == KIND_Y0 ? S.vscale : 1.0, sa = kind == KIND_Y1 ? I.tau_p : 1.0;
+    auto rhs = [&](const S3Line& l, T& b, T& di) {
+      T d = T(0);
+      if (A) {
+        const T* Al = A + (long long)l.lb * W15;
+        const int* gl = I.m.glin + s3_class(G, l) * PFC_GRID_W;
+        const int g = l.lb + G.x;
+#pragma unroll 5
+        for (int k = 0; k < W15; ++k) d += gldo(Al, xo, k * 64 * TS) * gldo(v, (unsigned)(g + gl[k]) * TS);
+      }
+      const double tt = t ? gldo(t + l.lb, xd) * ts : 0.0;
+      b = T(!A ? tt : (t ? tt - sa * (double)d : (double)d));
+      di = gldo(o.dinv + l.lb, xo);
+    };
+    rhs(lo, bo, dio);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rhs(s3_ring2(G, c), br[c], dir[c]);
+  } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
+    const double p = P.own[0], tp = P.own[1], u = P.own[3];
+    T* x = o.x + lo.lb;
+    vsto(x, xo, T((double)gldo((const T*)x, xo) + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+    return;
+  }
+  // operator rows of the own line and of the wave's line of the one-step ring, issued
+  // before the new p and u are formed (whose basis loads they wait for) and in
+  // flight across the barrier
+  T ao[W15], ar[W15], odi, rdi;
+  const S3Line l1 = s3_ring1(G, G.wave);
+  const short* goff3 = uni(I.m.goff3);
+  const Steps3 off1 = steps3(goff3, s3_class(G, lo), 0), off2 = steps3(goff3, s3_class(G, lo), 1);
+  Steps3 offr = steps3(goff3, s3_class(G, l1), 1);
+  const unsigned eo = (unsigned)lo.lb * W15 * TS + xo;
+  op_row<W15>(o, eo, ao);
+  odi = init ? dio : gldo(o.dinv + lo.lb, xo);
+  op_row<W15>(o, (unsigned)l1.lb * W15 * TS + xo, ar);
+  rdi = gldo(o.dinv + l1.lb, xo);
+  const T dg = op_at(o, eo, off1[15]);
+  const T xv = init ? T(0) : gldo((const T*)o.x + lo.lb, xo);
+  // new p on the two-step frame, new u on the one-step frame
+  auto pu = [&](const T* b, T& pn, T& un) {
+    pn = T(coef[5] * b[0] + coef[6] * b[1] + coef[7] * b[2] + coef[8] * b[3] + coef[9] * b[4]);
+    un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
+  };
+  T pn, un;
+  if (init) pn = un = dio * bo;
+  else pu(P.own, pn, un);
+  const int o2 = s3_p2(G, lo), o1 = s3_p1(G, lo);
+  s3_put(G, sp, o2, pn);
+  s3_put(G, su, o1, un);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const S3Line l = s3_ring2(G, c);
+    T pr, ur;
+    if (init) pr = ur = dir[c] * br[c];
+    else pu(P.ring[c], pr, ur);
+    s3_put(G, sp, s3_p2(G, l), pr);
+    if (l.yl >= -1 && l.yl <= 4 && l.zl >= -1 && l.zl <= 4) s3_put(G, su, s3_p1(G, l), ur);
+  }
+  lds_barrier();
+  PFC_SS_STAMP(0);
+  // T p on the one-step frame
+  auto tp_of = [&](const T* a, T di, int p2, const Steps3& off) {
+    T acc = T(0);
+#pragma unroll
+    for (int k = 0; k < W15; ++k) acc += a[k] * sp[p2 + off[k]];
+    return T(di * acc);
+  };
+  const T tpo = tp_of(ao, odi, o2, off2);
+  s3_put(G, stp, o1, tpo);
+  s3_put(G, stp, s3_p1(G, l1), tp_of(ar, rdi, s3_p2(G, l1), offr));
+  if (G.wave < 4) {  // the ring's last four lines
+    const S3Line l = s3_ring1(G, 16 + G.wave);
+    op_row<W15>(o, (unsigned)l.lb * W15 * TS + xo, ar);
+    offr = steps3(goff3, s3_class(G, l), 1);
+    s3_put(G, stp, s3_p1(G, l), tp_of(ar, gldo(o.dinv + l.lb, xo), s3_p2(G, l), offr));
+  }
+  lds_barrier();
+  PFC_SS_STAMP(1);
+  // own row: T u, T^2 p, the stores and the Gram products
+  T au = T(0), att = T(0);
+#pragma unroll
+  for (int k = 0; k < W15; ++k) {
+    const int i1 = o1 + off1[k];
+    au += ao[k] * su[i1];
+    att += ao[k] * stp[i1];
+  }
+  const T tuo = odi * au, ttp = odi * att;
+  double bbo = 0.0;
+  if (init) {
+    bbo = (double)bo * (double)bo;
+    vsto(o.x + lo.lb, xo, T(0));
+    const long long n3 = 3 * nn;
+    if (S.kind == KIND_Y0) {  // the Arnoldi vector v_j = w / ||w||
+      double* Vw = uni(I.V + (long long)S.j * n3 + lo.lb);
+      const double* W = uni(I.W + lo.lb);
+#pragma unroll
+      for (int blk = 0; blk < 3; ++blk) vsto(Vw + blk * nn, xd, gldo(W + blk * nn, xd) * S.vscale);
+    } else if (S.kind == KIND_X2) {  // (4): z_j = (y0 + (y1 - x1) / delta, x1, x2)
+      double* Zj = uni(I.Z + (long long)S.j * n3 + lo.lb);
+      const double y0i = (double)gldo(uni((const T*)I.y0 + lo.lb), xo), y1i = (double)gldo(uni((const T*)I.y1 + lo.lb), xo);
+      const double x1i = (double)gldo(uni((const T*)I.x1 + lo.lb), xo);
+      vsto(Zj, xd, y0i + (y1i - x1i) / I.delta);
+      vsto(Zj + nn, xd, x1i);
+    }
+  } else {
+    const double p = P.own[0], tp = P.own[1], u = P.own[3];
+    vsto(o.x + lo.lb, xo, T((double)xv + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+  }
+  vsto(bout + lo.lb, xo, pn);
+  vsto(bout + nn + lo.lb, xo, tpo);
+  vsto(bout + 2 * nn + lo.lb, xo, ttp);
+  vsto(bout + 3 * nn + lo.lb, xo, un);
+  vsto(bout + 4 * nn + lo.lb, xo, tuo);
+  ss_gram_out(dg, pn, tpo, ttp, un, tuo, bbo, spart_out + (long long)tm.rank * 32);
 }
 
 // ---- two Jacobi-PCG iterations per launch on blocks of 2D periodic grids -------
@@ -1852,7 +1883,7 @@ __device__ __forceinline__ GridOff<W> grid_off(const MeshDev& m, int f) {
 // 68 x 20 rows x0 - 2 .. x0 + 65, y0 - 2 .. y0 + 17, the one-step frame the
 // 66 x 18 rows x0 - 1 .. x0 + 64, y0 - 1 .. y0 + 16 (periodic), so a row's
 // neighbour in a frame is the row's frame position plus the entry's step, the
-// same for every row (MeshDev::goff).  Against a range of whole grid lines per
+// same for every row of a class (MeshDev::goff2).  Against a range of whole grid lines per
 // workgroup (ph_scg) the frames hold 1360 and 1188 rows instead of 3076 and 2050
 // at N = 512: the basis is read, and p and T p are formed, on fewer rows.
 // Thread t owns row x0 + t mod 64, y0 + t / 64 (a wave's own rows are one SELL
@@ -1863,8 +1894,8 @@ __device__ __forceinline__ GridOff<W> grid_off(const MeshDev& m, int f) {
 // issue (four waves a SIMD) and by its chain of round trips, not by bytes: frame
 // passes over all rows in thread order, with the own row's operator and basis read
 // again, division-built coordinates, a direction table in LDS and 64-bit address
-// arithmetic per load took 1097 vector instructions a wave, this form 699 (2D
-// 512^2 float64: stage solve 13.2 -> 10.1 ms, 128^2 mixed x 64 90.7 -> 72.4 ms a step).
+// arithmetic per load took 1097 vector instructions a wave, this form 648 (2D
+// 512^2 float64: stage solve 13.2 -> 10.0 ms, 128^2 mixed x 64 90.7 -> 71.0 ms a step).
 #define PFC_B2_W2 68
 #define PFC_B2_N2 (PFC_B2_W2 * 20)  // two-step frame
 #define PFC_B2_W1 66
@@ -1890,6 +1921,10 @@ __device__ __forceinline__ int b2_wrap(int v, int N) { return v < 0 ? v + N : (v
 // row at block coordinates (fx, fy), -3 <= fx < 67, -3 <= fy < 19
 __device__ __forceinline__ int b2_row(const B2Geo& G, int fx, int fy) {
   return b2_wrap(G.x0 + fx, G.N) + G.N * b2_wrap(G.y0 + fy, G.N);
+}
+// class (grid_class) of such a row
+__device__ __forceinline__ int b2_class(const B2Geo& G, int fx, int fy) {
+  return grid_edge(b2_wrap(G.x0 + fx, G.N), G.N) + 3 * grid_edge(b2_wrap(G.y0 + fy, G.N), G.N);
 }
 // block coordinates of row r of the ring of width d (rows 64 + 2 k wide) around
 // the frame k - d steps out: d full lines below, d above, then the sides
@@ -1983,6 +2018,7 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
     b2_ring<1, 1>(min(tid - PFC_B2_T2, PFC_B2_R1 - 1), rx, ry);
     rg = b2_row(G, rx, ry);
   }
+  const int co = b2_class(G, ox, oy), cr = b2_class(G, rx, ry);  // row classes
   const unsigned rge = (unsigned)((rg >> 6) * 64 * W7 + (rg & 63)) * TS;
   const int r1 = (rx + 1) + PFC_B2_W1 * (ry + 1), r2 = (rx + 2) + PFC_B2_W2 * (ry + 2);
   T x1f = T(0);  // x1 on the own row where this launch ends its solve
@@ -2023,29 +2059,28 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
       }
       lds_barrier();
     }
-    const GridOff<W7> off3 = grid_off<W7>(I.m, 2);
-    const PatView<PFC_COL_GRID> pv = op_pat<PFC_COL_GRID>(I, o, tm);
-    auto rhs = [&](int g, unsigned e, int q3, T& b, T& di) {
+    auto rhs = [&](int g, unsigned e, int c, int q3, T& b, T& di) {
       T d = T(0);
       if (A) {
         T a[W7];
 #pragma unroll
         for (int k = 0; k < W7; ++k) a[k] = gldo(A, e, k * 64 * TS);
         if (fz) {
+          const Steps2 off3 = steps2(I.m, c, 2);
 #pragma unroll
-          for (int k = 0; k < W7; ++k) d += a[k] * sv[q3 + off3.d[k]];
+          for (int k = 0; k < W7; ++k) d += a[k] * sv[q3 + off3[k]];
         } else {
-          const int base = (g >> 6) * 64 * W7 + (g & 63);
+          const int* gl = I.m.glin + c * PFC_GRID_W;
 #pragma unroll
-          for (int k = 0; k < W7; ++k) d += a[k] * gldo(v, (unsigned)pv.at((long long)base + k * 64, g) * TS);
+          for (int k = 0; k < W7; ++k) d += a[k] * gldo(v, (unsigned)(g + gl[k]) * TS);
         }
       }
       const double tt = t ? gldo(t, (unsigned)g * 8u) * ts : 0.0;
       b = T(!A ? tt : (t ? tt - sa * (double)d : (double)d));
       di = gldo(o.dinv, (unsigned)g * TS);
     };
-    rhs(gi, oe, o3, bo, dio);
-    if (w2) rhs(rg, rge, (rx + 3) + PFC_B2_W3 * (ry + 3), br, dir);
+    rhs(gi, oe, co, o3, bo, dio);
+    if (w2) rhs(rg, rge, cr, (rx + 3) + PFC_B2_W3 * (ry + 3), br, dir);
   } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
     const double p = P.own[0], tp = P.own[1], u = P.own[3];
     vsto(o.x, og, T((double)gldo(o.x, og) + (coef[0] * p + coef[1] * tp + coef[3] * u)));
@@ -2056,6 +2091,8 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
   T ao[W7], ar[W7], odi, rdi = T(0);
   op_row<W7>(o, oe, ao);
   odi = init ? dio : gldo(o.dinv, og);
+  const Steps2 off1 = steps2(I.m, co, 0);
+  const T dg = op_at(o, oe, off1[7]);
   const T xo = init ? T(0) : gldo(o.x, og);
   if (w1) {
     op_row<W7>(o, rge, ar);
@@ -2083,31 +2120,29 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
   lds_barrier();
   PFC_SS_STAMP(0);
   // T p on the one-step frame
-  const GridOff<W7> off2 = grid_off<W7>(I.m, 1);
-  auto tp_of = [&](const T* a, T di, int q2) {
+  auto tp_of = [&](const T* a, T di, int c, int q2) {
+    const Steps2 off2 = steps2(I.m, c, 1);
     T acc = T(0);
 #pragma unroll
-    for (int k = 0; k < W7; ++k) acc += a[k] * sp[q2 + off2.d[k]];
+    for (int k = 0; k < W7; ++k) acc += a[k] * sp[q2 + off2[k]];
     return T(di * acc);
   };
-  const T tpo = tp_of(ao, odi, o2);
+  const T tpo = tp_of(ao, odi, co, o2);
   stp[o1] = tpo;
   if (w1) {
-    const T tpr = tp_of(ar, rdi, r2);
+    const T tpr = tp_of(ar, rdi, cr, r2);
     if (in1) stp[r1] = tpr;
   }
   lds_barrier();
   PFC_SS_STAMP(1);
   // own row: T u, T^2 p, the stores and the Gram products
-  const GridOff<W7> off1 = grid_off<W7>(I.m, 0);
   T au = T(0), att = T(0);
 #pragma unroll
   for (int k = 0; k < W7; ++k) {
-    const int i1 = o1 + off1.d[k];
+    const int i1 = o1 + off1[k];
     au += ao[k] * su[i1];
     att += ao[k] * stp[i1];
   }
-  const T dg = ao[W7 / 2];
   const T tuo = odi * au, ttp = odi * att;
   double bbo = 0.0;
   if (init) {
@@ -2137,43 +2172,7 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
   vsto(uni(bout + 2 * nn), og, ttp);
   vsto(uni(bout + 3 * nn), og, un);
   vsto(uni(bout + 4 * nn), og, tuo);
-  double gp[PFC_SS_NG];
-  {
-    const double dgo = (double)dg;
-    const double v[5] = {(double)pn, (double)tpo, (double)ttp, (double)un, (double)tuo};
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const double di = dgo * v[i];
-#pragma unroll
-      for (int j = i; j < 5; ++j) gp[ss_tri(i, j, 5)] = di * v[j];
-    }
-#pragma unroll
-    for (int i = 1; i < 5; ++i) {
-      const double di = dgo * dgo * v[i];
-#pragma unroll
-      for (int j = i; j < 5; ++j) gp[15 + ss_tri(i - 1, j - 1, 4)] = di * v[j];
-    }
-  }
-  gp[25] = bbo;
-  PFC_SS_STAMP(2);
-  // workgroup sums as ph_scg: each wave by recursive halving, then over the waves
-  const int lane = tid & 63, wave = tid >> 6;
-  {
-    double v32[32];
-#pragma unroll
-    for (int m = 0; m < 32; ++m) v32[m] = m < PFC_SS_NG ? gp[m] : 0.0;
-    const double tot = ss_wave_sums32(v32, lane);
-    const int idx = ss_wave_sums32_index(lane);
-    if ((lane & 1) == 0) pfc_ssred[wave * 32 + idx] = tot;
-  }
-  lds_barrier();
-  if (tid < PFC_SS_NG) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < PFC_WAVES; ++w) t += pfc_ssred[w * 32 + tid];
-    vst(spart_out + (long long)tm.rank * 32 + tid, t);
-  }
-  PFC_SS_STAMP(3);
+  ss_gram_out(dg, pn, tpo, ttp, un, tuo, bbo, spart_out + (long long)tm.rank * 32);
 }
 
 // ---- orthogonalisation of an Arnoldi step (one reduction) ----------------------

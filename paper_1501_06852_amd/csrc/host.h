@@ -42,6 +42,7 @@ struct pfc_mesh {
   int* d_nv_el = nullptr;
   unsigned* d_nv_slot = nullptr;
   int* d_row_ptr = nullptr;            // CSR row offsets
+  short* d_goff3 = nullptr;            // MeshDev::goff3
   int* d_elem_nodes = nullptr;
   double* d_vol = nullptr;
   double* d_elemK = nullptr;           // element stiffness (P1 meshes), for the PFC1 mobility

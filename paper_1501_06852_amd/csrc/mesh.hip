@@ -229,10 +229,6 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_row_N(MeshDev m, const double* __
     });
   }
   if (!STAGE || !row_ptr) return;
-  __shared__ unsigned char row_class[PFC_ROW_T];
-  const unsigned char* cls = m.gdir_ok ? row_class : nullptr;
-  const int inner = m.dim == 2 ? 4 : 13;
-  if (m.gdir_ok) row_class[tid] = (unsigned char)(i < m.n ? grid_class(i, m.gN, m.gInv) : inner);
   __syncthreads();
   const int r0 = rank * T, r1 = min(r0 + T, m.n);
   if (r0 >= r1) return;
@@ -251,11 +247,7 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_row_N(MeshDev m, const double* __
         else hi = mid;
       }
     }
-    int k = m.zrow ? q - r * m.zrow : q - (row_ptr[r0 + r] - b0);
-    if (cls) {  // edge rows of grids: the column's stored position
-      const int c = cls[r];
-      if (c != inner) k = m.gcsr[c * PFC_GRID_W + k];
-    }
+    const int k = m.zrow ? q - r * m.zrow : q - (row_ptr[r0 + r] - b0);
     out[b0 + q] = pfc_row_lds[k * st + r];
   }
 }
@@ -359,7 +351,7 @@ static int upload(T** dst, const T* src, size_t count) {
 static void mesh_free(pfc_mesh* m) {
   if (!m) return;
   void* ptrs[] = {m->d_slice_ptr, m->d_col, m->d_M, m->d_K, m->d_Mf, m->d_Kf, m->d_dinvM, m->d_dinvMf,
-                  m->d_nv_ptr, m->d_nv_el, m->d_nv_slot, m->d_row_ptr, m->d_elem_nodes, m->d_vol,
+                  m->d_nv_ptr, m->d_nv_el, m->d_nv_slot, m->d_row_ptr, m->d_goff3, m->d_elem_nodes, m->d_vol,
                   m->d_w_slice_ptr, m->d_w_col, m->d_w_p1pos, m->d_w_tri_ptr, m->d_w_tri, m->d_elemK, m->d_p2tab};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -412,14 +404,15 @@ static int slot_of(const pfc_mesh* m, int row, int col) {
 // (grid_class) have the same column offsets j - i.  The offsets of a class are
 // read off its first row; every row, that one included, is then checked entry
 // by entry against grid_col.
-// Order of the stored entries of a grid mesh's rows by direction (MeshDev::gdir):
-// gdir [w], and per row class the stored position of each column in ascending
-// order (gcsr).  False (the rows keep ascending columns) if some entry is farther
-// than one step or some row has other directions than the interior rows.
-static bool detect_grid_dirs(const pfc_mesh* m, int w, int N, std::vector<unsigned char>& gdir,
-                             std::vector<unsigned char>& gcsr) {
+// Step of every entry of a grid mesh's rows (for sweeps over blocks of the grid):
+// per row class and entry (dx + 1) | (dy + 1) << 2 | (dz + 1) << 4, the step from the
+// row to the column (periodic, each component in -1..1), read off the class's first
+// row and checked on every row.  False if some entry is farther than one step.
+static bool detect_grid_dirs(const pfc_mesh* m, int w, int N, std::vector<unsigned char>& gdir) {
   const int n = m->n, dim = m->dim;
   const float inv = 1.0f / (float)N;
+  gdir.assign((size_t)PFC_GRID_CLASSES * PFC_GRID_W, 21);  // 21: no step
+  std::vector<char> have(PFC_GRID_CLASSES, 0);
   auto coord = [&](int v, int c) { return c == 0 ? v % N : (c == 1 ? (v / N) % N : v / (N * N)); };
   auto step = [&](int a, int b) {  // b - a on the circle of N, or 9 when farther than one step
     int d = b - a;
@@ -427,41 +420,20 @@ static bool detect_grid_dirs(const pfc_mesh* m, int w, int N, std::vector<unsign
     if (d < -(N / 2)) d += N;
     return (d >= -1 && d <= 1) ? d : 9;
   };
-  auto code_of = [&](int i, int j) {
-    int code = 0, mul = 1;
-    for (int c = 0; c < 3; ++c, mul *= 3) {
-      const int d = c < dim ? step(coord(i, c), coord(j, c)) : 0;
-      if (d == 9) return -1;
-      code += (d + 1) * mul;
-    }
-    return code;
-  };
-  gdir.assign(PFC_GRID_W, 13);  // 13: no step
-  gcsr.assign((size_t)PFC_GRID_CLASSES * PFC_GRID_W, 0);
-  int inner = 1 + N;  // the node one step from the origin in every direction
-  if (dim == 3) inner += N * N;
-  int where[27];
-  for (int& k : where) k = -1;
-  for (int k = 0; k < w; ++k) {
-    const int code = code_of(inner, m->col_idx[m->row_ptr[inner] + k]);
-    if (code < 0 || where[code] >= 0) return false;
-    gdir[k] = (unsigned char)code;
-    where[code] = k;
-  }
-  if (gdir[(w - 1) / 2] != 13) return false;
-  std::vector<char> have(PFC_GRID_CLASSES, 0);
   for (int i = 0; i < n; ++i) {
     const int cls = grid_class(i, N, inv);
-    unsigned seen = 0;
+    const int* col = m->col_idx.data() + m->row_ptr[i];
     for (int k = 0; k < w; ++k) {
-      const int code = code_of(i, m->col_idx[m->row_ptr[i] + k]);
-      if (code < 0 || where[code] < 0) return false;
-      unsigned char& g = gcsr[(size_t)cls * PFC_GRID_W + k];
-      if (!have[cls]) g = (unsigned char)where[code];
-      else if (g != where[code]) return false;
-      seen |= 1u << where[code];
+      int code = 0;
+      for (int c = 0; c < 3; ++c) {
+        const int d = c < dim ? step(coord(i, c), coord(col[k], c)) : 0;
+        if (d == 9) return false;
+        code |= (d + 1) << (2 * c);
+      }
+      unsigned char& g = gdir[(size_t)cls * PFC_GRID_W + k];
+      if (!have[cls]) g = (unsigned char)code;
+      else if (g != code) return false;
     }
-    if (seen != (1u << w) - 1u) return false;
     have[cls] = 1;
   }
   return true;
@@ -526,14 +498,6 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
 #ifndef PFC_NO_GRID_COLUMNS
   if (m->degree == 1 && m->uniform_width > 0 && !detect_grid(m, m->uniform_width, gN, glin)) gN = 0;
 #endif
-  // stored order of a row's entries: by direction on the grids that the block forms
-  // of the inner PCG take (2D sides 64 k, 3D side 64; the order differs in edge
-  // rows only), else as the columns ascend
-  std::vector<unsigned char> gdir, gcsr;
-  const bool dirs = gN && (m->dim == 2 ? gN % 64 == 0 : gN == 64) && detect_grid_dirs(m, m->uniform_width, gN, gdir, gcsr);
-  auto place = [&](int i, int k) {
-    return dirs ? (int)gcsr[(size_t)grid_class(i, gN, 1.0f / (float)gN) * PFC_GRID_W + k] : k;
-  };
   std::vector<int> scol((size_t)m->nnz_sell);
   m->csr2sell.assign(m->nnz, 0);
   for (int s = 0; s < m->n_slices; ++s) {
@@ -544,20 +508,13 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
       for (int kk = 0; kk < w; ++kk) {
         const long long pos = (long long)sptr[s] + kk * 64LL + l;
         if (kk < len) {
-          const long long at = (long long)sptr[s] + place(i, kk) * 64LL + l;
-          scol[at] = m->col_idx[m->row_ptr[i] + kk];
-          m->csr2sell[m->row_ptr[i] + kk] = at;
+          scol[pos] = m->col_idx[m->row_ptr[i] + kk];
+          m->csr2sell[m->row_ptr[i] + kk] = pos;
         } else {
           scol[pos] = i < n ? i : 0;
         }
       }
     }
-  }
-  if (dirs) {  // the offsets in the stored order
-    const std::vector<int> by_column = glin;
-    for (int c = 0; c < PFC_GRID_CLASSES; ++c)
-      for (int k = 0; k < m->uniform_width; ++k)
-        glin[(size_t)c * PFC_GRID_W + gcsr[(size_t)c * PFC_GRID_W + k]] = by_column[(size_t)c * PFC_GRID_W + k];
   }
   // simplices around each node, in element order, and the positions of their
   // nodes in the node's row
@@ -581,7 +538,7 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
   std::vector<int> at(n, -1), of(n, -1);  // position of a column in the row `of`
   for (int i = 0; i < n; ++i) {
     for (int t = m->row_ptr[i]; t < m->row_ptr[i + 1]; ++t) {
-      at[m->col_idx[t]] = place(i, t - m->row_ptr[i]);
+      at[m->col_idx[t]] = t - m->row_ptr[i];
       of[m->col_idx[t]] = i;
     }
     const long long vb = vptr[i / 64];
@@ -627,18 +584,33 @@ static int finish_layout(pfc_mesh* m, const int32_t* en, const std::vector<int>&
   d.gInv = gN ? 1.0f / (float)gN : 0.0f;
   std::memset(d.glin, 0, sizeof(d.glin));
   if (gN) std::memcpy(d.glin, glin.data(), sizeof(d.glin));
-  d.gdir_ok = dirs ? 1 : 0;
-  std::memset(d.gdir, 13, sizeof(d.gdir));
-  std::memset(d.gcsr, 0, sizeof(d.gcsr));
-  std::memset(d.goff, 0, sizeof(d.goff));
-  if (dirs) {
-    std::memcpy(d.gdir, gdir.data(), sizeof(d.gdir));
-    std::memcpy(d.gcsr, gcsr.data(), sizeof(d.gcsr));
-    for (int f = 0; f < 3; ++f)
-      for (int k = 0; k < m->uniform_width; ++k) {
-        const int dx = gdir[k] % 3 - 1, dy = gdir[k] / 3 % 3 - 1, dz = gdir[k] / 9 - 1;
-        d.goff[f][k] = (short)(m->dim == 2 ? dx + (66 + 2 * f) * dy : dx + 66 * (dy + (f == 0 ? 6 : 8) * dz));
+  // steps in the frames of the block forms
+  std::vector<unsigned char> gdir;
+  const int uw = m->uniform_width;
+  d.gdir_ok = gN && uw == (m->dim == 2 ? 7 : 15) && detect_grid_dirs(m, uw, gN, gdir) ? 1 : 0;
+  std::memset(d.goff2, 0, sizeof(d.goff2));
+  d.goff3 = nullptr;
+  if (d.gdir_ok) {
+    auto at = [&](int c, int k, int q) { return (gdir[(size_t)c * PFC_GRID_W + k] >> (2 * q) & 3) - 1; };
+    std::vector<short> off3((size_t)PFC_GRID_CLASSES * 2 * 16, 0);
+    for (int c = 0; c < PFC_GRID_CLASSES; ++c)
+      for (int k = 0; k < uw; ++k) {
+        const int dx = at(c, k, 0), dy = at(c, k, 1), dz = at(c, k, 2);
+        const bool diag = gdir[(size_t)c * PFC_GRID_W + k] == 21;
+        if (m->dim == 2 && c < 9)
+          for (int f = 0; f < 3; ++f) {
+            d.goff2[c][f] |= (unsigned long long)(unsigned char)(dx + (66 + 2 * f) * dy) << (8 * k);
+            if (diag) d.goff2[c][f] |= (unsigned long long)k << 56;
+          }
+        for (int f = 0; f < 2; ++f) {
+          off3[(size_t)(c * 2 + f) * 16 + k] = (short)(dx + 66 * (dy + (6 + 2 * f) * dz));
+          if (diag) off3[(size_t)(c * 2 + f) * 16 + 15] = (short)k;
+        }
       }
+    if (m->dim == 3) {
+      if ((rc = upload(&m->d_goff3, off3.data(), off3.size()))) return rc;
+      d.goff3 = m->d_goff3;
+    }
   }
   d.elem_nodes = m->d_elem_nodes; d.elem_vol = m->d_vol;
   return PFC_OK;

@@ -91,16 +91,14 @@ struct MeshDev {
   int gN;                 // periodic grid side N (grid_col), or 0
   float gInv;             // float(1 / N)
   int glin[PFC_GRID_CLASSES * PFC_GRID_W];  // column offset of each entry per row class (grid_col)
-  // gdir_ok: the entries of every row are stored in one order of their directions
-  // (dx + 1) + 3 (dy + 1) + 9 (dz + 1), the column's grid step from its row (periodic,
-  // each component in -1..1): that of an interior row's ascending columns, so that
-  // entry k of any row lies in direction gdir[k] and the diagonal in the middle.
-  // gcsr[class][t]: the stored position of a row's t-th column in ascending order.
-  // goff[f][k]: entry k's step in a frame of rows in LDS: 2D blocks, frames 66, 68
-  // and 70 rows wide; 3D blocks, lines of 66 in frames 6 and 8 lines wide
-  unsigned char gdir[PFC_GRID_W];
-  unsigned char gcsr[PFC_GRID_CLASSES * PFC_GRID_W];
-  __align__(4) short goff[3][PFC_GRID_W];
+  // gdir_ok: every entry of every row is one grid step from its row (periodic, each
+  // component in -1..1), the same steps in every row of a class; then, for frames of
+  // rows in LDS, entry k's step and the position of the diagonal per row class:
+  // 2D blocks (frames 66, 68 and 70 rows wide), goff2[class][f]: byte k, byte 7;
+  // 3D blocks (lines of 66 places, frames 6 and 8 lines wide), goff3[class][f][k],
+  // [15] (device memory)
+  unsigned long long goff2[9][3];
+  const short* goff3;
   int gdir_ok;
   const double* p2_M2;    // P2 reference tables (divided by |T|): M2[a][b],
   const double* p2_D;     //   D[i][j][a][b] = int d_i phi_a d_j phi_b (i, j barycentric),

@@ -176,11 +176,11 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_row_rhs(InstDev I, int stage, dou
   const long long e0 = (long long)base + lane;
   const WaveCols wc = wave_cols(I.m, sl, lane, e0);
   double b0, b1, b2;
-  stage_rhs_products(I, w, stage, [&](int k) { return e0 + 64LL * k; }, [&](int k) { return wc.at(k); },
-                     [&](int k, double mu, double ps) {
-                       sp[k * st] = ps;
-                       if constexpr (MOB) sm[k * st] = mu;
-                     }, b0, b1, b2);
+  const StageSums q = stage_rhs_products(I, w, stage, [&](int k) { return e0 + 64LL * k; },
+                                         [&](int k) { return wc.at(k); }, [&](int k, double mu, double ps) {
+                                           sp[k * st] = ps;
+                                           if constexpr (MOB) sm[k * st] = mu;
+                                         });
   double g = 0.0, kpm = 0.0;
   for_visits<Q, VisitU<Q>::lds, false, false>(I.m, sl, lane, [=](const Visit<Q>& v, int c) { return sp[v.slot(c) * st]; },
                                        [&](const Visit<Q>& v) {
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_row_rhs(InstDev I, int stage, dou
     if constexpr (MOB)
       kpm += visit_Kplus_mu<Q>(I.m, v, [=](const Visit<Q>& u, int c) { return sm[u.slot(c) * st]; }, I.psi_min);
   });
-  stage_rhs_finish(I, g, kpm, b0, b1);
+  stage_rhs_finish(I, q, stage, g, kpm, b0, b1, b2);
   if (i < n) { b[i] = b0; b[n + i] = b1; b[2 * n + i] = b2; }
 }
 

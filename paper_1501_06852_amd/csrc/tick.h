@@ -559,13 +559,19 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
       if (idx < len) pfc_lcol[idx] = cv[q];
     }
   }
-  pre.a += pre2.a;
-  pre.b += pre2.b;
-  pre.c += pre2.c;
-  pre.a = wave_sum(pre.a);
-  pre.b = wave_sum(pre.b);
-  pre.c = wave_sum(pre.c);
-  if ((tid & 63) == 0) lds4[tid >> 6] = pre;
+  // their sums over the waves, where the previous launch left any: two-iteration
+  // launches leave Gram partials instead.  Launches that serve many instances and
+  // have that form know their phase only after the barrier below, and sum there.
+  constexpr bool LATE = !SINGLE && SB2;
+  auto sum_partials = [&]() {
+    pre.a = wave_sum(pre.a + pre2.a);
+    pre.b = wave_sum(pre.b + pre2.b);
+    pre.c = wave_sum(pre.c + pre2.c);
+    if ((tid & 63) == 0) lds4[tid >> 6] = pre;
+  };
+  if constexpr (!LATE) {
+    if (!SINGLE || phase_partials(ph_in)) sum_partials();
+  }
   __syncthreads();
 #ifdef PFC_TICK_TIMING
   const unsigned long long t_ld = wall_clock64();
@@ -576,6 +582,12 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     kind_in = S0.kind;
     pcur_in = S0.pcur;
     if constexpr (SB2) fuse_in = S0.fuse;
+    if constexpr (LATE) {
+      if (phase_partials(ph_in)) {
+        sum_partials();
+        __syncthreads();
+      }
+    }
   }
   const InstDev& I = sI;
   const bool writer = (te.rank == 0);
