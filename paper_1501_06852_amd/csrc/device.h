@@ -150,7 +150,7 @@ __device__ __forceinline__ Red3 wg_sum3(Red3 v, Red3* lds4) {
   const int _sbeg = _rr ? (tm).rank : (tm).rank * _spw;                            \
   const int _send = _rr ? (I).m.n_slices : min(_sbeg + _spw, (I).m.n_slices);      \
   const int _sstep = _rr ? (tm).size * PFC_WAVES : PFC_WAVES;                      \
-  for (int sl = _sbeg + (_rr ? (tm).size * (tm).wave : (tm).wave); sl < _send; sl += _sstep)
+  for (int sl = __builtin_amdgcn_readfirstlane(_sbeg + (_rr ? (tm).size * (tm).wave : (tm).wave)); sl < _send; sl += _sstep)
 
 // Row loops over the entries of a slice: the P1 meshes of this solver have 7
 // (2D) or 15 (3D) entries per row, 2D P2 meshes 19 (vertex rows) or 9 (edge
@@ -231,6 +231,70 @@ template <typename T>
 __device__ __forceinline__ void vsto(T* base, unsigned off, T v) {
   typedef __attribute__((address_space(1))) char* P;
   vst((T*)((P)base + off), v);
+}
+
+// Rows of the solver phases.  A slice belongs to one wave, so its place in the
+// value arrays is a scalar; f(W) is called with the slice's width as a constant
+// (0: some other width) for the widths named at for_width.
+template <bool P2, typename F>
+__device__ __forceinline__ void with_width(int w, F f) {
+  if (w == 7) { f(std::integral_constant<int, 7>()); return; }
+  if (w == 15) { f(std::integral_constant<int, 15>()); return; }
+  if constexpr (P2) {
+    if (w == 9) { f(std::integral_constant<int, 9>()); return; }
+    if (w == 19) { f(std::integral_constant<int, 19>()); return; }
+  }
+  f(std::integral_constant<int, 0>());
+}
+// the columns of the row of (slice, lane), all loaded (or computed) at once
+template <int W, int L>
+__device__ __forceinline__ void row_cols(const PatView<L>& pv, int sl, int lane, int* j) {
+  const int i = sl * 64 + lane;
+  if constexpr (L == PFC_COL_GRID) {
+    const int r = i < pv.n ? i : pv.n - 1;
+    const int* gl = pv.gd + grid_class(r, pv.gN, pv.gInv) * PFC_GRID_W;
+#pragma unroll
+    for (int k = 0; k < W; ++k) j[k] = r + gl[k];
+  } else if constexpr (L == PFC_COL_LDS) {
+    const int* c = pfc_lcol + (pv.base(sl) + lane - pv.lo);
+#pragma unroll
+    for (int k = 0; k < W; ++k) j[k] = c[64 * k];
+  } else {
+    const int* c = uni(pv.col + pv.base(sl));
+#pragma unroll
+    for (int k = 0; k < W; ++k) j[k] = gldo(c, (unsigned)lane * 4u, k * 256u);
+  }
+}
+// sum over the entries of the row of (slice, lane), in order: load(k, j) gives what
+// entry k needs of memory (column j), use(v) adds it.  The columns are loaded at
+// once and the entries in chunks of CH, whose loads are issued together: a chunk is
+// one round trip (the columns' and the entries' loads one entry after the other
+// are two each).  Chunks: C::of(W, L) entries.
+template <typename C, int L, typename LoadF, typename UseF>
+__device__ __forceinline__ void row_entries(const PatView<L>& pv, int sl, int lane, LoadF load, UseF use) {
+  with_width<L == PFC_COL_MEM>(pv.width(sl), [&](auto wc) {  // (rows of 9 and 19 entries have no common width)
+    constexpr int W = decltype(wc)::value;
+    if constexpr (W > 0) {
+      constexpr int CH = C::of(W, L);
+      int j[W];
+      row_cols<W>(pv, sl, lane, j);
+#pragma unroll
+      for (int c = 0; c < W; c += CH) {
+        decltype(load(0, 0)) v[CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (c + u < W) v[u] = load(c + u, j[c + u]);
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (c + u < W) use(v[u]);
+        __builtin_amdgcn_sched_barrier(0);  // (the next chunk's loads would not fit beside this one's)
+        asm volatile("" ::: "memory");
+      }
+    } else {
+      const int w = pv.width(sl), e0 = pv.base(sl) + lane;
+      for (int k = 0; k < w; ++k) use(load(k, pv.at((long long)e0 + 64LL * k, sl * 64 + lane)));
+    }
+  });
 }
 
 // Workgroup placement.  The dispatcher deals the workgroups of a launch to the
@@ -746,7 +810,7 @@ __device__ __forceinline__ void stage_rhs_row(const InstDev& I, const PatView<L>
 template <int L>
 __device__ __forceinline__ Red3 ph_solve_init(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
-  const bool rb = (S.job == JOB_RB);
+  const bool rb = __builtin_amdgcn_readfirstlane(S.job) == JOB_RB;
   const PatView<L> pv = p1_pat<L>(I, tm);
   double* X = rb ? (I.ys + (long long)(S.stage - 1) * 3 * n) : I.x_user;
   const double im = I.rs;
@@ -866,23 +930,72 @@ __device__ __forceinline__ T opval_g(const PcgOps<T>& o, long long e) {
   return o.C ? gld(o.C + e) : (gld(o.Mv + e) + o.cK * gld(o.Kv + e));
 }
 
-// y_i = (A v)_i for a stored operator A (typed) over the row of thread lane
-template <typename T, int L, typename VF>
-__device__ __forceinline__ T row_dot(const PatView<L>& pv, int sl, int lane, const T* A, VF v) {
+// values of a slice's entries: entry k of the lane's row, W entries a slice
+template <typename T>
+struct SliceVals {
+  const T* a;
+  unsigned off;
+  __device__ __forceinline__ T operator()(int k) const { return gldo(a, off + (unsigned)k * 64u * (unsigned)sizeof(T)); }
+};
+template <typename T>
+__device__ __forceinline__ SliceVals<T> slice_vals(const T* a, int base, int lane) {
+  return SliceVals<T>{uni(a + base), (unsigned)lane * (unsigned)sizeof(T)};
+}
+// row_entries over a row of an operator, stored or M + cK (one choice for the row:
+// a branch per entry would keep its loads apart); load(a, j) with the value a
+template <typename C, typename T, int L, typename LoadF, typename UseF>
+__device__ __forceinline__ void op_entries(const PcgOps<T>& o, const PatView<L>& pv, int sl, int lane, LoadF load, UseF use) {
   const int base = pv.base(sl);
-  const int w = pv.width(sl);
+  if (o.C) {
+    const SliceVals<T> c = slice_vals(o.C, base, lane);
+    row_entries<C>(pv, sl, lane, [&](int k, int j) { return load(c(k), j); }, use);
+  } else {
+    const SliceVals<T> m = slice_vals(o.Mv, base, lane), q = slice_vals(o.Kv, base, lane);
+    row_entries<C>(pv, sl, lane, [&](int k, int j) { return load(m(k) + o.cK * q(k), j); }, use);
+  }
+}
+// Chunks of the row loops: as many entries as the kernel's 128 registers hold beside
+// the rest of the phase without spilling (the grid kernels also hold the block forms).
+template <typename T>
+struct ChunkIter {  // five values an entry
+  static constexpr int of(int W, int L) {
+    if (sizeof(T) == 8) return L == PFC_COL_MEM ? (W == 9 ? 5 : 4) : (W == 7 ? 3 : 4);
+    return L == PFC_COL_MEM ? (W == 9 ? 9 : 7) : (W == 7 ? 4 : 7);
+  }
+};
+struct ChunkInit {  // three
+  static constexpr int of(int, int L) { return L == PFC_COL_GRID ? 4 : 6; }
+};
+struct ChunkBlock {  // six (eight with the mobility)
+  static constexpr int of(int, int) { return 2; }
+};
+struct ChunkDot {  // two
+  static constexpr int of(int, int L) { return L == PFC_COL_GRID ? 4 : 8; }
+};
+
+// an entry of a vector of T
+template <typename T>
+__device__ __forceinline__ T vat(const T* v, int j) { return gldo(v, (unsigned)j * (unsigned)sizeof(T)); }
+
+// y_i = (A v)_i for a stored operator A (typed) over the row of thread lane
+template <typename T>
+struct DotTerm {
+  T a, v;
+};
+template <typename T, int L>
+__device__ __forceinline__ T row_dot(const PatView<L>& pv, int sl, int lane, const T* A, const T* v) {
+  const SliceVals<T> a = slice_vals(A, pv.base(sl), lane);
+  const T* u = uni(v);
   T acc = T(0);
-  for_width(w, [&](int k) {
-    const long long e = (long long)base + k * 64 + lane;
-    acc += A[e] * v(pv.at(e, sl * 64 + lane));
-  });
+  row_entries<ChunkDot>(pv, sl, lane, [&](int k, int j) { return DotTerm<T>{a(k), vat(u, j)}; },
+                 [&](const DotTerm<T>& t) { acc += t.a * t.v; });
   return acc;
 }
 
 template <typename T, int L>
 __device__ __forceinline__ Red3 ph_pcg_setup(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
-  const int kind = S.kind;
+  const int kind = __builtin_amdgcn_readfirstlane(S.kind);
   PcgOps<T> o = pcg_ops<T>(I, kind);
   const PatView<L> pv = p1_pat<L>(I, tm);   // every right-hand side is a P1 product
   T* r = (T*)I.r_;
@@ -907,23 +1020,23 @@ __device__ __forceinline__ Red3 ph_pcg_setup(const InstDev& I, const State& S, c
       } break;
       case KIND_Y1: {  // (2): b1 - tau K y0
         const T* y0 = (const T*)I.y0;
-        const T ky = row_dot<T>(pv, sl, lane, Kv, [&](int j) { return y0[j]; });
+        const T ky = row_dot<T>(pv, sl, lane, Kv, y0);
         if (i < n) rhs = Vj[n + i] - I.tau_p * (double)ky;
       } break;
       case KIND_SD:   // (3) with S_D: M y1
       case KIND_Z: {  // (3.1): M y1
         const T* y1 = (const T*)I.y1;
-        const T my = row_dot<T>(pv, sl, lane, Mv, [&](int j) { return y1[j]; });
+        const T my = row_dot<T>(pv, sl, lane, Mv, y1);
         rhs = (double)my;
       } break;
       case KIND_X1: {  // (3.2): M z
         const T* zt = (const T*)I.zt;
-        const T mz = row_dot<T>(pv, sl, lane, Mv, [&](int j) { return zt[j]; });
+        const T mz = row_dot<T>(pv, sl, lane, Mv, zt);
         rhs = (double)mz;
       } break;
       case KIND_X2: {  // (5): b2 - K x1, and (4): x0 = y0 + (y1 - x1)/delta
         const T* x1 = (const T*)I.x1;
-        const T kx = row_dot<T>(pv, sl, lane, Kv, [&](int j) { return x1[j]; });
+        const T kx = row_dot<T>(pv, sl, lane, Kv, x1);
         if (i < n) {
           rhs = Vj[2 * n + i] - (double)kx;
           const double y0i = (double)((const T*)I.y0)[i], y1i = (double)((const T*)I.y1)[i];
@@ -933,7 +1046,7 @@ __device__ __forceinline__ Red3 ph_pcg_setup(const InstDev& I, const State& S, c
         }
       } break;
       case KIND_CI_OMEGA: {  // M omega_0 = -K psi_0
-        const double kp = row_dot<double>(pv, sl, lane, I.m.K, [&](int j) { return I.xk[n + j]; });
+        const double kp = row_dot<double>(pv, sl, lane, I.m.K, I.xk + n);
         rhs = -kp;
       } break;
       case KIND_CI_MU: {  // M mu_0 = (1+r) M psi_0 - 2 K psi_0 - K omega_0 + g(psi_0)
@@ -1032,23 +1145,34 @@ __device__ __forceinline__ Red3 ph_pcg_b(const InstDev& I, const State& S, const
 //   w1 = t K mu + s M psi
 //   w2 = K psi + M omega
 //   PFC1 (MOB): w1 = t K_+ mu + s M psi + t F psi
-template <int L, bool MOB, typename YF>
+template <typename X2>
+struct BlockVec {  // mu and psi in one vector, omega in another (of X2)
+  const double* v;
+  const X2* om;
+};
+template <int L, bool MOB, typename X2>
 __device__ __forceinline__ void block_row(const InstDev& I, const PatView<L>& pv, int sl, int lane, double t, double s,
-                                          YF y, double& w0, double& w1, double& w2) {
-  const int base = pv.base(sl);
-  const int w = pv.width(sl);
+                                          BlockVec<X2> y, double& w0, double& w1, double& w2) {
   const double c1 = -(1.0 + I.r);
+  const int base = pv.base(sl);
+  const SliceVals<double> M = slice_vals(I.m.M, base, lane), K = slice_vals(I.m.K, base, lane), N = slice_vals((const double*)I.N, base, lane);
+  const SliceVals<double> Kp = slice_vals((const double*)I.Kp, MOB ? base : 0, lane), Fm = slice_vals((const double*)I.Fm, MOB ? base : 0, lane);
+  const double* mu = uni(y.v);
+  const double* ps = uni(y.v + I.n);
+  const X2* om = uni(y.om);
+  struct Term {
+    double M, K, N, Kp, Fm, mu, ps;
+    X2 om;
+  };
   w0 = w1 = w2 = 0.0;
-  for_width(w, [&](int k) {
-    const long long e = (long long)base + k * 64 + lane;
-    const int j = pv.at(e, sl * 64 + lane);
-    const double Mv = I.m.M[e], Kv = I.m.K[e], Nv = I.N[e];
-    double mu, ps, om;
-    y(j, mu, ps, om);
-    w0 += Mv * mu + (c1 * Mv + 2.0 * Kv + Nv) * ps + Kv * om;
-    if constexpr (MOB) w1 += t * I.Kp[e] * mu + s * Mv * ps + t * I.Fm[e] * ps;
-    else w1 += t * Kv * mu + s * Mv * ps;
-    w2 += Kv * ps + Mv * om;
+  row_entries<ChunkBlock>(pv, sl, lane, [&](int k, int j) {
+    return Term{M(k), K(k), N(k), MOB ? Kp(k) : 0.0, MOB ? Fm(k) : 0.0, vat(mu, j), vat(ps, j), vat(om, j)};
+  }, [&](const Term& q) {
+    const double qo = (double)q.om;
+    w0 += q.M * q.mu + (c1 * q.M + 2.0 * q.K + q.N) * q.ps + q.K * qo;
+    if constexpr (MOB) w1 += t * q.Kp * q.mu + s * q.M * q.ps + t * q.Fm * q.ps;
+    else w1 += t * q.K * q.mu + s * q.M * q.ps;
+    w2 += q.K * q.ps + q.M * qo;
   });
 }
 
@@ -1076,7 +1200,7 @@ __device__ __forceinline__ Red3 ph_true_res(const InstDev& I, const State& S, co
   const int n = I.n;
   const PatView<L> pv = p1_pat<L>(I, tm);
   const long long n3 = 3LL * n;
-  const bool rb = (S.job == JOB_RB);
+  const bool rb = __builtin_amdgcn_readfirstlane(S.job) == JOB_RB;
   const double* X = rb ? (I.ys + (long long)(S.stage - 1) * n3) : I.x_user;
   const double* bsrc = rb ? I.b : I.b_user;
   const double im = I.rs;
@@ -1084,9 +1208,7 @@ __device__ __forceinline__ Red3 ph_true_res(const InstDev& I, const State& S, co
   PFC_SLICES(I, tm) {
     const int i = sl * 64 + tm.lane;
     double w0, w1, w2;
-    block_row<L, MOB>(I, pv, sl, tm.lane, I.tau, I.m11,
-              [&](int j, double& mu, double& ps, double& om) { mu = X[j]; ps = X[n + j]; om = X[2 * n + j]; },
-              w0, w1, w2);
+    block_row<L, MOB, double>(I, pv, sl, tm.lane, I.tau, I.m11, {X, X + 2LL * n}, w0, w1, w2);
     if (i < n) {
       const double r0 = bsrc[i] - w0, r1 = bsrc[n + i] - w1, r2 = bsrc[2 * n + i] - w2;
       const double rs1 = r1 * im;
@@ -1122,82 +1244,79 @@ __device__ __forceinline__ Red3 ph_pch_out(const InstDev& I, const Team& tm) {
 //   alpha_{i+1} = gamma_{i+1} / (delta_{i+1} - beta_{i+1} gamma_{i+1} / alpha_i).
 // u_{i+1} at gathered neighbours is recomputed from r_i, w_i, s_{i-1}; r, w, s
 // are double-buffered, p and x are updated in place by their owners.
-template <typename T>
-__device__ __forceinline__ T cg_s(const T* wc, const T* so, T beta, bool first, int j) {
-  return first ? wc[j] : (wc[j] + beta * so[j]);
-}
-template <typename T>
-__device__ __forceinline__ T cg_unew(const T* dinv, const T* rc, const T* wc, const T* so, T alpha, T beta, bool first,
-                                      int j) {
-  return dinv[j] * (rc[j] - alpha * cg_s(wc, so, beta, first, j));
-}
-
 template <typename T, int L>
 __device__ __forceinline__ Red3 ph_cg_init(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
   PcgOps<T> o = pcg_ops<T>(I, S.kind);
   const PatView<L> pv = op_pat<L>(I, o, tm);
-  const T* r = (const T*)I.r_;
-  T* w = (T*)I.q;
+  const T* r = uni((const T*)I.r_);
+  T* w = uni((T*)I.q);
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+  struct Term {
+    T a, d, r;
+  };
   PFC_SLICES(I, tm) {
     const int i = sl * 64 + tm.lane;
-    const int base = pv.base(sl);
-    const int wd = pv.width(sl);
     T acc = T(0);
-    for_width(wd, [&](int k) {
-      const long long e = (long long)base + k * 64 + tm.lane;
-      const int j = pv.at(e, i);
-      acc += opval(o, e) * (o.dinv[j] * r[j]);
-    });
+    op_entries<ChunkInit>(o, pv, sl, tm.lane, [&](T a, int j) { return Term{a, vat(o.dinv, j), vat(r, j)}; },
+                  [&](const Term& t) { acc += t.a * (t.d * t.r); });
     if (i < n) {
-      vst(w + i, acc);
-      const T u = o.dinv[i] * r[i];
-      a0 += (double)r[i] * (double)u;
+      const unsigned oi = (unsigned)i * (unsigned)sizeof(T);
+      vsto(w, oi, acc);
+      const T ri = gldo(r, oi), u = gldo(o.dinv, oi) * ri;
+      a0 += (double)ri * (double)u;
       a1 += (double)acc * (double)u;
-      a2 += (double)r[i] * (double)r[i];
+      a2 += (double)ri * (double)ri;
     }
   }
   return red3(a0, a1, a2);
 }
 
+// One iteration.  Bound by the round trips of the gathers (four vectors at every
+// neighbour), so the columns of a row are loaded at once and its entries in chunks
+// that the registers hold (5 in float64: 4 + 1 round trips for the 19 entries of a
+// P2 vertex row instead of 14): P2 256^2 float64 solve 80.6 -> 65.4 ms.
 template <typename T, int L>
 __device__ __forceinline__ Red3 ph_cg_iter(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
   PcgOps<T> o = pcg_ops<T>(I, S.kind);
   const PatView<L> pv = op_pat<L>(I, o, tm);
-  const int c = S.cur;
-  const T* rc = (const T*)(c ? I.rB : I.r_);
-  T* rn = (T*)(c ? I.r_ : I.rB);
-  const T* wc = (const T*)(c ? I.wB : I.q);
-  T* wn = (T*)(c ? I.q : I.wB);
-  const T* so = (const T*)(c ? I.sB : I.sA);
-  T* sn = (T*)(c ? I.sA : I.sB);
-  T* p = (T*)I.pA;
-  const T alpha = T(S.alpha), beta = T(S.beta_cg);
-  const bool first = (S.it == 0);
+  const int c = __builtin_amdgcn_readfirstlane(S.cur);
+  const T* rc = uni((const T*)(c ? I.rB : I.r_));
+  T* rn = uni((T*)(c ? I.r_ : I.rB));
+  const T* wc = uni((const T*)(c ? I.wB : I.q));
+  T* wn = uni((T*)(c ? I.q : I.wB));
+  T* sn = uni((T*)(c ? I.sA : I.sB));
+  T* p = uni((T*)I.pA);
+  // the first iteration has no previous s (s = w + 0 w) and no previous p
+  const bool first = __builtin_amdgcn_readfirstlane(S.it) == 0;
+  const T* so = first ? wc : uni((const T*)(c ? I.sB : I.sA));
+  const T alpha = T(S.alpha), beta = first ? T(0) : T(S.beta_cg);
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+  struct Term {
+    T a, d, r, w, s;
+  };
+  auto s_of = [&](T w, T s) { return w + beta * s; };
   PFC_SLICES(I, tm) {
     const int i = sl * 64 + tm.lane;
-    const int base = pv.base(sl);
-    const int wd = pv.width(sl);
+    const unsigned oi = (unsigned)(i < n ? i : n - 1) * (unsigned)sizeof(T);
+    const T di = gldo(o.dinv, oi), ro = gldo(rc, oi), wo = gldo(wc, oi), so_ = gldo(so, oi), po = gldo((const T*)p, oi),
+            xo = gldo((const T*)o.x, oi);
     T acc = T(0);
-    for_width(wd, [&](int k) {
-      const long long e = (long long)base + k * 64 + tm.lane;
-      const int j = pv.at(e, i);
-      acc += opval(o, e) * cg_unew(o.dinv, rc, wc, so, alpha, beta, first, j);
-    });
+    op_entries<ChunkIter<T>>(
+        o, pv, sl, tm.lane, [&](T a, int j) { return Term{a, vat(o.dinv, j), vat(rc, j), vat(wc, j), vat(so, j)}; },
+        [&](const Term& t) { acc += t.a * (t.d * (t.r - alpha * s_of(t.w, t.s))); });
     if (i < n) {
-      const T si = cg_s(wc, so, beta, first, i);
-      const T uo = o.dinv[i] * rc[i];
-      const T pi = first ? uo : (uo + beta * p[i]);
-      vst(o.x + i, o.x[i] + alpha * pi);
-      const T ri = rc[i] - alpha * si;
-      const T ui = cg_unew(o.dinv, rc, wc, so, alpha, beta, first, i);
-      vst(sn + i, si);
-      vst(p + i, pi);
-      vst(rn + i, ri);
-      vst(wn + i, acc);
+      const T si = s_of(wo, so_);
+      const T uo = di * ro;
+      const T pi = first ? uo : (uo + beta * po);
+      vsto(o.x, oi, T(xo + alpha * pi));
+      const T ri = ro - alpha * si;
+      const T ui = di * (ro - alpha * si);
+      vsto(sn, oi, si);
+      vsto(p, oi, pi);
+      vsto(rn, oi, ri);
+      vsto(wn, oi, acc);
       a0 += (double)ri * (double)ui;
       a1 += (double)acc * (double)ui;
       a2 += (double)ri * (double)ri;
@@ -1379,7 +1498,7 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
       }
     }
   }
-  if (!init && S.pcur) {  // the solve ends within these two iterations: x only
+  if (!init && __builtin_amdgcn_readfirstlane(S.pcur)) {  // the solve ends within these two iterations: x only
     if (w.own) {
 #pragma unroll
       for (int c = 0; c < PFC_SS_NA; ++c)
@@ -1665,7 +1784,7 @@ __device__ __forceinline__ void ss_gram_out(T dg, T p, T tp, T ttp, T u, T tu, d
 // instructions issued and the chain of round trips (as ph_scg2b): against passes
 // over the frames in thread order, wrapped neighbour places from a direction
 // table and a second read of the own rows, 1019 -> 793 vector instructions a wave
-// (3D 64^3 mixed step 20.7 -> 17.5 ms).
+// (3D 64^3 mixed step 20.7 -> 17.0 ms).
 #define PFC_S3_N 64
 #define PFC_S3_L 66  // places of a line
 __device__ __forceinline__ int s3_wrap(int v) { return v & (PFC_S3_N - 1); }
@@ -1777,35 +1896,36 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
     rhs(lo, bo, dio);
 #pragma unroll
     for (int c = 0; c < 3; ++c) rhs(s3_ring2(G, c), br[c], dir[c]);
-  } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
+  } else if (__builtin_amdgcn_readfirstlane(S.pcur)) {  // the solve ends within these two iterations: x only, on the own row
     const double p = P.own[0], tp = P.own[1], u = P.own[3];
     T* x = o.x + lo.lb;
     vsto(x, xo, T((double)gldo((const T*)x, xo) + (coef[0] * p + coef[1] * tp + coef[3] * u)));
     return;
   }
-  // operator rows of the own line and of the wave's line of the one-step ring, issued
-  // before the new p and u are formed (whose basis loads they wait for) and in
-  // flight across the barrier
+  // the own line's operator row, issued before the new p and u are formed (whose basis
+  // loads they wait for); the row of the wave's line of the one-step ring follows when
+  // the basis values are used up (both at once would not fit the registers) and is in
+  // flight across the barrier and the own line's T p
   T ao[W15], ar[W15], odi, rdi;
   const S3Line l1 = s3_ring1(G, G.wave);
   const short* goff3 = uni(I.m.goff3);
-  const Steps3 off1 = steps3(goff3, s3_class(G, lo), 0), off2 = steps3(goff3, s3_class(G, lo), 1);
-  Steps3 offr = steps3(goff3, s3_class(G, l1), 1);
   const unsigned eo = (unsigned)lo.lb * W15 * TS + xo;
+  const Steps3 off2 = steps3(goff3, s3_class(G, lo), 1);
   op_row<W15>(o, eo, ao);
   odi = init ? dio : gldo(o.dinv + lo.lb, xo);
-  op_row<W15>(o, (unsigned)l1.lb * W15 * TS + xo, ar);
-  rdi = gldo(o.dinv + l1.lb, xo);
-  const T dg = op_at(o, eo, off1[15]);
-  const T xv = init ? T(0) : gldo((const T*)o.x + lo.lb, xo);
   // new p on the two-step frame, new u on the one-step frame
   auto pu = [&](const T* b, T& pn, T& un) {
     pn = T(coef[5] * b[0] + coef[6] * b[1] + coef[7] * b[2] + coef[8] * b[3] + coef[9] * b[4]);
     un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
   };
   T pn, un;
-  if (init) pn = un = dio * bo;
-  else pu(P.own, pn, un);
+  double dx = 0.0;  // increment of x
+  if (init) {
+    pn = un = dio * bo;
+  } else {
+    pu(P.own, pn, un);
+    dx = coef[0] * (double)P.own[0] + coef[1] * (double)P.own[1] + coef[3] * (double)P.own[3];
+  }
   const int o2 = s3_p2(G, lo), o1 = s3_p1(G, lo);
   s3_put(G, sp, o2, pn);
   s3_put(G, su, o1, un);
@@ -1818,8 +1938,15 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
     s3_put(G, sp, s3_p2(G, l), pr);
     if (l.yl >= -1 && l.yl <= 4 && l.zl >= -1 && l.zl <= 4) s3_put(G, su, s3_p1(G, l), ur);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  Steps3 offr = steps3(goff3, s3_class(G, l1), 1);
+  op_row<W15>(o, (unsigned)l1.lb * W15 * TS + xo, ar);
+  rdi = gldo(o.dinv + l1.lb, xo);
+  const T dg = op_at(o, eo, off2[15]);
+  const T xv = init ? T(0) : gldo((const T*)o.x + lo.lb, xo);
   lds_barrier();
   PFC_SS_STAMP(0);
+  const Steps3 off1 = steps3(goff3, s3_class(G, lo), 0);  // (used after the next barrier)
   // T p on the one-step frame
   auto tp_of = [&](const T* a, T di, int p2, const Steps3& off) {
     T acc = T(0);
@@ -1865,8 +1992,7 @@ __device__ __forceinline__ void ph_scg3(const InstDev& I, const State& S, const 
       vsto(Zj + nn, xd, x1i);
     }
   } else {
-    const double p = P.own[0], tp = P.own[1], u = P.own[3];
-    vsto(o.x + lo.lb, xo, T((double)xv + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+    vsto(o.x + lo.lb, xo, T((double)xv + dx));
   }
   vsto(bout + lo.lb, xo, pn);
   vsto(bout + nn + lo.lb, xo, tpo);
@@ -2043,18 +2169,23 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
       // halos) and is stored by the next launch (b2_end_store)
       const T* xp = pcg_ops<T>(I, S.fkind).x;
       const double c0 = coef[0], c1 = coef[1], c3 = coef[3];
-      auto fin = [&](T xo, double p, double tp, double u) { return T((double)xo + (c0 * p + c1 * tp + c3 * u)); };
-      x1f = fin(gldo(xp, og), P.own[0], P.own[1], P.own[3]);
+      // (the basis loads issued ahead are not used here: held for this path they would
+      // be live through every other phase's code)
+      const T* bold = uni((const T*)I.sbas + (long long)par * 5 * nn);
+      const T *b1 = uni(bold + nn), *b3 = uni(bold + 3 * nn);
+      auto fin = [&](unsigned q) {
+        const double p = gldo(bold, q), tp = gldo(b1, q), u = gldo(b3, q);
+        return T((double)gldo(xp, q) + (c0 * p + c1 * tp + c3 * u));
+      };
+      x1f = fin(og);
       sv[o3] = x1f;
       if (w2) {
-        const T xr = fin(gldo(xp, (unsigned)rg * TS), P.ring[0], P.ring[1], P.ring[3]);
+        const T xr = fin((unsigned)rg * TS);
         if (in2) sv[(rx + 3) + PFC_B2_W3 * (ry + 3)] = xr;
       } else if (tid >= PFC_B2_T1 && tid < PFC_B2_T3) {
         int qx, qy;
         b2_ring<3, 1>(min(tid - PFC_B2_T1, PFC_B2_R3 - 1), qx, qy);
-        const unsigned q = (unsigned)b2_row(G, qx, qy) * TS;
-        const T* bold = uni((const T*)I.sbas + (long long)par * 5 * nn);
-        const T xr = fin(gldo(xp, q), gldo(bold, q), gldo(uni(bold + nn), q), gldo(uni(bold + 3 * nn), q));
+        const T xr = fin((unsigned)b2_row(G, qx, qy) * TS);
         if (tid < PFC_B2_T1 + PFC_B2_R3) sv[(qx + 3) + PFC_B2_W3 * (qy + 3)] = xr;
       }
       lds_barrier();
@@ -2081,7 +2212,7 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
     };
     rhs(gi, oe, co, o3, bo, dio);
     if (w2) rhs(rg, rge, cr, (rx + 3) + PFC_B2_W3 * (ry + 3), br, dir);
-  } else if (S.pcur) {  // the solve ends within these two iterations: x only, on the own row
+  } else if (__builtin_amdgcn_readfirstlane(S.pcur)) {  // the solve ends within these two iterations: x only, on the own row
     const double p = P.own[0], tp = P.own[1], u = P.own[3];
     vsto(o.x, og, T((double)gldo(o.x, og) + (coef[0] * p + coef[1] * tp + coef[3] * u)));
     return;
@@ -2091,9 +2222,6 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
   T ao[W7], ar[W7], odi, rdi = T(0);
   op_row<W7>(o, oe, ao);
   odi = init ? dio : gldo(o.dinv, og);
-  const Steps2 off1 = steps2(I.m, co, 0);
-  const T dg = op_at(o, oe, off1[7]);
-  const T xo = init ? T(0) : gldo(o.x, og);
   if (w1) {
     op_row<W7>(o, rge, ar);
     rdi = gldo(o.dinv, (unsigned)rg * TS);
@@ -2104,8 +2232,13 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
     un = T(coef[10] * b[0] + coef[11] * b[1] + coef[12] * b[2] + coef[13] * b[3] + coef[14] * b[4]);
   };
   T pn, un;
-  if (init) pn = un = dio * bo;
-  else pu(P.own, pn, un);
+  double dx = 0.0;  // increment of x
+  if (init) {
+    pn = un = dio * bo;
+  } else {
+    pu(P.own, pn, un);
+    dx = coef[0] * (double)P.own[0] + coef[1] * (double)P.own[1] + coef[3] * (double)P.own[3];
+  }
   sp[o2] = pn;
   su[o1] = un;
   if (w2) {
@@ -2117,6 +2250,9 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
       if (rx >= -1 && rx < 65 && ry >= -1 && ry < 17) su[r1] = ur;
     }
   }
+  const Steps2 off1 = steps2(I.m, co, 0);
+  const T dg = op_at(o, oe, off1[7]);
+  const T xo = init ? T(0) : gldo(o.x, og);
   lds_barrier();
   PFC_SS_STAMP(0);
   // T p on the one-step frame
@@ -2164,8 +2300,7 @@ __device__ __forceinline__ void ph_scg2b(const InstDev& I, const State& S, const
       vsto(uni(Zj + nn), od, x1i);
     }
   } else {
-    const double p = P.own[0], tp = P.own[1], u = P.own[3];
-    vsto(o.x, og, T((double)xo + (coef[0] * p + coef[1] * tp + coef[3] * u)));
+    vsto(o.x, og, T((double)xo + dx));
   }
   vsto(bout, og, pn);
   vsto(uni(bout + nn), og, tpo);
@@ -2221,9 +2356,7 @@ __device__ __forceinline__ void ph_aspmv(const InstDev& I, const State& S, const
   PFC_SLICES(I, tm) {
     const int i = sl * 64 + tm.lane;
     double w0, w1, w2;
-    block_row<L, MOB>(I, pv, sl, tm.lane, I.tau_s, I.m11_s,
-              [&](int j, double& mu, double& ps, double& om) { mu = Zj[j]; ps = Zj[n + j]; om = (double)x2[j]; },
-              w0, w1, w2);
+    block_row<L, MOB, T>(I, pv, sl, tm.lane, I.tau_s, I.m11_s, {Zj, x2}, w0, w1, w2);
     if (i < n) {
       vst(I.W + i, w0); vst(I.W + n + i, w1); vst(I.W + 2 * n + i, w2);
       vst(Zj + 2 * n + i, (double)x2[i]);

@@ -127,14 +127,14 @@ __global__ void k_mass_moments(InstDev I, const double* __restrict__ psi) {
 }
 
 __global__ void k_apply_AR(InstDev I, const double* __restrict__ y, double* __restrict__ out) {
-  const int sl = blockIdx.x * PFC_WAVES + (threadIdx.x >> 6);
+  const int sl = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PFC_WAVES + (threadIdx.x >> 6)));
   if (sl >= I.m.n_slices) return;
   const int lane = threadIdx.x & 63;
   const int i = sl * 64 + lane;
   const int n = I.n;
   double w0, w1, w2;
   const PatView<PFC_COL_MEM> pv{I.m.slice_ptr, I.m.col, I.m.uw, 0, I.n, 0, 0.0f, nullptr};
-  auto yv = [&](int j, double& mu, double& ps, double& om) { mu = y[j]; ps = y[n + j]; om = y[2 * n + j]; };
+  const BlockVec<double> yv{y, y + 2LL * n};
   if (I.model == PFC_MODEL_PFC1) block_row<PFC_COL_MEM, true>(I, pv, sl, lane, I.tau, I.m11, yv, w0, w1, w2);
   else block_row<PFC_COL_MEM, false>(I, pv, sl, lane, I.tau, I.m11, yv, w0, w1, w2);
   if (i < n) { out[i] = w0; out[n + i] = w1; out[2 * n + i] = w2; }

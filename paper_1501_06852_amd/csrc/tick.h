@@ -442,7 +442,7 @@ template <typename T, int COLS, int PH>
 __device__ __forceinline__ Red3 pcg_phase(const InstDev& I, const State& S, const Team& tm, bool sd) {
   constexpr bool uses_pattern = (PH != PH_PCG_SETUP && PH != PH_PCG_B);  // the operator's own SpMV
   if constexpr (!std::is_same<T, double>::value) {
-    if (is_ci(S.kind)) return pcg_phase_one<double, COLS, PH>(I, S, tm);
+    if (is_ci(__builtin_amdgcn_readfirstlane(S.kind))) return pcg_phase_one<double, COLS, PH>(I, S, tm);
   }
   if constexpr (COLS != PFC_COL_MEM && uses_pattern) {
     if (sd) return pcg_phase_one<T, PFC_COL_MEM, PH>(I, S, tm);
@@ -578,10 +578,10 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   unsigned long long t_red = 0;
 #endif
   if constexpr (!SINGLE) {
-    ph_in = S0.phase;
-    kind_in = S0.kind;
-    pcur_in = S0.pcur;
-    if constexpr (SB2) fuse_in = S0.fuse;
+    ph_in = __builtin_amdgcn_readfirstlane(S0.phase);
+    kind_in = __builtin_amdgcn_readfirstlane(S0.kind);
+    pcur_in = __builtin_amdgcn_readfirstlane(S0.pcur);
+    if constexpr (SB2) fuse_in = __builtin_amdgcn_readfirstlane(S0.fuse);
     if constexpr (LATE) {
       if (phase_partials(ph_in)) {
         sum_partials();
@@ -606,31 +606,38 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     // launches after a two-iteration launch, or after the set-up that formed the first basis,
     // of an instance whose two-iteration form is this launch's (a launch that serves many
     // instances may hold instances of either form: the others run one iteration per launch)
-    form = SB2 ? I.sstep == 3 : (SS ? I.sstep == 1 : I.sstep == 2);
+    form = __builtin_amdgcn_readfirstlane(I.sstep) == (SB2 ? 3 : (SS ? 1 : 2));
     scg = form && (ph_in == PH_SCG_ITER || (ph_in == PH_PCG_SETUP && scg_kind(kind_in)));
-    if (scg && !(ph_in == PH_SCG_ITER && pcur_in)) {
-      // the previous launch's Gram partials: loaded in the prologue where the
-      // launch serves one instance, else here from the instance's buffer
-      const double* gin = SINGLE ? gram_in_arg : I.spart + (long long)parity * te.size * 32;
-      if constexpr (!SINGLE) ss_gram_prefetch(gin, gin, te.size, gpl);
-      // in flight during the reduction and the transition
-      if constexpr (SB2) b2_load<T>(I, te.rank, b2p, parity);
-      else if constexpr (SS) ss_load(I, S, ss_rows(I, te.rank, te.size), ssp, parity);
-      else s3_load<float>(I, S, te.rank, s3p, parity);
-      ss_gram(gin, te.size, gpl, ss_g);
-#ifdef PFC_TICK_TIMING
-      if (tid == 0) pfc_sst[4] = wall_clock64();
-#endif
-    }
   }
-  if (tid == 0) {
-    if (scg) {
-      if constexpr (SSX) scg_transition(S, I, writer, ss_g, ss_coef);
-      if constexpr (SB2) b2_fuse_end(S, I, writer, ss_coef);
+  // (one branch from the loads to the end of the transition: values loaded here would
+  // otherwise have to survive the call of the general transition)
+  if (SSX && __builtin_expect(scg, 1)) {
+    if constexpr (SSX) {
+      if (!(ph_in == PH_SCG_ITER && pcur_in)) {
+        // the previous launch's Gram partials: loaded in the prologue where the
+        // launch serves one instance, else here from the instance's buffer
+        const double* gin = SINGLE ? gram_in_arg : I.spart + (long long)parity * te.size * 32;
+        if constexpr (!SINGLE) ss_gram_prefetch(gin, gin, te.size, gpl);
+        // in flight during the reduction and the transition
+        if constexpr (SB2) b2_load<T>(I, te.rank, b2p, parity);
+        else if constexpr (SS) ss_load(I, S, ss_rows(I, te.rank, te.size), ssp, parity);
+        else s3_load<float>(I, S, te.rank, s3p, parity);
+        ss_gram(gin, te.size, gpl, ss_g);
 #ifdef PFC_TICK_TIMING
-      if constexpr (SSX) pfc_sst[5] = wall_clock64();
+        if (tid == 0) pfc_sst[4] = wall_clock64();
 #endif
-    } else {
+      }
+      if (tid == 0) {
+        scg_transition(S, I, writer, ss_g, ss_coef);
+        if constexpr (SB2) b2_fuse_end(S, I, writer, ss_coef);
+#ifdef PFC_TICK_TIMING
+        pfc_sst[5] = wall_clock64();
+#endif
+      }
+      lds_barrier();  // the basis loads stay in flight
+    }
+  } else {
+    if (tid == 0) {
       S.fuse = 0;
       Red3 red = red3(0.0, 0.0, 0.0);
       if (phase_partials(S.phase)) {
@@ -641,11 +648,6 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
       else if (!cg_iter_continues(S, I, red)) transition(S, I, writer, red, ybuf, gcol, SS && I.sstep);
       if (S.phase == PH_SOLVE_INIT || S.phase == PH_RB_RHS) S.t0 = (long long)wall_clock64();  // a solve starts
     }
-  }
-  if constexpr (SSX) {
-    if (scg) lds_barrier();  // the basis loads issued in the prologue stay in flight
-    else __syncthreads();
-  } else {
     __syncthreads();
   }
   PFC_STAMP(t_trans);
@@ -659,12 +661,16 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
       b2_end_store<T>(I, te.rank, Se.fkind, Se.xc0, Se.xc1, Se.xc3, parity);
     }
   }
-  const bool sd = (S.kind == KIND_SD);  // second-ring pattern, never staged
+  // (scalars: the compiler then branches by phase instead of running through the
+  // phases under masks, with what a later phase needs held in registers)
+  const int phase = __builtin_amdgcn_readfirstlane(S.phase), kind = __builtin_amdgcn_readfirstlane(S.kind);
+  const bool sd = (kind == KIND_SD);  // second-ring pattern, never staged
+  const bool mob = __builtin_amdgcn_readfirstlane(I.model) == PFC_MODEL_PFC1;
   Red3 acc = red3(0.0, 0.0, 0.0);
   bool fused = false;  // a set-up launch that formed a two-iteration solve's first basis (Gram partials only)
   bool scg_done = false;
   if constexpr (SSX) {
-    if (__builtin_expect(S.phase == PH_SCG_ITER, 1)) {  // the common launch, laid out first
+    if (__builtin_expect(phase == PH_SCG_ITER, 1)) {  // the common launch, laid out first
       double* gout = I.spart + (long long)(1 - parity) * te.size * 32;
       if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, false, gout, b2p, parity);
       else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, false, gout, ss_rows(I, te.rank, te.size), ssp, parity);
@@ -672,7 +678,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
       scg_done = true;
     }
   }
-  if (!scg_done) switch (S.phase) {
+  if (!scg_done) switch (phase) {
     case PH_SOLVE_INIT:
     case PH_RB_RHS: acc = ph_solve_init<COLS>(I, S, tm); break;
     case PH_RB_BEGIN: acc = ph_rb_begin<COLS>(I, tm); break;
@@ -680,7 +686,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     // the mass solves of the consistent initial values run in float64 in every precision
     case PH_PCG_SETUP:
       if constexpr (SSX) {
-        if (form && scg_kind(S.kind)) {  // set-up and first basis of a two-iteration solve
+        if (form && scg_kind(kind)) {  // set-up and first basis of a two-iteration solve
           fused = true;
           double* gout = I.spart + (long long)(1 - parity) * te.size * 32;
           if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, true, gout, b2p, parity);
@@ -695,13 +701,13 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     case PH_PCG_B: acc = pcg_phase<T, COLS, PH_PCG_B>(I, S, tm, sd); break;
     case PH_ASPMV: {
       double* gout = I.gpart + (long long)(1 - parity) * te.size * PFC_GS_NV;
-      if (I.model == PFC_MODEL_PFC1) ph_aspmv<T, COLS, true>(I, S, tm, gout);
+      if (mob) ph_aspmv<T, COLS, true>(I, S, tm, gout);
       else ph_aspmv<T, COLS, false>(I, S, tm, gout);
     } break;
     case PH_GS_UPDATE: acc = ph_gs_update(I, S, tm, hbuf); break;
     case PH_UPDATE_X: acc = ph_update_x(I, S, tm, ybuf); break;
     case PH_TRUE_RES:
-      acc = I.model == PFC_MODEL_PFC1 ? ph_true_res<COLS, true>(I, S, tm) : ph_true_res<COLS, false>(I, S, tm);
+      acc = mob ? ph_true_res<COLS, true>(I, S, tm) : ph_true_res<COLS, false>(I, S, tm);
       break;
     case PH_PCH_OUT: acc = ph_pch_out<T>(I, tm); break;
     case PH_CG_INIT: acc = pcg_phase<T, COLS, PH_CG_INIT>(I, S, tm, sd); break;
@@ -709,7 +715,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     default: break;  // PH_SCG_ITER above
   }
   PFC_STAMP(t_work);
-  if (phase_partials(S.phase) && !fused) {
+  if (phase_partials(phase) && !fused) {
     acc.a = wave_sum(acc.a);
     acc.b = wave_sum(acc.b);
     acc.c = wave_sum(acc.c);
