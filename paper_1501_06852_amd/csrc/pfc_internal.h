@@ -21,6 +21,7 @@
 #define PFC_SLICE 64
 #define PFC_MAXM 32
 #define PFC_NSTEPS_P 5
+#define PFC_SPREAD 2048  // slices of the meshes that launches serving one instance spread over more workgroups
 // rows of at most this many entries have byte-wide positions in the visit lists
 // and are staged whole in LDS by the mesh-level element sums
 #define PFC_ROW_MAX 96
@@ -182,6 +183,7 @@ struct InstDev {
   int inner_fixed[5], pad_if;   // fixed inner iteration counts (0: to inner_tol)
   int sstep, sH;                // two PCG iterations per launch: 0 no, 1 row ranges of a 2D grid (halo sH = N + 1
                                 // rows), 2 blocks of a 3D grid of side 64, 3 blocks of a 2D grid (side 64 k)
+  int solo_wgs, pad_sw;         // workgroups of launches that serve the instance alone
   double outer_tol, inner_tol, ci_tol;
   // job parameters; tau_p = m0 tau_s is the preconditioner's time step
   // rs: factor of block row 1 in the system FGMRES works on (1/m11 for
@@ -211,11 +213,12 @@ struct InstDev {
   void *r_, *pA, *pB, *q, *y0, *y1, *zt, *x1, *x2;
   void *rB, *wB, *sA, *sB;      // extra buffers of the single-reduction PCG
   double* part;                 // [2][team_size][4] partial sums
-  double* gpart;                // [2][team_size][64] Gram partial sums of the orthogonalisation
+  double* gpart;                // [2][team_size][64] Gram partial sums of the orthogonalisation, or the per-slice
+                                // sums (4 a slice) of launches on more workgroups than the team's
   // s-step double buffers, indexed by the launch's parity: a launch reads the
   // previous launch's basis and Gram partials from [parity], writes to [1 - parity]
   double* sbas;                 // s-step basis [2][5][n] (p, Tp, T^2 p, u, Tu), or null
-  double* spart;                // s-step Gram partial sums [2][team_size][32], or null
+  double* spart;                // s-step Gram partial sums [2][workgroups][32], or null
   State* st;                    // [2]
   Hist* hist;
   const int* sched_meta;        // replay: per solve {cycle offset, cycles, apply offset, applies}

@@ -182,7 +182,8 @@ int rebuild(pfc_server* S) {
   S->grp.release();
   if (S->active.empty()) return PFC_OK;
   std::vector<int> ts;
-  for (Request* q : S->active) ts.push_back(q->inst->team_size);
+  // (a request that may be joined by others keeps its team: it continues in their launches)
+  for (Request* q : S->active) ts.push_back(S->o.max_slots == 1 ? q->inst->solo_wgs : q->inst->team_size);
   int rc = S->grp.alloc(ts);
   if (rc) return rc;
   for (size_t i = 0; i < S->active.size(); ++i) S->grp.h_descs[i] = S->active[i]->inst->h;

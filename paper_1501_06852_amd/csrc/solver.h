@@ -21,7 +21,7 @@ struct TickLaunch {
   const double* gram_in;
   int parity;
   const int* col;
-  int uw, n_slices;
+  int uw, n_slices, team;  // ... and its team size
   int n_wg, cols;       // workgroups; where the columns come from (PFC_COL_*)
   bool single, b2;      // serves one instance; has the 2D block form
 };
@@ -48,6 +48,8 @@ struct Group {
 };
 
 size_t carve(InstDev& h, char* base, const pfc_mesh* m, const pfc_opts& o, int team_size);
+// workgroups of the launches that serve the instance alone
+int solo_workgroups(const pfc_mesh* m, const pfc_opts& o, int team_size);
 int team_size_for(int n_slices, int rows_per_thread);
 // whether an instance with these options on this mesh takes the 2D block form of
 // two PCG iterations per launch (with pcg_steps_per_launch = 2)
@@ -68,6 +70,7 @@ struct pfc_instance {
   pfc_mesh* mesh = nullptr;
   pfc_opts opts{};
   int team_size = 0;
+  int solo_wgs = 0;              // workgroups of launches that serve it alone
   int ticks = 64;
   size_t bytes = 0;
   char* arena = nullptr;

@@ -276,6 +276,25 @@ bool block_form_applies(const pfc_mesh* m, const pfc_opts& o) {
   return sstep_block2(m, o2, team_size_for(m->n_slices, o.rows_per_thread));
 }
 
+// Workgroups of launches that serve the instance alone: its team, or, on meshes of
+// at most PFC_SPREAD slices, as few slices a workgroup as the chip's 256 CUs allow.
+// Measured with 16 (the team), 4 and 1 slices at most a workgroup: P_CH apply 3D 20^3
+// float64 1684, 1141, 1044 us; 2D 50^2 mixed 954, 851, 818; stage solve 2D P2 50^2
+// 48.1, 30.6, 26.8 ms; 2D 100^2 (ranges of grid lines) 7.6, 7.0, 6.8; PFC1 step 100^2
+// 37.9, 34.6, 33.8.  Not for several rows per thread (a wave's sums have to be one
+// slice's), the block forms (their workgroups are blocks) and launches that stage
+// columns (those of the team's slices).
+int solo_workgroups(const pfc_mesh* m, const pfc_opts& o, int team_size) {
+  const MeshDev& d = m->dev;
+  const bool grid = d.gN > 0 && o.grid_columns;
+  const bool staged = !grid && d.uw >= 1 && d.uw <= PFC_LCOL_W && !(o.precision == PFC_FP64 && d.uw < 8);
+  if (o.rows_per_thread > 1 || d.n_slices > PFC_SPREAD || staged || sstep_block2(m, o, team_size) ||
+      sstep_block3(m, o, team_size))
+    return team_size;
+  const int spw = (d.n_slices + 255) / 256;
+  return (d.n_slices + spw - 1) / spw;
+}
+
 // Carve the instance arena.  With base == nullptr only the size is computed.
 size_t carve(InstDev& h, char* base, const pfc_mesh* m, const pfc_opts& o, int team_size) {
   size_t off = 0;
@@ -317,12 +336,17 @@ size_t carve(InstDev& h, char* base, const pfc_mesh* m, const pfc_opts& o, int t
   h.rB = take(n * 8); h.wB = take(n * 8); h.sA = take(n * 8); h.sB = take(n * 8);
   h.xbak = (double*)take(n3 * 8);
   h.errpart = (double*)take((size_t)m->n_slices * 2 * 8);
+  h.solo_wgs = solo_workgroups(m, o, team_size);
   h.part = (double*)take(2 * (size_t)team_size * 4 * sizeof(double));
   h.gpart = (double*)take(2 * (size_t)team_size * PFC_GS_NV * sizeof(double));
   h.sH = sstep_halo(m, o, team_size);
   h.sstep = sstep_block2(m, o, team_size) ? 3 : (h.sH > 0 ? 1 : (sstep_block3(m, o, team_size) ? 2 : 0));
   h.sbas = h.sstep ? (double*)take(10 * n * 8) : nullptr;
-  h.spart = h.sstep ? (double*)take(2 * (size_t)team_size * 32 * sizeof(double)) : nullptr;
+  // (of launches on more workgroups than the team's, at most one a slice: in sA and sB,
+  // 16 n bytes that only the one-iteration form uses, in solves of its own)
+  h.spart = !h.sstep ? nullptr
+            : h.solo_wgs != team_size ? (double*)h.sA
+                                      : (double*)take(2 * (size_t)team_size * 32 * sizeof(double));
   h.st = (State*)take(2 * sizeof(State));
   h.hist = (Hist*)take(sizeof(Hist));
   h.rec_inner = (int*)take((size_t)o.max_steps * 5 * sizeof(int));
@@ -389,7 +413,7 @@ int Group::build(hipStream_t capture, int precision, int ticks) {
       set_error("internal: launch group built before its descriptors were set");
       return PFC_ERR_STATE;
     }
-  if (count == 1 && h_descs[0].team_size != n_wg) {
+  if (count == 1 && h_descs[0].team_size != n_wg && h_descs[0].solo_wgs != n_wg) {
     set_error("internal: team size mismatch");
     return PFC_ERR_STATE;
   }
@@ -433,17 +457,24 @@ int Group::build(hipStream_t capture, int precision, int ticks) {
     double* pout = nullptr;
     const double* gin = nullptr;
     if (count == 1) {
+      // launches on more workgroups than the team's leave a sum per slice, in the buffer of
+      // the orthogonalisation's sums: 64 numbers a workgroup of the team are 4 for each of
+      // its 16 slices, and no launch leaves both kinds
+      const bool spread = n_wg != h_descs[0].team_size;
+      double* part = spread ? h_descs[0].gpart : h_descs[0].part;
+      const size_t np = spread ? (size_t)h_descs[0].team_size * (PFC_GS_NV / 4) : n_wg;
       sin = h_descs[0].st + par;
       sout = h_descs[0].st + (1 - par);
-      pin = h_descs[0].part + (size_t)par * n_wg * 4;
-      pout = h_descs[0].part + (size_t)(1 - par) * n_wg * 4;
+      pin = part + (size_t)par * np * 4;
+      pout = part + (size_t)(1 - par) * np * 4;
       if (h_descs[0].spart) gin = h_descs[0].spart + (size_t)par * n_wg * 32;
     }
     // the launches have the 2D block form (ph_scg2b) when some instance takes it;
     // the other instances run one PCG iteration per launch in them
     bool b2 = false;
     for (int i = 0; i < count; ++i) b2 = b2 || h_descs[i].sstep == 3;
-    const TickLaunch q{d_teams, d_descs, sin, sout, pin, pout, gin, par, pcol, puw, pnsl, n_wg, cols, count == 1, b2};
+    const int team = count == 1 ? h_descs[0].team_size : 0;
+    const TickLaunch q{d_teams, d_descs, sin, sout, pin, pout, gin, par, pcol, puw, pnsl, team, n_wg, cols, count == 1, b2};
     if (precision == PFC_MIXED) launch_tick_f32(q, capture);
     else launch_tick_f64(q, capture);
   }
@@ -522,7 +553,7 @@ int Group::run(hipStream_t s, const std::vector<State*>& dev_states, double time
 
 static int ensure_group(pfc_instance* I) {
   if (I->grp.exec) return PFC_OK;
-  int rc = I->grp.alloc(std::vector<int>{I->team_size});
+  int rc = I->grp.alloc(std::vector<int>{I->solo_wgs});
   if (rc) return rc;
   I->grp.h_descs[0] = I->h;
   return I->grp.build(I->capture, I->opts.precision, I->ticks);
@@ -790,6 +821,7 @@ int pfc_instance_create(pfc_mesh* m, const pfc_opts* o, pfc_instance** out) {
   for (int k = 0; k < 5; ++k) h.inner_fixed[k] = o->inner_fixed[k];
   h.m0 = 1.0;
   h.team_size = I->team_size;
+  I->solo_wgs = h.solo_wgs;
   h.outer_tol = o->outer_tol;
   h.inner_tol = o->inner_tol;
   h.ci_tol = 1e-13;
@@ -1171,7 +1203,7 @@ int pfc_batch_run(pfc_instance* const* insts, int count, double* const* states, 
     if (rcm) return rcm;
     set_params(h, r[i], tau[i], 1.0 / ROS_GAMMA);
     h.replay = 0;
-    ts[i] = insts[i]->team_size;
+    ts[i] = count == 1 ? insts[i]->solo_wgs : insts[i]->team_size;
     sts[i] = h.st;
     int rc = prep_ops(insts[i], s);
     if (rc) return rc;

@@ -459,11 +459,21 @@ __device__ __forceinline__ Red3 pcg_phase(const InstDev& I, const State& S, cons
 // (uniform slice width, at most PFC_WAVES slices per workgroup); PFC_COL_GRID
 // computes them from the row (periodic grid meshes).  The host picks the
 // variant that the launch's meshes allow.
-template <typename T, bool SINGLE, int COLS, bool B2>
+// SPREAD: a launch that serves one instance and deals its slices to more workgroups
+// (wgs) than the instance's team has, fewer to each: a team of 16 slices a
+// workgroup leaves most of the chip idle on a small mesh, and the gathers of its 16
+// waves queue up in one CU (3D 40^3 float64, 63 workgroups: 15.1 us a launch, the first
+// wave's work 4.8).  Phases that leave partial sums then leave one per slice, and the
+// next launch adds them up in the team's order (the slices of each of its workgroups,
+// then the workgroups): the same bits as the team's own launches.  The sums of the
+// orthogonalisation stay the team's.  Measured, P_CH apply 3D 40^3 float64: 1645 ->
+// 1271 us; a variant of its own, for in the others the choice at run time cost 2.5%
+// (2D 512^2 float64) and 4% (3D 64^3 mixed).
+template <typename T, bool SINGLE, int COLS, bool B2, bool SPREAD>
 __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ teams, const InstDev* __restrict__ insts,
                                                  const State* st_in_arg, State* st_out_arg, const double* part_in_arg,
                                                  double* part_out_arg, int parity, const int* __restrict__ col_arg,
-                                                 int uw_arg, int nsl_arg, const double* gram_in_arg) {
+                                                 int uw_arg, int nsl_arg, const double* gram_in_arg, int team_arg) {
   __shared__ State S;
   __shared__ State S0;  // entry state of launches that serve many instances (path choice)
   __shared__ InstDev sI;
@@ -479,7 +489,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   // blocks of 3D grids of side 64 in float
   constexpr bool SB2 = B2 && COLS == PFC_COL_GRID;
   constexpr bool SS = SINGLE && COLS == PFC_COL_GRID && std::is_same<T, double>::value && !B2;
-  constexpr bool SS3 = SINGLE && COLS == PFC_COL_GRID && std::is_same<T, float>::value && !B2;
+  constexpr bool SS3 = SINGLE && COLS == PFC_COL_GRID && std::is_same<T, float>::value && !B2 && !SPREAD;
   constexpr bool SSX = SS || SS3 || SB2;
   __shared__ double ss_g[SSX ? 32 : 1];
   __shared__ double ss_coef[SSX ? 16 : 1];
@@ -492,7 +502,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   const double* part_in;
   double* part_out;
   if (SINGLE) {
-    te.inst = 0; te.rank = xcd_rank(blockIdx.x, gridDim.x); te.size = gridDim.x;
+    te.inst = 0; te.rank = xcd_rank(blockIdx.x, gridDim.x); te.size = SPREAD ? team_arg : (int)gridDim.x;
     te.uw = uw_arg; te.col = col_arg; te.n_slices = nsl_arg; te.pad = 0;
     gI = insts;
     st_in = st_in_arg; st_out = st_out_arg; part_in = part_in_arg; part_out = part_out_arg;
@@ -503,6 +513,9 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     part_in = gI->part + (long long)parity * te.size * 4;
     part_out = gI->part + (long long)(1 - parity) * te.size * 4;
   }
+  static_assert(!SPREAD || (SINGLE && !B2 && COLS != PFC_COL_LDS), "spread launches serve one instance, no blocks");
+  const int wgs = SPREAD ? (int)gridDim.x : te.size;
+  const int ssz = SS ? wgs : te.size;  // workgroups of the two-iteration form
   // one round trip: the state record and the instance descriptor (a word per
   // thread, every thread loading at a clamped position), the partial sums of
   // the previous launch and, in single-instance launches of two-iteration
@@ -524,7 +537,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     if constexpr (SB2) fuse_in = st_in->fuse;
   }
   double gpl[SSX ? PFC_SS_GL : 1];
-  if constexpr (SSX && SINGLE) ss_gram_prefetch(gram_in_arg, part_in, te.size, gpl);
+  if constexpr (SSX && SINGLE) ss_gram_prefetch(gram_in_arg, part_in, ssz, gpl);
   // columns of this workgroup's slices: positions [lo, lo + len) of the SELL
   // pattern, issued first and written to LDS once everything has arrived
   int lo = 0, len = 0;
@@ -542,9 +555,17 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     }
   }
   Red3 pre = red3(0.0, 0.0, 0.0), pre2 = red3(0.0, 0.0, 0.0);
-  if (tid < te.size) { pre.a = part_in[4 * tid]; pre.b = part_in[4 * tid + 1]; pre.c = part_in[4 * tid + 2]; }
-  for (int k = tid + PFC_WG; k < te.size; k += PFC_WG) {  // teams of more than PFC_WG workgroups
-    pre2.a += part_in[4 * k]; pre2.b += part_in[4 * k + 1]; pre2.c += part_in[4 * k + 2];
+  if constexpr (SPREAD) {
+    if (tid < te.n_slices) { pre.a = part_in[4 * tid]; pre.b = part_in[4 * tid + 1]; pre.c = part_in[4 * tid + 2]; }
+    if (tid + PFC_WG < te.n_slices) {
+      const double* q = part_in + 4 * (tid + PFC_WG);
+      pre2.a = q[0]; pre2.b = q[1]; pre2.c = q[2];
+    }
+  } else {
+    if (tid < te.size) { pre.a = part_in[4 * tid]; pre.b = part_in[4 * tid + 1]; pre.c = part_in[4 * tid + 2]; }
+    for (int k = tid + PFC_WG; k < te.size; k += PFC_WG) {  // teams of more than PFC_WG workgroups
+      pre2.a += part_in[4 * k]; pre2.b += part_in[4 * k + 1]; pre2.c += part_in[4 * k + 2];
+    }
   }
   if (tid < NS) {
     ((int*)&S)[tid] = word;
@@ -570,7 +591,27 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     if ((tid & 63) == 0) lds4[tid >> 6] = pre;
   };
   if constexpr (!LATE) {
-    if (!SINGLE || phase_partials(ph_in)) sum_partials();
+    if (!SINGLE || phase_partials(ph_in)) {
+      if constexpr (SPREAD) {
+        static_assert(3 * PFC_SPREAD <= PFC_SS_LDS && PFC_SPREAD == 2 * PFC_WG, "slice sums in the s-step LDS, two per thread");
+        double *sa = pfc_ss, *sb = sa + PFC_SPREAD, *sc = sb + PFC_SPREAD;  // by slice
+        sa[tid] = pre.a; sb[tid] = pre.b; sc[tid] = pre.c;
+        sa[PFC_WG + tid] = pre2.a; sb[PFC_WG + tid] = pre2.b; sc[PFC_WG + tid] = pre2.c;
+        __syncthreads();
+        pre = pre2 = red3(0.0, 0.0, 0.0);
+        if (tid < te.size) {  // workgroup tid of the team: its slices (PFC_SLICES), one per wave
+          const bool rr = te.uw == 0;
+          const int spw = (te.n_slices + te.size - 1) / te.size, first = rr ? tid : tid * spw;
+          const int step = rr ? te.size : 1, end = rr ? te.n_slices : min(first + spw, te.n_slices);
+#pragma unroll
+          for (int w = 0; w < PFC_WAVES; ++w) {
+            const int sl = first + w * step;
+            if (sl < end) { pre.a += sa[sl]; pre.b += sb[sl]; pre.c += sc[sl]; }
+          }
+        }
+      }
+      sum_partials();
+    }
   }
   __syncthreads();
 #ifdef PFC_TICK_TIMING
@@ -620,9 +661,9 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
         if constexpr (!SINGLE) ss_gram_prefetch(gin, gin, te.size, gpl);
         // in flight during the reduction and the transition
         if constexpr (SB2) b2_load<T>(I, te.rank, b2p, parity);
-        else if constexpr (SS) ss_load(I, S, ss_rows(I, te.rank, te.size), ssp, parity);
+        else if constexpr (SS) ss_load(I, S, ss_rows(I, te.rank, ssz), ssp, parity);
         else s3_load<float>(I, S, te.rank, s3p, parity);
-        ss_gram(gin, te.size, gpl, ss_g);
+        ss_gram(gin, ssz, gpl, ss_g);
 #ifdef PFC_TICK_TIMING
         if (tid == 0) pfc_sst[4] = wall_clock64();
 #endif
@@ -653,7 +694,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   PFC_STAMP(t_trans);
   // the new state is final: workgroup 0 stores it while the phase runs
   if (writer && tid < NS) ((int*)st_out)[tid] = ((const int*)&S)[tid];
-  Team tm{te.rank, te.size, tid >> 6, tid & 63, lo};
+  Team tm{te.rank, wgs, tid >> 6, tid & 63, lo};
   if constexpr (SB2) {
     // the previous launch ended a solve in its set-up: that solve's x on the own rows
     if (__builtin_expect(fuse_in != 0, 0)) {
@@ -671,9 +712,9 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   bool scg_done = false;
   if constexpr (SSX) {
     if (__builtin_expect(phase == PH_SCG_ITER, 1)) {  // the common launch, laid out first
-      double* gout = I.spart + (long long)(1 - parity) * te.size * 32;
+      double* gout = I.spart + (long long)(1 - parity) * ssz * 32;
       if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, false, gout, b2p, parity);
-      else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, false, gout, ss_rows(I, te.rank, te.size), ssp, parity);
+      else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, false, gout, ss_rows(I, te.rank, ssz), ssp, parity);
       else ph_scg3<float>(I, S, tm, ss_coef, false, gout, s3p, parity);
       scg_done = true;
     }
@@ -688,9 +729,9 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
       if constexpr (SSX) {
         if (form && scg_kind(kind)) {  // set-up and first basis of a two-iteration solve
           fused = true;
-          double* gout = I.spart + (long long)(1 - parity) * te.size * 32;
+          double* gout = I.spart + (long long)(1 - parity) * ssz * 32;
           if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, true, gout, b2p, parity);
-          else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, true, gout, ss_rows(I, te.rank, te.size), ssp, parity);
+          else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, true, gout, ss_rows(I, te.rank, ssz), ssp, parity);
           else ph_scg3<float>(I, S, tm, ss_coef, true, gout, s3p, parity);
           break;
         }
@@ -700,6 +741,10 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     case PH_PCG_A: acc = pcg_phase<T, COLS, PH_PCG_A>(I, S, tm, sd); break;
     case PH_PCG_B: acc = pcg_phase<T, COLS, PH_PCG_B>(I, S, tm, sd); break;
     case PH_ASPMV: {
+      if constexpr (SPREAD) {  // the team's sums: its workgroups, its slices
+        if (te.rank >= te.size) break;
+        tm.size = te.size;
+      }
       double* gout = I.gpart + (long long)(1 - parity) * te.size * PFC_GS_NV;
       if (mob) ph_aspmv<T, COLS, true>(I, S, tm, gout);
       else ph_aspmv<T, COLS, false>(I, S, tm, gout);
@@ -719,23 +764,32 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     acc.a = wave_sum(acc.a);
     acc.b = wave_sum(acc.b);
     acc.c = wave_sum(acc.c);
-    if ((tid & 63) == 0) lds4[tid >> 6] = acc;
-    __syncthreads();
+    if constexpr (SPREAD) {  // the slice's own sums (a wave has one slice at most)
+      const int wave = tid >> 6, spw = (te.n_slices + wgs - 1) / wgs;
+      const int sl = te.uw == 0 ? te.rank + wgs * wave : (wave < spw ? te.rank * spw + wave : te.n_slices);
+      if ((tid & 63) == 0 && sl < te.n_slices) {
+        double* dst = part_out + 4LL * sl;
+        vst(dst, acc.a); vst(dst + 1, acc.b); vst(dst + 2, acc.c);
+      }
+    } else {
+      if ((tid & 63) == 0) lds4[tid >> 6] = acc;
+      __syncthreads();
 #ifdef PFC_TICK_TIMING
-    t_red = wall_clock64();
+      t_red = wall_clock64();
 #endif
-    if (tid == 0) {
-      Red3 r = red3(0.0, 0.0, 0.0);
+      if (tid == 0) {
+        Red3 r = red3(0.0, 0.0, 0.0);
 #pragma unroll
-      for (int w = 0; w < PFC_WAVES; ++w) { r.a += lds4[w].a; r.b += lds4[w].b; r.c += lds4[w].c; }
-      double* dst = part_out + (long long)te.rank * 4;
-      dst[0] = r.a; dst[1] = r.b; dst[2] = r.c;
+        for (int w = 0; w < PFC_WAVES; ++w) { r.a += lds4[w].a; r.b += lds4[w].b; r.c += lds4[w].c; }
+        double* dst = part_out + (long long)te.rank * 4;
+        dst[0] = r.a; dst[1] = r.b; dst[2] = r.c;
+      }
     }
   }
 #ifdef PFC_TICK_TIMING
   __syncthreads();
   PFC_STAMP(t_exit);
-  if (tid == 0 && (te.rank == 0 || te.rank == te.size - 1) && g_trace) {
+  if (tid == 0 && (te.rank == 0 || te.rank == wgs - 1) && g_trace) {
     const unsigned long long k = atomicAdd(&g_trace_n, 1ULL);
     if (k < g_trace_cap) {
       unsigned long long* r = g_trace + 14 * k;
@@ -751,19 +805,22 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
 // Enqueues one launch on `stream`: the instantiation that the launch allows.
 template <typename T>
 static void launch_tick_T(const TickLaunch& q, hipStream_t stream) {
-#define PFC_TICK(SG, LD, BB)                                                                                           \
-  hipLaunchKernelGGL((k_tick<T, SG, LD, BB>), dim3(q.n_wg), dim3(PFC_WG), 0, stream, q.teams, q.insts, q.st_in, q.st_out, \
-                     q.part_in, q.part_out, q.parity, q.col, q.uw, q.n_slices, q.gram_in)
+#define PFC_TICK(SG, LD, BB, SP)                                                                                       \
+  hipLaunchKernelGGL((k_tick<T, SG, LD, BB, SP>), dim3(q.n_wg), dim3(PFC_WG), 0, stream, q.teams, q.insts, q.st_in,     \
+                     q.st_out, q.part_in, q.part_out, q.parity, q.col, q.uw, q.n_slices, q.gram_in, q.team)
 #define PFC_TICK_COLS(SG)                                                      \
   switch (q.cols) {                                                            \
     case PFC_COL_GRID:                                                         \
-      if (q.b2) { PFC_TICK(SG, PFC_COL_GRID, true); }                          \
-      else { PFC_TICK(SG, PFC_COL_GRID, false); }                              \
+      if (q.b2) { PFC_TICK(SG, PFC_COL_GRID, true, false); }                   \
+      else { PFC_TICK(SG, PFC_COL_GRID, false, false); }                       \
       break;                                                                   \
-    case PFC_COL_LDS: PFC_TICK(SG, PFC_COL_LDS, false); break;                 \
-    default: PFC_TICK(SG, PFC_COL_MEM, false); break;                          \
+    case PFC_COL_LDS: PFC_TICK(SG, PFC_COL_LDS, false, false); break;          \
+    default: PFC_TICK(SG, PFC_COL_MEM, false, false); break;                   \
   }
-  if (q.single) { PFC_TICK_COLS(true); } else { PFC_TICK_COLS(false); }
+  if (q.single && q.n_wg != q.team) {
+    if (q.cols == PFC_COL_GRID) { PFC_TICK(true, PFC_COL_GRID, false, true); }
+    else { PFC_TICK(true, PFC_COL_MEM, false, true); }
+  } else if (q.single) { PFC_TICK_COLS(true); } else { PFC_TICK_COLS(false); }
 #undef PFC_TICK_COLS
 #undef PFC_TICK
 }
