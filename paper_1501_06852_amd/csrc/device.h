@@ -1338,6 +1338,11 @@ __device__ __forceinline__ Red3 ph_cg_iter(const InstDev& I, const State& S, con
 // rows (mod n) on 2D periodic grids, whose neighbours lie within N + 1 rows.
 #define PFC_SS_NG 26  // 15 entries of G, 10 of H, and ||b||^2 in the first launch of a solve
 #define PFC_SS_NA 4   // passes of a workgroup over the two-step halo (R + 4H <= 4096 rows)
+// passes of launches on more workgroups than the team's (at most 512 own rows; grids of
+// side 362 at most): half the basis registers of four, and waves without rows in a
+// pass skip it.  2D 100^2 float64, one slice a workgroup: 11.9 -> 8.7 us a launch
+// (sums over the prefetched Gram partials 3.1 -> 1.4, new p and u 2.8 -> 1.5)
+#define PFC_SS_NA_SPREAD 2
 #define PFC_SS_NB 3   // passes over the one-step halo (R + 2H <= 3072 rows); 7 entries per row
 __shared__ double pfc_ssred[64 * 32];
 #ifdef PFC_TICK_TIMING
@@ -1416,33 +1421,39 @@ __device__ __forceinline__ SsRows ss_rows(const InstDev& I, int rank, int size) 
 
 // Loads of the current basis on the two-step halo (and x on the own row), issued
 // before the launch's reductions so that their latency overlaps them.
+template <int NA>
 struct SsPre {
-  double bv[PFC_SS_NA][5];
+  double bv[NA][5];
   double xo;
 };
-__device__ __forceinline__ void ss_load(const InstDev& I, const State& S, const SsRows& w, SsPre& P, int par) {
+template <int NA>
+__device__ __forceinline__ void ss_load(const InstDev& I, const State& S, const SsRows& w, SsPre<NA>& P, int par) {
   const int n = I.n;
   const long long nn = n;
   const int tid = threadIdx.x;
   const double* bin = I.sbas + (long long)par * 5 * nn;  // the basis of the previous launch
+  // (a wave skips the passes in which it has no rows)
+  const int first = __builtin_amdgcn_readfirstlane(tid & ~63);
 #pragma unroll
-  for (int c = 0; c < PFC_SS_NA; ++c) {
-    const int g = ss_wrap(w.lo - 2 * w.H + min(tid + c * PFC_WG, w.L2 - 1), n);
+  for (int c = 0; c < NA; ++c) {
+    if (NA > 2 || first + c * PFC_WG < w.L2) {
+      const int g = ss_wrap(w.lo - 2 * w.H + min(tid + c * PFC_WG, w.L2 - 1), n);
 #pragma unroll
-    for (int k = 0; k < 5; ++k) P.bv[c][k] = gld(bin + k * nn + g);
+      for (int k = 0; k < 5; ++k) P.bv[c][k] = gld(bin + k * nn + g);
+    }
   }
   P.xo = gld(pcg_ops<double>(I, S.kind).x + min(w.go, n - 1));  // used on the own row only
 }
 
 // coef: x increment [0..4], new p [5..9], new u [10..14] over B; S.pcur: x only.
 // par: the launch's parity (reads basis [par], writes basis [1 - par]).
-template <int L>
+template <int L, int NA>
 __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const Team& tm, const double* coef, bool init,
-                                       double* spart_out, const SsRows& w, SsPre& P, int par) {
+                                       double* spart_out, const SsRows& w, SsPre<NA>& P, int par) {
   const int n = I.n, H = w.H, R = w.R, L1 = w.L1, L2 = w.L2, lo = w.lo;
   PcgOps<double> o = pcg_ops<double>(I, S.kind);
   const PatView<L> pv = op_pat<L>(I, o, tm);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, first = __builtin_amdgcn_readfirstlane(tid & ~63);
   const long long nn = n;
   double* bout = I.sbas + (long long)(1 - par) * 5 * nn;
   double bbo = 0.0;  // ||b||^2 over the own rows (first launch of a solve)
@@ -1463,7 +1474,8 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
     const double ts = kind == KIND_Y0 ? S.vscale : 1.0, sa = kind == KIND_Y1 ? I.tau_p : 1.0;
     double bo = 0.0;
 #pragma unroll
-    for (int c = 0; c < PFC_SS_NA; ++c) {
+    for (int c = 0; c < NA; ++c) {
+      if (NA <= 2 && first + c * PFC_WG >= L2) break;
       const int g = ss_wrap(lo - 2 * H + min(tid + c * PFC_WG, L2 - 1), n);
       const int base = (g >> 6) * 64 * 7 + (g & 63);
       double d = 0.0;
@@ -1501,7 +1513,7 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
   if (!init && __builtin_amdgcn_readfirstlane(S.pcur)) {  // the solve ends within these two iterations: x only
     if (w.own) {
 #pragma unroll
-      for (int c = 0; c < PFC_SS_NA; ++c)
+      for (int c = 0; c < NA; ++c)
         if (tid + c * PFC_WG == w.qo)
           vst(o.x + w.go, P.xo + (coef[0] * P.bv[c][0] + coef[1] * P.bv[c][1] + coef[3] * P.bv[c][3]));
     }
@@ -1511,7 +1523,7 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
   double* su = sp + L2;    // new u on [lo - H, lo + R + H)
   double* stp = su + L1;   // T p on [lo - H, lo + R + H)
 #pragma unroll
-  for (int c = 0; c < PFC_SS_NA; ++c) {
+  for (int c = 0; c < NA; ++c) {
     const int q = tid + c * PFC_WG;
     if (q < L2) {
       const double* b = P.bv[c];
@@ -1537,13 +1549,15 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
   double av[3][7], dv[3];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    const int g = ss_wrap(lo - H + min(tid + c * PFC_WG, L1 - 1), n);
-    const int base = (g >> 6) * 64 * 7 + (g & 63);
+    if (NA > 2 || first + c * PFC_WG < L1) {
+      const int g = ss_wrap(lo - H + min(tid + c * PFC_WG, L1 - 1), n);
+      const int base = (g >> 6) * 64 * 7 + (g & 63);
 #pragma unroll
-    for (int k = 0; k < 7; ++k) av[c][k] = opval_g(o, (long long)base + k * 64);
-    dv[c] = gld(o.dinv + g);
+      for (int k = 0; k < 7; ++k) av[c][k] = opval_g(o, (long long)base + k * 64);
+      dv[c] = gld(o.dinv + g);
+    }
   }
-  if (L1 > 2 * PFC_WG && tid < 64) {
+  if (NA > 2 && L1 > 2 * PFC_WG && tid < 64) {
     const int g = ss_wrap(lo - H + min(tid + 2 * PFC_WG, L1 - 1), n);
     const int base = (g >> 6) * 64 * 7 + (g & 63);
 #pragma unroll
@@ -1556,29 +1570,31 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
   int q1o = -1;
   double tpo = 0.0, tuo = 0.0, dgo = 0.0, dvo = 0.0;
   double ao[7];
+  int so[7];  // its entries' steps
 #pragma unroll
-  for (int k = 0; k < 7; ++k) ao[k] = 0.0;
+  for (int k = 0; k < 7; ++k) { ao[k] = 0.0; so[k] = 0; }
   auto trow = [&](int q1, const double* a, double di) {
     const int g = ss_wrap(lo - H + q1, n);
     const bool own = q1 >= H && q1 < H + R;
     const int base = (g >> 6) * 64 * 7 + (g & 63);
     double acc = 0.0, acc2 = 0.0, dg = 0.0;
+    int d[7];
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
-      const int d = ss_step(pv.at((long long)base + k * 64, g) - g, n);
-      acc += a[k] * sp[q1 + H + d];
-      dg += d == 0 ? a[k] : 0.0;
+      d[k] = ss_step(pv.at((long long)base + k * 64, g) - g, n);
+      acc += a[k] * sp[q1 + H + d[k]];
+      dg += d[k] == 0 ? a[k] : 0.0;
     }
     if (own) {
 #pragma unroll
-      for (int k = 0; k < 7; ++k) acc2 += a[k] * su[q1 + ss_step(pv.at((long long)base + k * 64, g) - g, n)];
+      for (int k = 0; k < 7; ++k) acc2 += a[k] * su[q1 + d[k]];
     }
     const double tp = di * acc;
     stp[q1] = tp;
     if (own) {
       q1o = q1; tpo = tp; tuo = di * acc2; dgo = dg; dvo = di;
 #pragma unroll
-      for (int k = 0; k < 7; ++k) ao[k] = a[k];
+      for (int k = 0; k < 7; ++k) { ao[k] = a[k]; so[k] = d[k]; }
       vst(bout + nn + g, tpo);
       vst(bout + 4 * nn + g, tuo);
     }
@@ -1586,7 +1602,7 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
 #pragma unroll
   for (int c = 0; c < 2; ++c)
     if (tid + c * PFC_WG < L1) trow(tid + c * PFC_WG, av[c], dv[c]);
-  if (tid + 2 * PFC_WG < L1) {  // third pass (at most PFC_SS_NB)
+  if (NA > 2 && tid + 2 * PFC_WG < L1) {  // third pass (at most PFC_SS_NB)
     if (tid < 64) {
       trow(tid + 2 * PFC_WG, av[2], dv[2]);
     } else {
@@ -1606,10 +1622,9 @@ __device__ __forceinline__ void ph_scg(const InstDev& I, const State& S, const T
   for (int m = 0; m < PFC_SS_NG; ++m) gp[m] = 0.0;
   if (q1o >= 0) {
     const int g = lo + (q1o - H);
-    const int base = (g >> 6) * 64 * 7 + (g & 63);
     double acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < 7; ++k) acc += ao[k] * stp[q1o + ss_step(pv.at((long long)base + k * 64, g) - g, n)];
+    for (int k = 0; k < 7; ++k) acc += ao[k] * stp[q1o + so[k]];
     const double ttp = dvo * acc;
     vst(bout + 2 * nn + g, ttp);
     const double v[5] = {sp[q1o + H], tpo, ttp, su[q1o], tuo};

@@ -278,10 +278,8 @@ bool block_form_applies(const pfc_mesh* m, const pfc_opts& o) {
 
 // Workgroups of launches that serve the instance alone: its team, or, on meshes of
 // at most PFC_SPREAD slices, as few slices a workgroup as the chip's 256 CUs allow.
-// Measured with 16 (the team), 4 and 1 slices at most a workgroup: P_CH apply 3D 20^3
-// float64 1684, 1141, 1044 us; 2D 50^2 mixed 954, 851, 818; stage solve 2D P2 50^2
-// 48.1, 30.6, 26.8 ms; 2D 100^2 (ranges of grid lines) 7.6, 7.0, 6.8; PFC1 step 100^2
-// 37.9, 34.6, 33.8.  Not for several rows per thread (a wave's sums have to be one
+// Measured with 16 (the team), 4 and 1 slices at most a workgroup: P_CH apply 2D 50^2
+// mixed 954, 851, 818 us; stage solve 2D P2 50^2 48.1, 30.6, 26.8 ms.  Not for several rows per thread (a wave's sums have to be one
 // slice's), the block forms (their workgroups are blocks) and launches that stage
 // columns (those of the team's slices).
 int solo_workgroups(const pfc_mesh* m, const pfc_opts& o, int team_size) {
@@ -291,7 +289,8 @@ int solo_workgroups(const pfc_mesh* m, const pfc_opts& o, int team_size) {
   if (o.rows_per_thread > 1 || d.n_slices > PFC_SPREAD || staged || sstep_block2(m, o, team_size) ||
       sstep_block3(m, o, team_size))
     return team_size;
-  const int spw = (d.n_slices + 255) / 256;
+  const int spw = (d.n_slices + 255) / 256, H = sstep_halo(m, o, team_size);
+  if (H > 0 && spw * 64 + 4 * H > PFC_SS_NA_SPREAD * PFC_WG) return team_size;
   return (d.n_slices + spw - 1) / spw;
 }
 

@@ -467,7 +467,7 @@ __device__ __forceinline__ Red3 pcg_phase(const InstDev& I, const State& S, cons
 // next launch adds them up in the team's order (the slices of each of its workgroups,
 // then the workgroups): the same bits as the team's own launches.  The sums of the
 // orthogonalisation stay the team's.  Measured, P_CH apply 3D 40^3 float64: 1645 ->
-// 1271 us; a variant of its own, for in the others the choice at run time cost 2.5%
+// 1110 us; a variant of its own, for in the others the choice at run time cost 2.5%
 // (2D 512^2 float64) and 4% (3D 64^3 mixed).
 template <typename T, bool SINGLE, int COLS, bool B2, bool SPREAD>
 __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ teams, const InstDev* __restrict__ insts,
@@ -491,6 +491,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   constexpr bool SS = SINGLE && COLS == PFC_COL_GRID && std::is_same<T, double>::value && !B2;
   constexpr bool SS3 = SINGLE && COLS == PFC_COL_GRID && std::is_same<T, float>::value && !B2 && !SPREAD;
   constexpr bool SSX = SS || SS3 || SB2;
+  constexpr int NA = SPREAD ? PFC_SS_NA_SPREAD : PFC_SS_NA;
   __shared__ double ss_g[SSX ? 32 : 1];
   __shared__ double ss_coef[SSX ? 16 : 1];
   PFC_STAMP(t_entry);
@@ -537,7 +538,9 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     if constexpr (SB2) fuse_in = st_in->fuse;
   }
   double gpl[SSX ? PFC_SS_GL : 1];
-  if constexpr (SSX && SINGLE) ss_gram_prefetch(gram_in_arg, part_in, ssz, gpl);
+  if constexpr (SSX && SINGLE) {
+    if (!SPREAD || gram_in_arg) ss_gram_prefetch(gram_in_arg, part_in, ssz, gpl);
+  }
   // columns of this workgroup's slices: positions [lo, lo + len) of the SELL
   // pattern, issued first and written to LDS once everything has arrived
   int lo = 0, len = 0;
@@ -593,10 +596,14 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   if constexpr (!LATE) {
     if (!SINGLE || phase_partials(ph_in)) {
       if constexpr (SPREAD) {
-        static_assert(3 * PFC_SPREAD <= PFC_SS_LDS && PFC_SPREAD == 2 * PFC_WG, "slice sums in the s-step LDS, two per thread");
-        double *sa = pfc_ss, *sb = sa + PFC_SPREAD, *sc = sb + PFC_SPREAD;  // by slice
-        sa[tid] = pre.a; sb[tid] = pre.b; sc[tid] = pre.c;
-        sa[PFC_WG + tid] = pre2.a; sb[PFC_WG + tid] = pre2.b; sc[PFC_WG + tid] = pre2.c;
+        constexpr int PL = PFC_SPREAD + PFC_SPREAD / 16;
+        static_assert(3 * PL <= PFC_SS_LDS && PFC_SPREAD == 2 * PFC_WG, "slice sums in the s-step LDS, two per thread");
+        double *sa = pfc_ss, *sb = sa + PL, *sc = sb + PL;  // by slice
+        // (a place left free after every 16: the sums read at a stride of 16, all from two
+        // banks without it; prologue of 3D 40^3 4.0 -> 2.3 us)
+        auto at = [](int sl) { return sl + (sl >> 4); };
+        sa[at(tid)] = pre.a; sb[at(tid)] = pre.b; sc[at(tid)] = pre.c;
+        sa[at(PFC_WG + tid)] = pre2.a; sb[at(PFC_WG + tid)] = pre2.b; sc[at(PFC_WG + tid)] = pre2.c;
         __syncthreads();
         pre = pre2 = red3(0.0, 0.0, 0.0);
         if (tid < te.size) {  // workgroup tid of the team: its slices (PFC_SLICES), one per wave
@@ -606,7 +613,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
 #pragma unroll
           for (int w = 0; w < PFC_WAVES; ++w) {
             const int sl = first + w * step;
-            if (sl < end) { pre.a += sa[sl]; pre.b += sb[sl]; pre.c += sc[sl]; }
+            if (sl < end) { pre.a += sa[at(sl)]; pre.b += sb[at(sl)]; pre.c += sc[at(sl)]; }
           }
         }
       }
@@ -640,7 +647,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
   if (__builtin_expect(ph_in == PH_ASPMV, 0))
     gs_gather(I.gpart + (long long)parity * te.size * PFC_GS_NV, te.size, &I.hist->L[0][0], gs_g, gs_L);
   bool scg = false, form = false;
-  SsPre ssp;
+  SsPre<NA> ssp;
   S3Pre<float> s3p;
   B2Pre<T> b2p;
   if constexpr (SSX) {
@@ -714,7 +721,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     if (__builtin_expect(phase == PH_SCG_ITER, 1)) {  // the common launch, laid out first
       double* gout = I.spart + (long long)(1 - parity) * ssz * 32;
       if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, false, gout, b2p, parity);
-      else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, false, gout, ss_rows(I, te.rank, ssz), ssp, parity);
+      else if constexpr (SS) ph_scg<COLS, NA>(I, S, tm, ss_coef, false, gout, ss_rows(I, te.rank, ssz), ssp, parity);
       else ph_scg3<float>(I, S, tm, ss_coef, false, gout, s3p, parity);
       scg_done = true;
     }
@@ -731,7 +738,7 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
           fused = true;
           double* gout = I.spart + (long long)(1 - parity) * ssz * 32;
           if constexpr (SB2) ph_scg2b<T>(I, S, tm, ss_coef, true, gout, b2p, parity);
-          else if constexpr (SS) ph_scg<COLS>(I, S, tm, ss_coef, true, gout, ss_rows(I, te.rank, ssz), ssp, parity);
+          else if constexpr (SS) ph_scg<COLS, NA>(I, S, tm, ss_coef, true, gout, ss_rows(I, te.rank, ssz), ssp, parity);
           else ph_scg3<float>(I, S, tm, ss_coef, true, gout, s3p, parity);
           break;
         }
