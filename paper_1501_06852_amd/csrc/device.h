@@ -1244,6 +1244,38 @@ __device__ __forceinline__ Red3 ph_pch_out(const InstDev& I, const Team& tm) {
 //   alpha_{i+1} = gamma_{i+1} / (delta_{i+1} - beta_{i+1} gamma_{i+1} / alpha_i).
 // u_{i+1} at gathered neighbours is recomputed from r_i, w_i, s_{i-1}; r, w, s
 // are double-buffered, p and x are updated in place by their owners.
+// What an iteration gathers of a row j: r, w, s and d = D^{-1}.  In float they stand side
+// by side, 16 bytes a row in two buffers of two vectors each (RA: rB, wB; RB: sA, sB): one
+// load an entry instead of four, the address units being what bounds the gathers of
+// the long rows (P2 256^2 mixed stage solve 42.6 -> 36.2 ms, 3D 48^3 mixed step 22.0 ->
+// 20.4).  In float64 each is a vector of its own: side by side the rows would be 24 or 32
+// bytes apart, and measured slower (24 bytes, P2 256^2 55.0 -> 60.3 ms).
+typedef float Float4 __attribute__((ext_vector_type(4)));
+typedef unsigned UInt4 __attribute__((ext_vector_type(4)));
+template <typename T>
+struct CgRow {
+  T d, r, w, s;
+};
+template <typename T>
+struct CgBufs {  // float64
+  const T *r, *w, *s, *dinv;
+  __device__ __forceinline__ CgRow<T> operator()(int j) const { return CgRow<T>{vat(dinv, j), vat(r, j), vat(w, j), vat(s, j)}; }
+};
+template <>
+struct CgBufs<float> {
+  const Float4* q;
+  __device__ __forceinline__ CgRow<float> operator()(int j) const {
+    const Float4 v = gld(q + j);
+    return CgRow<float>{v.w, v.x, v.y, v.z};
+  }
+};
+// row sl * 64 + lane of such a buffer (write-through, as vst)
+__device__ __forceinline__ void cg_row_store(void* q, int sl, int lane, float r, float w, float s, float d) {
+  const __amdgpu_buffer_rsrc_t b = __builtin_amdgcn_make_buffer_rsrc((char*)q + (long long)sl * 1024, 0, 1024, 0x00027000);
+  const UInt4 v = {__float_as_uint(r), __float_as_uint(w), __float_as_uint(s), __float_as_uint(d)};
+  __builtin_amdgcn_raw_buffer_store_b128(v, b, lane * 16, 0, 16);  // sc1
+}
+
 template <typename T, int L>
 __device__ __forceinline__ Red3 ph_cg_init(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
@@ -1262,8 +1294,9 @@ __device__ __forceinline__ Red3 ph_cg_init(const InstDev& I, const State& S, con
                   [&](const Term& t) { acc += t.a * (t.d * t.r); });
     if (i < n) {
       const unsigned oi = (unsigned)i * (unsigned)sizeof(T);
-      vsto(w, oi, acc);
-      const T ri = gldo(r, oi), u = gldo(o.dinv, oi) * ri;
+      const T ri = gldo(r, oi), di = gldo(o.dinv, oi), u = di * ri;
+      if constexpr (sizeof(T) == 4) cg_row_store(uni(I.rB), sl, tm.lane, ri, acc, acc, di);  // (s: read times beta = 0)
+      else vsto(w, oi, acc);
       a0 += (double)ri * (double)u;
       a1 += (double)acc * (double)u;
       a2 += (double)ri * (double)ri;
@@ -1282,41 +1315,53 @@ __device__ __forceinline__ Red3 ph_cg_iter(const InstDev& I, const State& S, con
   PcgOps<T> o = pcg_ops<T>(I, S.kind);
   const PatView<L> pv = op_pat<L>(I, o, tm);
   const int c = __builtin_amdgcn_readfirstlane(S.cur);
-  const T* rc = uni((const T*)(c ? I.rB : I.r_));
-  T* rn = uni((T*)(c ? I.r_ : I.rB));
-  const T* wc = uni((const T*)(c ? I.wB : I.q));
-  T* wn = uni((T*)(c ? I.q : I.wB));
-  T* sn = uni((T*)(c ? I.sA : I.sB));
+  constexpr bool AOS = sizeof(T) == 4;
+  const T *rc, *wc;
+  T *rn, *wn, *sn;
+  if constexpr (!AOS) {
+    rc = uni((const T*)(c ? I.rB : I.r_));
+    rn = uni((T*)(c ? I.r_ : I.rB));
+    wc = uni((const T*)(c ? I.wB : I.q));
+    wn = uni((T*)(c ? I.q : I.wB));
+    sn = uni((T*)(c ? I.sA : I.sB));
+  }
   T* p = uni((T*)I.pA);
   // the first iteration has no previous s (s = w + 0 w) and no previous p
   const bool first = __builtin_amdgcn_readfirstlane(S.it) == 0;
-  const T* so = first ? wc : uni((const T*)(c ? I.sB : I.sA));
+  CgBufs<T> in;
+  if constexpr (AOS) in.q = uni((const Float4*)(c ? I.sA : I.rB));
+  else in = CgBufs<T>{rc, wc, first ? wc : uni((const T*)(c ? I.sB : I.sA)), o.dinv};
   const T alpha = T(S.alpha), beta = first ? T(0) : T(S.beta_cg);
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
   struct Term {
-    T a, d, r, w, s;
+    T a;
+    CgRow<T> v;
   };
   auto s_of = [&](T w, T s) { return w + beta * s; };
   PFC_SLICES(I, tm) {
     const int i = sl * 64 + tm.lane;
     const unsigned oi = (unsigned)(i < n ? i : n - 1) * (unsigned)sizeof(T);
-    const T di = gldo(o.dinv, oi), ro = gldo(rc, oi), wo = gldo(wc, oi), so_ = gldo(so, oi), po = gldo((const T*)p, oi),
-            xo = gldo((const T*)o.x, oi);
+    const CgRow<T> own = in(i < n ? i : n - 1);
+    const T di = own.d, ro = own.r, po = gldo((const T*)p, oi), xo = gldo((const T*)o.x, oi);
     T acc = T(0);
     op_entries<ChunkIter<T>>(
-        o, pv, sl, tm.lane, [&](T a, int j) { return Term{a, vat(o.dinv, j), vat(rc, j), vat(wc, j), vat(so, j)}; },
-        [&](const Term& t) { acc += t.a * (t.d * (t.r - alpha * s_of(t.w, t.s))); });
+        o, pv, sl, tm.lane, [&](T a, int j) { return Term{a, in(j)}; },
+        [&](const Term& t) { acc += t.a * (t.v.d * (t.v.r - alpha * s_of(t.v.w, t.v.s))); });
     if (i < n) {
-      const T si = s_of(wo, so_);
+      const T si = s_of(own.w, own.s);
       const T uo = di * ro;
       const T pi = first ? uo : (uo + beta * po);
       vsto(o.x, oi, T(xo + alpha * pi));
       const T ri = ro - alpha * si;
       const T ui = di * (ro - alpha * si);
-      vsto(sn, oi, si);
+      if constexpr (!AOS) vsto(sn, oi, si);
       vsto(p, oi, pi);
-      vsto(rn, oi, ri);
-      vsto(wn, oi, acc);
+      if constexpr (AOS) {
+        cg_row_store(uni(c ? I.rB : I.sA), sl, tm.lane, ri, acc, si, di);
+      } else {
+        vsto(rn, oi, ri);
+        vsto(wn, oi, acc);
+      }
       a0 += (double)ri * (double)ui;
       a1 += (double)acc * (double)ui;
       a2 += (double)ri * (double)ri;

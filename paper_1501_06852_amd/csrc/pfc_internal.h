@@ -211,7 +211,8 @@ struct InstDev {
   double* errpart;              // [2 n_slices] per-slice partial sums (embedded error, mobility mean)
   // inner PCG vectors (sized for float64; typed by precision)
   void *r_, *pA, *pB, *q, *y0, *y1, *zt, *x1, *x2;
-  void *rB, *wB, *sA, *sB;      // extra buffers of the single-reduction PCG
+  void *rB, *wB, *sA, *sB;      // extra buffers of the single-reduction PCG (adjacent: in float rB, wB and sA, sB
+                                // are two buffers of 16 bytes a row, CgRow)
   double* part;                 // [2][team_size][4] partial sums
   double* gpart;                // [2][team_size][64] Gram partial sums of the orthogonalisation, or the per-slice
                                 // sums (4 a slice) of launches on more workgroups than the team's
