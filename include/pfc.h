@@ -411,15 +411,16 @@ int pfc_apply_AR_x(pfc_instance* inst, const double* x_k, double r, double tau, 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid allocation): out = A^R y as
  * pfc_apply_AR, on a PFC2 mesh without an instance.  N(psi_k) is reassembled
- * into a library-owned static device array of PFC_NOALLOC_MAX_ENTRIES float64
- * values (32 MiB; each GPU the library runs on holds its own copy until the
- * process ends) instead of an instance's memory; the call performs no device
+ * on the chip, row by row; for meshes with a row of more than 96 entries into a
+ * library-owned static device array of PFC_NOALLOC_MAX_ENTRIES float64 values
+ * (32 MiB; each GPU the library runs on holds its own copy until the process
+ * ends) instead of an instance's memory; the call performs no device
  * allocation or free.
  *   mesh      any mesh whose stored pattern has at most PFC_NOALLOC_MAX_ENTRIES
  *             entries (2D 512^2: 1.84M, 3D 64^3: 3.93M); a larger one returns
  *             PFC_ERR_ARG before anything is enqueued
  *   psi_k     device float64 [n]; y, out device float64 [3n]
- * Unlike the other calls it only enqueues its two kernels on `stream` and
+ * Unlike the other calls it only enqueues its kernels on `stream` and
  * returns (so it can be captured into a graph); the caller synchronises.
  * The first call on a device resolves the array's address (no allocation);
  * make it outside graph capture.  Every call on a GPU uses that GPU's one

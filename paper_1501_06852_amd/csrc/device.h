@@ -1249,7 +1249,7 @@ __device__ __forceinline__ Red3 ph_pch_out(const InstDev& I, const Team& tm) {
 // load an entry instead of four, the address units being what bounds the gathers of
 // the long rows (P2 256^2 mixed stage solve 42.6 -> 36.2 ms, 3D 48^3 mixed step 22.0 ->
 // 20.4).  In float64 each is a vector of its own: side by side the rows would be 24 or 32
-// bytes apart, and measured slower (24 bytes, P2 256^2 55.0 -> 60.3 ms).
+// bytes apart, and measured slower (P2 256^2: 55.0 ms, at 24 bytes 60.3, at 32 59.3).
 typedef float Float4 __attribute__((ext_vector_type(4)));
 typedef unsigned UInt4 __attribute__((ext_vector_type(4)));
 template <typename T>

@@ -92,7 +92,7 @@ __global__ void k_prep_sd(InstDev I) {
   if (i < I.n) ((T*)I.dinvSD)[i] = T(1.0 / dg);
 }
 
-// K_+(psi) and F(mu) of the PFC1 model on the P1 pattern, in place (LDS: 16 per thread)
+// K_+(psi) and F(mu) of the PFC1 model on the P1 pattern, in place (LDS: 8 per thread)
 #define PFC_MOB_CAP 8
 __global__ void k_assemble_mob(InstDev I, const double* __restrict__ psi, const double* __restrict__ mu) {
   __shared__ double acc[PFC_MOB_CAP * 256];
