@@ -30,12 +30,23 @@ CASES = [(2, 8, 0.2, 1, 0, 1), (2, 9, 0.0, 1, 1, 1), (2, 32, 0.2, 1, 1, 1), (2, 
 
 @pytest.mark.parametrize("dim,N,jit,degree,prec,grid", CASES)
 def test_spread_launches_equal_team_launches(pfc, dim, N, jit, degree, prec, grid):
-    P, Q = Problem(dim, N, jit, seed=41, degree=degree), Problem(2, 10, 0.0, seed=42)
+    _alone_equals_batch(pfc, Problem(dim, N, jit, seed=41, degree=degree), precision=prec, grid_columns=grid)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("opts", [dict(model=1), dict(schur_variant=1), dict(single_reduction=0), dict(shared_ops=1)],
+                         ids=lambda o: next(iter(o)))
+def test_spread_launches_options(pfc, opts, prec):
+    _alone_equals_batch(pfc, Problem(2, 33, 0.2, seed=44), precision=prec, **opts)
+
+
+def _alone_equals_batch(pfc, P, **opts):
+    Q = Problem(2, 10, 0.0, seed=42)
     prm = wl.draw_params(2, 700)
     insts, states = [], []
     try:
         for p, X in zip(prm, (P, Q)):
-            o = pfc.pfc_opts_default(precision=prec, rows_per_thread=1, pcg_steps_per_launch=1, grid_columns=grid)
+            o = pfc.pfc_opts_default(rows_per_thread=1, pcg_steps_per_launch=1, **opts)
             insts.append(pfc.pfc_instance_create(X.gpu_mesh(), o))
             states.append(np.concatenate([np.zeros(X.n), wl.psi0(X.n, p.psibar, 0.01, seed=p.seed), np.zeros(X.n)]))
         alone = []
