@@ -41,8 +41,8 @@ HBM_PEAK_GBS = 8000.0
 # was taken on: when their digest differs, `traffic` is reported as null.
 TRAFFIC = {
     # workload: (sha256 of the kernel sources, bytes per launch, algorithmic bytes per launch of the same run)
-    "pfc2d_512_fp64": ("746c2a21660abb65c1d66b34a9d9c660a7f1880cb7ef40cc3d1a63de3558ae57", 45883405.0, 85211856.0),
-    "pfc3d_64_mixed": ("746c2a21660abb65c1d66b34a9d9c660a7f1880cb7ef40cc3d1a63de3558ae57", 37414157.0, 71753338.0),
+    "pfc2d_512_fp64": ("5d5cd65844577a56e2b1a161728419fd8b5c8c648fe81de45ee6a64c1930da38", 45884907.0, 85211856.0),
+    "pfc3d_64_mixed": ("5d5cd65844577a56e2b1a161728419fd8b5c8c648fe81de45ee6a64c1930da38", 37439688.0, 71753338.0),
 }
 
 

@@ -279,9 +279,14 @@ bool block_form_applies(const pfc_mesh* m, const pfc_opts& o) {
 // Workgroups of launches that serve the instance alone: its team, or, on meshes of
 // at most PFC_SPREAD slices, as few slices a workgroup as the chip's 256 CUs allow.
 // Measured with 16 (the team), 4 and 1 slices at most a workgroup: P_CH apply 2D 50^2
-// mixed 954, 851, 818 us; stage solve 2D P2 50^2 48.1, 30.6, 26.8 ms.  Not for several rows per thread (a wave's sums have to be one
-// slice's), the block forms (their workgroups are blocks) and launches that stage
-// columns (those of the team's slices).
+// mixed 954, 851, 818 us; stage solve 2D P2 50^2 48.1, 30.6, 26.8 ms.  Near the limit
+// the gain runs out: team and spread, 3D 50^3 float64 1701, 1382 us, mixed 1123, 1057,
+// 2D 350^2 mixed 980, 943.  A limit of 3840
+// slices (four sums a thread in the prologue instead of two) measured slower above
+// 2048 (P_CH apply 3D 56^3 float64 1698 -> 1737 us) and below (3D 20^3 967 -> 1100).
+// Not for several rows per thread (a wave's sums have to be one slice's), the block
+// forms (their workgroups are blocks) and launches that stage columns (those of the
+// team's slices).
 int solo_workgroups(const pfc_mesh* m, const pfc_opts& o, int team_size) {
   const MeshDev& d = m->dev;
   const bool grid = d.gN > 0 && o.grid_columns;
