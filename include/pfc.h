@@ -345,9 +345,11 @@ int pfc_last_inner_counts(const pfc_instance* inst, int* counts, int cap, int* n
 
 /* Launch statistics of the instance's most recent solve or run (for
  * pfc_rosenbrock_adaptive: summed over all its attempted steps): number of
- * solver-kernel launches issued (replayed graphs times launches per graph,
- * including launches that found the instance finished) and number of graph
- * replays.  Host outputs; either may be NULL. */
+ * solver-kernel launches that advanced the instance, up to and including the
+ * one that found it finished (counted on the device; the launches behind it in
+ * the graphs that were already queued do nothing and are not counted), and
+ * number of graph replays issued, which depends on when the host saw the end.
+ * Host outputs; either may be NULL. */
 int pfc_instance_launch_stats(const pfc_instance* inst, long long* launches, long long* graphs);
 
 /* Launch configuration an instance runs with when a launch serves it alone

@@ -147,6 +147,7 @@ struct State {
   double xc0, xc1, xc3;      // its last increment of x over the basis [p, Tp, ., u] (stored the launch after)
   double vscale, bnorm, bnorm_s, est_thresh, w0, est, rel;
   long long t0;             // device clock at the solve's first launch
+  int launches, pad_l;      // launches that advanced the instance (counted where the state is stored)
 };
 
 // Single-buffered FGMRES history of the current cycle.  Every entry is

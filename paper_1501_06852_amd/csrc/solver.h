@@ -29,18 +29,19 @@ void launch_tick_f64(const TickLaunch& q, hipStream_t stream);
 void launch_tick_f32(const TickLaunch& q, hipStream_t stream);
 
 struct Group {
-  int count = 0, n_wg = 0, graph_ticks = 0;
+  int count = 0, n_wg = 0;
   TeamEntry* d_teams = nullptr;
   std::vector<TeamEntry> h_teams;
   int cols = 0;                 // where the launches take the P1 columns from (PFC_COL_*)
   InstDev* d_descs = nullptr;
   InstDev* h_descs = nullptr;   // pinned staging of the descriptors
   State* h_states = nullptr;    // pinned staging of the initial states
-  int* h_flags = nullptr;       // pinned, mapped: phase of each instance after each replay
+  int* h_flags = nullptr;       // pinned, mapped: after each replay, the phase of each instance, then its launches
   int* d_flags = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   long long graphs_run = 0;
+  long long launches = 0;       // launches of the last run until its last instance was done
   int alloc(const std::vector<int>& team_sizes);
   int build(hipStream_t capture, int precision, int ticks);
   int run(hipStream_t s, const std::vector<State*>& dev_states, double timeout_s);

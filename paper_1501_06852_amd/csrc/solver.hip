@@ -35,7 +35,10 @@ extern "C" unsigned long long pfc_debug_trace_count(void) {
 
 __global__ void k_report(const InstDev* __restrict__ insts, int count, int* __restrict__ flags) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) flags[i] = insts[i].st[0].phase;
+  if (i < count) {
+    flags[i] = insts[i].st[0].phase;
+    flags[count + i] = insts[i].st[0].launches;
+  }
 }
 
 // Per-tau operator values: C_d = M + delta K, C_sd = M + sqrt(delta) K (stored
@@ -411,7 +414,6 @@ void fill_info(pfc_solve_info* dst, const InfoDev& s) {
 // The descriptors (h_descs) must be filled before build(): a one-instance
 // group bakes that instance's state and partial-sum buffers into the launches.
 int Group::build(hipStream_t capture, int precision, int ticks) {
-  graph_ticks = ticks;
   for (int i = 0; i < count; ++i)
     if (!h_descs[i].st || !h_descs[i].part || h_descs[i].team_size <= 0) {
       set_error("internal: launch group built before its descriptors were set");
@@ -502,7 +504,7 @@ int Group::alloc(const std::vector<int>& team_sizes) {
   PFC_HIP(hipMalloc((void**)&d_descs, sizeof(InstDev) * count));
   PFC_HIP(hipHostMalloc((void**)&h_descs, sizeof(InstDev) * count, hipHostMallocDefault));
   PFC_HIP(hipHostMalloc((void**)&h_states, sizeof(State) * count, hipHostMallocDefault));
-  PFC_HIP(hipHostMalloc((void**)&h_flags, sizeof(int) * count, hipHostMallocMapped));
+  PFC_HIP(hipHostMalloc((void**)&h_flags, sizeof(int) * 2 * count, hipHostMallocMapped));
   PFC_HIP(hipHostGetDevicePointer((void**)&d_flags, h_flags, 0));
   for (int i = 0; i < count; ++i) h_flags[i] = -1;
   PFC_HIP(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
@@ -552,6 +554,8 @@ int Group::run(hipStream_t s, const std::vector<State*>& dev_states, double time
   }
   graphs_run = k + 2;
   PFC_HIP(hipStreamSynchronize(s));
+  launches = 0;
+  for (int i = 0; i < count; ++i) launches = std::max(launches, (long long)((volatile int*)h_flags)[count + i]);
   return PFC_OK;
 }
 
@@ -907,7 +911,7 @@ int pfc_solve_x(pfc_instance* I, const double* x_k, double r, double psibar, dou
 int pfc_instance_launch_stats(const pfc_instance* I, long long* launches, long long* graphs) {
   if (!I) { set_error("pfc_instance_launch_stats: null instance"); return PFC_ERR_ARG; }
   if (graphs) *graphs = I->grp.graphs_run;
-  if (launches) *launches = I->grp.graphs_run * (long long)I->grp.graph_ticks;
+  if (launches) *launches = I->grp.launches;
   return PFC_OK;
 }
 
@@ -991,7 +995,7 @@ int pfc_rosenbrock_adaptive(pfc_instance* I, double* state, double r, double psi
   *n_rejected = 0;
   int rc = set_mobility_mean(I, state + n, s), worst = PFC_OK;
   std::vector<double> part(ns);
-  long long graphs = 0;  // launch statistics of the whole call (one run per attempted step)
+  long long graphs = 0, launches = 0;  // launch statistics of the whole call (one run per attempted step)
   if (!rc && init == PFC_INIT_CONSISTENT) {
     set_params(h, r, tau0, 1.0 / ROS_GAMMA);
     h.n_steps = 0;
@@ -999,6 +1003,7 @@ int pfc_rosenbrock_adaptive(pfc_instance* I, double* state, double r, double psi
     rc = prep_ops(I, s);
     if (!rc) rc = run_single(I, s, JOB_RB);
     graphs += I->grp.graphs_run;
+    launches += I->grp.launches;
   }
   double t = 0.0, tau = tau0;
   bool after_reject = false;  // the step after a rejection may not grow
@@ -1012,6 +1017,7 @@ int pfc_rosenbrock_adaptive(pfc_instance* I, double* state, double r, double psi
     if (!rc) rc = run_single(I, s, JOB_RB);
     if (rc) break;
     graphs += I->grp.graphs_run;
+    launches += I->grp.launches;
     State fin;
     if (hipMemcpy(&fin, h.st, sizeof(State), hipMemcpyDeviceToHost) != hipSuccess) { rc = PFC_ERR_HIP; break; }
     if (infos) {  // the three stage solves of this attempt, accepted or not
@@ -1052,6 +1058,7 @@ int pfc_rosenbrock_adaptive(pfc_instance* I, double* state, double r, double psi
   }
   if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = PFC_ERR_HIP;
   I->grp.graphs_run = graphs;
+  I->grp.launches = launches;
   h.xk = own_xk;
   if (rc) return rc;
   if (worst < 0) return worst;

@@ -10,6 +10,7 @@
 // tick_f32.hip), which compile side by side.
 #pragma once
 #include <cmath>
+#include <cstddef>
 #include <type_traits>
 
 #include "device.h"
@@ -699,8 +700,10 @@ __global__ __launch_bounds__(PFC_WG) void k_tick(const TeamEntry* __restrict__ t
     __syncthreads();
   }
   PFC_STAMP(t_trans);
-  // the new state is final: workgroup 0 stores it while the phase runs
-  if (writer && tid < NS) ((int*)st_out)[tid] = ((const int*)&S)[tid];
+  // the new state is final: workgroup 0 stores it while the phase runs (and counts the
+  // launch there, off the transition's scalar chain)
+  if (writer && tid < NS)
+    ((int*)st_out)[tid] = ((const int*)&S)[tid] + (tid == (int)(offsetof(State, launches) / 4) ? 1 : 0);
   Team tm{te.rank, wgs, tid >> 6, tid & 63, lo};
   if constexpr (SB2) {
     // the previous launch ended a solve in its set-up: that solve's x on the own rows
