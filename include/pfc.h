@@ -403,7 +403,8 @@ int pfc_rosenbrock_adaptive(pfc_instance* inst, double* state, double r, double 
                             int* n_rejected, pfc_solve_info* infos, void* stream);
 
 /* Operator-level entry points of the hot path (device pointers). */
-/* out = A^R y with N(psi_k) reassembled from psi_k; y, out [3n]. */
+/* out = A^R y with N(psi_k) reassembled from psi_k; y, out [3n].  out may
+ * overlap psi_k (here and in the two calls below), but not y. */
 int pfc_apply_AR(pfc_instance* inst, const double* psi_k, double r, double tau, double m11,
                  const double* y, double* out, void* stream);
 /* out = A^R y at the full state x_k [3n] (N(psi_k), and for PFC1 K_+(psi_k)
@@ -413,11 +414,11 @@ int pfc_apply_AR_x(pfc_instance* inst, const double* x_k, double r, double tau, 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid allocation): out = A^R y as
  * pfc_apply_AR, on a PFC2 mesh without an instance.  N(psi_k) is reassembled
- * on the chip, row by row; for meshes with a row of more than 96 entries into a
- * library-owned static device array of PFC_NOALLOC_MAX_ENTRIES float64 values
- * (32 MiB; each GPU the library runs on holds its own copy until the process
- * ends) instead of an instance's memory; the call performs no device
- * allocation or free.
+ * on the chip, row by row; for meshes with a row of more than 96 entries, or
+ * where out overlaps psi_k, into a library-owned static device array of
+ * PFC_NOALLOC_MAX_ENTRIES float64 values (32 MiB; each GPU the library runs on
+ * holds its own copy until the process ends) instead of an instance's memory;
+ * the call performs no device allocation or free.
  *   mesh      any mesh whose stored pattern has at most PFC_NOALLOC_MAX_ENTRIES
  *             entries (2D 512^2: 1.84M, 3D 64^3: 3.93M); a larger one returns
  *             PFC_ERR_ARG before anything is enqueued

@@ -58,9 +58,10 @@ struct pfc_mesh {
 namespace pfc {
 int build_second_ring(pfc_mesh* m);
 // N(psi) on the mesh's stored pattern (csr: in CSR order); A^R y with N(psi_k)
-// formed on the way, where the mesh's rows are short enough for that
+// formed on the way, where the mesh's rows are short enough for that and psi does
+// not overlap out
 int launch_row_N(const pfc_mesh* m, const double* psi, double* out, bool csr, hipStream_t s);
-bool row_AR_applies(const pfc_mesh* m);
+bool row_AR_applies(const pfc_mesh* m, const double* psi, const double* out);
 int launch_row_AR(const pfc_mesh* m, const double* psi, double r, double tau, double m11, const double* y, double* out,
                   hipStream_t s);
 }

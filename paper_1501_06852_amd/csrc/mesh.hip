@@ -5,6 +5,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -324,7 +325,13 @@ static int launch_row_psi3(const pfc_mesh* m, const double* psi, double* g, hipS
   return PFC_OK;
 }
 
-bool row_AR_applies(const pfc_mesh* m) { return !m->dev.nv_wide; }
+// k_row_AR reads psi at neighbours while other workgroups write out: where the two
+// overlap (the caller may keep psi_k in the vector that it lets the result replace),
+// N is formed by a launch of its own, which has read psi before out is written.
+bool row_AR_applies(const pfc_mesh* m, const double* psi, const double* out) {
+  const std::less<const double*> before;
+  return !m->dev.nv_wide && !(before(psi, out + 3LL * m->n) && before(out, psi + m->n));
+}
 
 int launch_row_AR(const pfc_mesh* m, const double* psi, double r, double tau, double m11, const double* y, double* out,
                   hipStream_t s) {

@@ -1076,7 +1076,7 @@ static int apply_AR_impl(pfc_instance* I, const double* psi_k, const double* mu_
   InstDev h = I->h;
   h.r = r; h.tau = tau; h.m11 = m11;
   int rc;
-  if (h.model == PFC_MODEL_PFC2 && row_AR_applies(I->mesh)) {
+  if (h.model == PFC_MODEL_PFC2 && row_AR_applies(I->mesh, psi_k, out)) {
     rc = launch_row_AR(I->mesh, psi_k, r, tau, m11, y, out, s);
   } else {
     rc = launch_row_N(I->mesh, psi_k, h.N, false, s);
@@ -1116,10 +1116,10 @@ int pfc_apply_AR_noalloc(const pfc_mesh* m, const double* psi_k, double r, doubl
               " matrix entries, more than the scratch buffer's " + std::to_string(PFC_NOALLOC_MAX_ENTRIES));
     return PFC_ERR_ARG;
   }
-  if (row_AR_applies(m)) return launch_row_AR(m, psi_k, r, tau, m11, y, out, (hipStream_t)stream);
   double* N = nullptr;
-  int rc = scratch_address(&N);
+  int rc = scratch_address(&N);  // (by whichever call is a device's first: a later one may be captured)
   if (rc) return rc;
+  if (row_AR_applies(m, psi_k, out)) return launch_row_AR(m, psi_k, r, tau, m11, y, out, (hipStream_t)stream);
   hipStream_t s = (hipStream_t)stream;
   InstDev h;
   std::memset(&h, 0, sizeof(h));
