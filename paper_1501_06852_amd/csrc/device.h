@@ -354,8 +354,7 @@ __device__ __forceinline__ double cm_of(int dim) { return dim == 2 ? (1.0 / 360.
 // Measured per call, launch and wait (19 us) included: pfc_assemble_N on 3D 64^3
 // 429 -> 67 us, pfc_apply_AR on 2D 512^2 65 -> 31 us, pfc_stage_rhs on 3D 48^3
 // 128 -> 49 us, pfc_load_psi3 on P2 200^2 68 -> 33 us; inside the solver's
-// launches (psi through the element's nodes, eight entries a round) a 3D 64^3
-// step 25.8 -> 25.3 ms.
+// launches (psi through the element's nodes, row_matrix) a 3D 64^3 step 25.8 -> 25.3 ms.
 
 // one visit: the simplex, its volume, the node's local index a, psi at the
 // simplex's Q nodes; slot(c): position of its local node c in the row
@@ -483,6 +482,24 @@ struct RowAcc {
   }
 };
 
+// ... in the row's stored entries themselves: entry k at out[64 k] (device memory)
+struct RowMem {
+  double* out;
+  template <int Q>
+  __device__ __forceinline__ void add(const Visit<Q>& v, const double* x, const double* y) const {
+    double t[Q];
+    int s[Q];
+#pragma unroll
+    for (int b = 0; b < Q; ++b) { s[b] = 64 * v.slot(b); t[b] = gld(out + s[b]); }
+#pragma unroll
+    for (int b = 0; b < Q; ++b) *gp(out + s[b]) = fma(x[b], y[b], t[b]);
+  }
+  __device__ __forceinline__ void add1(int pos, double x, double y) const {
+    double* p = out + 64 * pos;
+    *gp(p) = fma(x, y, gld(p));
+  }
+};
+
 // the simplex's contributions to Mpsi2 between the node and each of its nodes
 template <int Q, typename Acc>
 __device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v, const Acc& acc) {
@@ -576,6 +593,27 @@ __device__ __forceinline__ void row_sums(double* acc, int st, int cap, int w, Te
     term(RowAcc<ALL>{acc, st, s0, c});
     for (int k = 0; k < c; ++k) put(s0 + k, acc[k * st]);
     if (ALL) break;
+  }
+}
+
+// Row of a matrix of element sums in the mesh's layout (entry k at out[64 k]), times
+// scale, with room for cap sums per thread in LDS.  A round of row_sums walks all
+// simplices of the row again, so its time grows with the square of a long row: rows of
+// more than two rounds are summed in place in one walk (ANY: the mesh may have them),
+// at the price of a read of the stored sums per visit; P2 rows always, whose visits are
+// the dearer part (all Q terms of a visit are formed in every round).  A step with one
+// Arnoldi step and one inner iteration a solve, rounds -> in place: hub of 1000
+// triangles 86.1 -> 14.5 ms, unstructured tetrahedra with 10^5 nodes (rows of 16, at
+// most 54) 4.09 -> 3.77, P2 tetrahedra 20^3 3.92 -> 3.47, unstructured P2 tetrahedra
+// with 173665 nodes 25.5 -> 13.7; grids of rows up to 16 keep the rounds (1.06, 1.06).
+template <bool ANY, int Q, typename TermF>
+__device__ __forceinline__ void row_matrix(double* acc, int st, int cap, int w, double* out, double scale, TermF term) {
+  if (Q > 4 || (ANY && w > 2 * cap)) {
+    for (int k = 0; k < w; ++k) *gp(out + 64LL * k) = 0.0;
+    term(RowMem{out});
+    for (int k = 0; k < w; ++k) *gp(out + 64LL * k) = scale * gld(out + 64LL * k);
+  } else {
+    row_sums<false>(acc, st, cap, w, term, [&](int k, double x) { out[64LL * k] = scale * x; });
   }
 }
 
@@ -674,33 +712,33 @@ __device__ __forceinline__ double node_psi3(const MeshDev& m, int sl, int lane, 
   return g;
 }
 
-// N(psi) = -3 Mpsi2 on the row of (slice, lane), put(position, value)
-template <bool ANY, typename PsiF, typename PutF>
+// N(psi) = -3 Mpsi2 on the row of (slice, lane), stored at out[64 k]
+template <bool ANY, typename PsiF>
 __device__ __forceinline__ void row_N(const MeshDev& m, int sl, int lane, double* acc, int st, int cap, int w,
-                                      PsiF psi, PutF put) {
+                                      PsiF psi, double* out) {
   with_nloc<ANY>(m, [&](auto q) {
     constexpr int Q = decltype(q)::value;
-    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+    row_matrix<ANY, Q>(acc, st, cap, w, out, -3.0, [&](auto sums) {
       for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi),
                                           [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
-    }, [&](int k, double x) { put(k, -3.0 * x); });
+    });
   });
 }
 
-// K_+(psi) and F(mu) on the row of (slice, lane) (PFC1: P1 meshes)
-template <bool ANY, typename PsiF, typename MuF, typename PutF, typename PutG>
+// K_+(psi) and F(mu) on the row of (slice, lane) (PFC1: P1 meshes), stored at kp[64 k], fm[64 k]
+template <bool ANY, typename PsiF, typename MuF>
 __device__ __forceinline__ void row_mob(const MeshDev& m, int sl, int lane, double* acc, int st, int cap, int w,
-                                        PsiF psi, MuF mu, double psi_min, PutF put_k, PutG put_f) {
+                                        PsiF psi, MuF mu, double psi_min, double* kp, double* fm) {
   with_nloc<false>(m, [&](auto q) {
     constexpr int Q = decltype(q)::value;
-    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+    row_matrix<ANY, Q>(acc, st, cap, w, kp, 1.0, [&](auto sums) {
       for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, psi),
                                           [&](const Visit<Q>& v) { visit_Kplus<Q>(m, v, psi_min, sums); });
-    }, put_k);
-    row_sums<false>(acc, st, cap, w, [&](auto sums) {
+    });
+    row_matrix<ANY, Q>(acc, st, cap, w, fm, 1.0, [&](auto sums) {
       for_visits<Q, VisitU<Q>::mem, true, ANY>(m, sl, lane, node_psi<Q>(m, mu),
                                           [&](const Visit<Q>& v) { visit_F<Q>(m, v, sums); });
-    }, put_f);
+    });
   });
 }
 
@@ -732,10 +770,10 @@ __device__ __forceinline__ Red3 ph_rb_begin(const InstDev& I, const Team& tm) {
     const long long e0 = (long long)pv.base(sl) + lane;
     double* acc = pfc_ss + threadIdx.x;
     constexpr int cap = PFC_SS_LDS / PFC_WG;
-    row_N<L != PFC_COL_GRID>(I.m, sl, lane, acc, PFC_WG, cap, w, psi, [&](int k, double x) { I.N[e0 + 64LL * k] = x; });
+    row_N<L != PFC_COL_GRID>(I.m, sl, lane, acc, PFC_WG, cap, w, psi, I.N + e0);
     if (I.model == PFC_MODEL_PFC1)
       row_mob<L != PFC_COL_GRID>(I.m, sl, lane, acc, PFC_WG, cap, w, psi, [&](int j) { return xk[j]; }, I.psi_min,
-              [&](int k, double x) { I.Kp[e0 + 64LL * k] = x; }, [&](int k, double x) { I.Fm[e0 + 64LL * k] = x; });
+                                 I.Kp + e0, I.Fm + e0);
   }
   return red3(0.0, 0.0);
 }

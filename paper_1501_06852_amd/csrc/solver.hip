@@ -106,8 +106,7 @@ __global__ void k_assemble_mob(InstDev I, const double* __restrict__ psi, const 
   const int w = (I.m.slice_ptr[sl + 1] - base) >> 6;
   const long long e0 = (long long)base + lane;
   row_mob<true>(I.m, sl, lane, acc + threadIdx.x, 256, PFC_MOB_CAP, w, [&](int j) { return psi[j]; },
-          [&](int j) { return mu[j]; }, I.psi_min, [&](int k, double x) { I.Kp[e0 + 64LL * k] = x; },
-          [&](int k, double x) { I.Fm[e0 + 64LL * k] = x; });
+                [&](int j) { return mu[j]; }, I.psi_min, I.Kp + e0, I.Fm + e0);
 }
 
 // per slice: sum of (M psi)_i and of (M 1)_i over its rows (the mobility mean
