@@ -500,13 +500,18 @@ struct RowMem {
   }
 };
 
+// the bracket of int_T psi_h^2 lambda_a lambda_b (one rounding sequence, whatever the
+// compiler could contract: with float32 inner solves a last place here can move a
+// result by far more)
+__device__ __forceinline__ double psi2_product(double S1, double S2, double pa, double pb) {
+  return fma(2.0, fma(pa, pb, fma(pa, pa, pb * pb)), fma(pa + pb, S1 + S1, fma(S1, S1, S2)));
+}
+
 // the simplex's contributions to Mpsi2 between the node and each of its nodes
 template <int Q, typename Acc>
 __device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v, const Acc& acc) {
   if constexpr (Q <= 4) {
     const double cm = cm_of(Q - 1);
-    // (one rounding sequence, whatever the compiler could contract: with float32
-    // inner solves a last place here can move a result by far more)
     double S1 = 0.0, S2 = 0.0;
 #pragma unroll
     for (int c = 0; c < Q; ++c) { S1 += v.p[c]; S2 = fma(v.p[c], v.p[c], S2); }
@@ -516,9 +521,8 @@ __device__ __forceinline__ void visit_Mpsi2(const MeshDev& m, const Visit<Q>& v,
     double x[Q], y[Q];
 #pragma unroll
     for (int b = 0; b < Q; ++b) {
-      const double pb = v.p[b];
       x[b] = v.vol * cm * (v.a == b ? 2.0 : 1.0);
-      y[b] = fma(2.0, fma(pa, pb, fma(pa, pa, pb * pb)), fma(pa + pb, S1 + S1, fma(S1, S1, S2)));
+      y[b] = psi2_product(S1, S2, pa, v.p[b]);
     }
     acc.add(v, x, y);
   } else {

@@ -25,7 +25,8 @@ struct pfc_mesh {
   int dim = 0, n = 0, nnz = 0, n_elem = 0, n_slices = 0;
   int uniform_width = 0;               // common slice width (1..16), 0 if slices differ
   int degree = 1, nloc = 0;            // Lagrange degree and nodes per element
-  double* d_p2tab = nullptr;           // P2 reference tables (M2, D, C2, C3)
+  double* d_p2tab = nullptr;           // P2 reference tables (M2, D, C2, C3, C2 transposed)
+  const double* d_p2C2t = nullptr;
   long long nnz_sell = 0;
   std::vector<int> row_ptr, col_idx;   // CSR pattern (host)
   std::vector<long long> csr2sell;     // CSR slot -> SELL position
@@ -69,16 +70,16 @@ int launch_row_AR(const pfc_mesh* m, const double* psi, double r, double tau, do
 namespace pfc {
 // Launch shape of the mesh-level kernels with element sums with `arrays` values per row entry in LDS:
 // as many threads as keep four workgroups on a CU, down to one wave; rows too
-// long for that are not staged (one array of cap entries per thread, in rounds).
+// long for that are not staged.
 // The mesh's byte-wide positions (rows of at most PFC_ROW_MAX entries) go with staging.
 #define PFC_ROW_T 256  // threads of a workgroup at most, a row each
 struct RowPlan {
   int T, cap;
   bool stage;
-  size_t lds(int arrays) const { return (size_t)(stage ? arrays : 1) * cap * (T + 1) * sizeof(double); }
+  size_t lds(int arrays) const { return (size_t)arrays * cap * (T + 1) * sizeof(double); }
 };
 inline RowPlan row_plan(const pfc_mesh* m, int arrays) {
-  if (m->dev.nv_wide) return RowPlan{64, 64, false};
+  if (m->dev.nv_wide) return RowPlan{64, 0, false};
   RowPlan p{PFC_ROW_T, m->dev.zmax, true};
   while (p.T > 64 && p.lds(arrays) > 40 * 1024) p.T /= 2;
   return p;

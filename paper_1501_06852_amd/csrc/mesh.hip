@@ -191,8 +191,8 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_spmv(MeshDev m, const double* __r
 // and the stage right-hand side that contain them).  STAGE: psi at the row's
 // neighbours is gathered once into LDS (sp[k * st], position k of the row), and
 // every visit reads it there; otherwise (rows too long for that) each visit
-// gathers it through the element's nodes.  st = threads + 1, so that reading a
-// row's sums back along the row has no bank conflicts.
+// gathers it through the element's nodes (N then: k_lanes_N).  st = threads + 1, so
+// that reading a row's sums back along the row has no bank conflicts.
 
 template <int Q, bool STAGE, typename F>
 __device__ __forceinline__ void row_visits(const MeshDev& m, int sl, int lane, const double* psi, const double* sp, int st,
@@ -204,52 +204,148 @@ __device__ __forceinline__ void row_visits(const MeshDev& m, int sl, int lane, c
 }
 
 // N(psi) = -3 Mpsi2, in the mesh's layout (row_ptr null) or in CSR order.
-template <int Q, bool STAGE>
+// LDS accesses of a wave's lanes to each other's places, ordered
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// N(psi) with L lanes of a wave per row (lanes_N: where).  A batch is as many of the
+// row's simplices as have L nodes in all: a lane per (simplex, node b) gathers psi there
+// and forms the simplex's term between the row's node and b; the terms are then added in
+// element order, a lane per b (the positions of a simplex's nodes differ), to the row's
+// sums in LDS, or in the row itself where it has more than cap entries.  Bound by the
+// batch's three round trips and its serial additions; 64 lanes for long rows, 16 for the
+// 9 and 19 entries of 2D P2 (2D P2 40^2 22 us a call, 32 lanes 24, 64 lanes 26).  Against
+// the walk per stored entry: hub of 200 triangles 117 -> 43 us a call, of 1000 510 -> 138
+// (k_row_N in rounds of 64 entries: 495 and 8990), of 40 P2 vertices in 3D 119 -> 45,
+// unstructured P2 tetrahedra with 34350 nodes 426 -> 305, 3D P2 12^3 180 -> 130.
+#define PFC_LANES_ROWS 4    // rows of a wave, 64 / L side by side
+#define PFC_LANES_CAP 2048  // sums of a row in LDS at most
+#define PFC_LANES_BUF 224   // further LDS of a wave, in doubles: psi, the terms' factors, positions
+template <int Q, int L>
+__global__ __launch_bounds__(PFC_ROW_T) void k_lanes_N(MeshDev m, const double* __restrict__ psi, double* out,
+                                                       const int* __restrict__ row_ptr, int cap,
+                                                       const double* __restrict__ Ct) {
+  constexpr int B = L / Q, G = 64 / L, BITS = Q <= 4 ? 2 : 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane / L, ln = lane % L;
+  const int rank = xcd_rank(blockIdx.x, gridDim.x);
+  double* ps = pfc_row_lds + wave * (PFC_LANES_BUF + G * cap);
+  double *xs = ps + 64, *ys = xs + 64, *acc = ps + PFC_LANES_BUF + g * cap;
+  int* ss = (int*)(ys + 64);
+  const int t = ln / Q, b = ln - t * Q;  // the lane's simplex of the batch, and its node
+  const int i0 = __builtin_amdgcn_readfirstlane((rank * (PFC_ROW_T / 64) + wave) * PFC_LANES_ROWS), sl = i0 >> 6;
+  if (sl >= m.n_slices) return;
+  const long long vb = m.nv_ptr[sl];
+  const int vw = (int)((m.nv_ptr[sl + 1] - vb) >> 6);
+  const int base = m.slice_ptr[sl], ws = (m.slice_ptr[sl + 1] - base) >> 6;
+  for (int q = 0; q < PFC_LANES_ROWS; q += G) {
+    const int i = i0 + q + g, il = i & 63;
+    // the row's place in the result: w entries, entry k at dst[st k]
+    const bool in = !row_ptr || i < m.n;
+    const int o = row_ptr ? (in ? row_ptr[i] : 0) : base + il, st = row_ptr ? 1 : 64;
+    const int w = row_ptr ? (in ? row_ptr[i + 1] - o : 0) : ws;
+    double* dst = out + o;
+    const bool lds = w <= cap;
+    for (int k = ln; k < w; k += L) {
+      if (lds) acc[k] = 0.0;
+      else dst[(long long)k * st] = 0.0;
+    }
+    const int* el_l = m.nv_el + vb + il;
+    const unsigned* slot_l = m.nv_slot + vb * m.nv_words + il;
+    for (int t0 = 0; t0 < vw; t0 += B) {
+      const int tv = t0 + t;
+      const int pk = t < B && tv < vw ? el_l[64LL * tv] : -1;
+      if (pk >= 0) {
+        const unsigned word = slot_l[64LL * ((long long)m.nv_words * tv + (m.nv_wide ? b : b >> 2))];
+        ps[lane] = psi[m.elem_nodes[(long long)(pk >> BITS) * Q + b]];
+        ss[lane] = m.nv_wide ? (int)word : (int)((word >> (8 * (b & 3))) & 255u);
+      }
+      wave_lds_sync();
+      if (pk >= 0) {
+        const int a = pk & ((1 << BITS) - 1);
+        const double vol = m.elem_vol[pk >> BITS];
+        const double* p = ps + g * L + t * Q;
+        double x, y;
+        if constexpr (Q <= 4) {
+          double S1 = 0.0, S2 = 0.0;
+#pragma unroll
+          for (int c = 0; c < Q; ++c) { S1 += p[c]; S2 = fma(p[c], p[c], S2); }
+          x = vol * cm_of(Q - 1) * (a == b ? 2.0 : 1.0);
+          y = psi2_product(S1, S2, p[a], p[b]);
+        } else {
+          const double* C = Ct + a * Q + b;
+          int e = 0;
+          x = vol;
+          y = 0.0;
+#pragma unroll
+          for (int c = 0; c < Q; ++c) {
+            double r = 0.0;
+#pragma unroll
+            for (int d = c; d < Q; ++d) r += C[e++ * (Q * Q)] * p[d];
+            y += p[c] * r;
+          }
+        }
+        xs[lane] = x;
+        ys[lane] = y;
+      }
+      const unsigned long long have = __ballot(pk >= 0);
+      wave_lds_sync();
+      if (!have) break;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int e = g * L + u * Q + ln;
+        if (ln < Q && (have >> e & 1)) {
+          const int k = ss[e];
+          if (lds) acc[k] = fma(xs[e], ys[e], acc[k]);
+          else dst[(long long)k * st] = fma(xs[e], ys[e], dst[(long long)k * st]);
+        }
+        wave_lds_sync();
+      }
+    }
+    for (int k = ln; k < w; k += L) dst[(long long)k * st] = -3.0 * (lds ? acc[k] : dst[(long long)k * st]);
+    wave_lds_sync();
+  }
+}
+
+template <int Q>
 __global__ __launch_bounds__(PFC_ROW_T) void k_row_N(MeshDev m, const double* __restrict__ psi, double* __restrict__ out,
                                                      const int* __restrict__ row_ptr, int cap) {
-  const int T = blockDim.x, tid = threadIdx.x, st = T + 1;
-  const int rank = xcd_rank(blockIdx.x, gridDim.x);
-  const int sl = rank * (T >> 6) + (tid >> 6), lane = tid & 63, i = sl * 64 + lane;
+  const int T = blockDim.x, tid = threadIdx.x, st = T + 1, rank = xcd_rank(blockIdx.x, gridDim.x);
+  const int sl = rank * (T >> 6) + (tid >> 6), lane = tid & 63;
   double* acc = pfc_row_lds + tid;
   double* sp = acc + cap * st;
   if (sl < m.n_slices) {
     const int base = m.slice_ptr[sl], w = (m.slice_ptr[sl + 1] - base) >> 6;
     const long long e0 = (long long)base + lane;
-    if constexpr (STAGE) {
-      const WaveCols wc = wave_cols(m, sl, lane, e0);
-      for_width(w, [&](int k) { sp[k * st] = psi[wc.at(k)]; });
-    }
-    const int o = row_ptr && i < m.n ? row_ptr[i] : 0, len = row_ptr ? (i < m.n ? row_ptr[i + 1] - o : 0) : w;
-    row_sums<STAGE>(acc, st, cap, w, [&](auto sums) {
-      row_visits<Q, STAGE>(m, sl, lane, psi, sp, st, [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
+    const WaveCols wc = wave_cols(m, sl, lane, e0);
+    for_width(w, [&](int k) { sp[k * st] = psi[wc.at(k)]; });
+    row_sums<true>(acc, st, cap, w, [&](auto sums) {
+      row_visits<Q, true>(m, sl, lane, psi, sp, st, [&](const Visit<Q>& v) { visit_Mpsi2<Q>(m, v, sums); });
     }, [&](int k, double x) {
       x *= -3.0;
       if (!row_ptr) out[e0 + 64LL * k] = x;
-      else if (STAGE) acc[k * st] = x;  // stored along the rows below
-      else if (k < len) out[o + k] = x;
+      else acc[k * st] = x;  // stored along the rows below
     });
   }
-  if (!STAGE || !row_ptr) return;
-  __syncthreads();
-  const int r0 = rank * T, r1 = min(r0 + T, m.n);
-  if (r0 >= r1) return;
-  const int b0 = row_ptr[r0], nb = row_ptr[r1] - b0;
-  const float iz = m.zrow ? 1.0f / (float)m.zrow : 0.0f;
-  for (int q = tid; q < nb; q += T) {
-    int r;
-    if (m.zrow) {
-      r = grid_div(q, iz);
-    } else {  // the last row that begins at or before q
-      int hi = r1 - r0;
-      r = 0;
-      while (hi - r > 1) {
-        const int mid = (r + hi) >> 1;
-        if (row_ptr[r0 + mid] - b0 <= q) r = mid;
-        else hi = mid;
-      }
+  if (!row_ptr) return;
+  if (m.zrow) {  // rows of one length: the workgroup's entries side by side
+    __syncthreads();
+    const int b0 = rank * T * m.zrow, nb = min(T, m.n - rank * T) * m.zrow;
+    const float iz = 1.0f / (float)m.zrow;
+    for (int q = tid; q < nb; q += T) {
+      const int r = grid_div(q, iz);
+      out[b0 + q] = pfc_row_lds[(q - r * m.zrow) * st + r];
     }
-    const int k = m.zrow ? q - r * m.zrow : q - (row_ptr[r0 + r] - b0);
-    out[b0 + q] = pfc_row_lds[k * st + r];
+  } else if (sl < m.n_slices) {  // the wave's rows one after the other (a search of each entry's row in
+                                 // row_ptr instead: unstructured tetrahedra, 10^5 nodes, 196 -> 168 us)
+    wave_lds_sync();
+    const int i = sl * 64 + lane, o = i < m.n ? row_ptr[i] : 0, len = i < m.n ? row_ptr[i + 1] - o : 0;
+    for (int r = 0; r < 64; ++r) {
+      const int orow = __builtin_amdgcn_readlane(o, r), lrow = __builtin_amdgcn_readlane(len, r);
+      for (int k = lane; k < lrow; k += 64) out[orow + k] = pfc_row_lds[k * st + (tid & ~63) + r];
+    }
   }
 }
 
@@ -300,15 +396,42 @@ __global__ __launch_bounds__(PFC_ROW_T) void k_row_AR(MeshDev m, const double* _
   if (i < n) { out[i] = w0; out[n + i] = w1; out[2 * n + i] = w2; }
 }
 
+// Which kernel forms N: a thread per row (k_row_N) wherever its rows fill the chip.
+// Not on meshes with a row too long to stage.  On P2 meshes a thread's walk is long (24
+// simplices of 10 terms around a 3D vertex), so that up to about 640 slices, where the
+// walk of one wave decides, several lanes per row are faster, and in 2D also beyond that
+// where the staged rows (of 40 entries and more) leave k_row_N fewer than four waves a CU.
+// Per call, a thread per row / lanes: 2D P2 40^2 43 / 22 us, 100^2 (625 slices) 42 / 43,
+// 200^2 70 / 118; 3D P2 12^3 (216 slices) 267 / 129, 20^3 (1000) 417 / 464; unstructured
+// triangles with 79976 nodes (1250 slices, rows up to 49) 111 / 82.
+static bool few_waves(const RowPlan& p) { return 4 * p.lds(2) / (p.T / 64) > 160 * 1024; }
+static bool lanes_N(const pfc_mesh* m, const RowPlan& p) {
+  return m->dev.nv_wide || (m->degree == 2 && (m->n_slices <= 640 || (m->dim == 2 && few_waves(p))));
+}
+
 int launch_row_N(const pfc_mesh* m, const double* psi, double* out, bool csr, hipStream_t s) {
-  const RowPlan p = row_plan(m, 2);
   const int* rp = csr ? m->d_row_ptr : nullptr;
-#define PFC_X(Q)                                                                                                      \
-  if (p.stage) hipLaunchKernelGGL((k_row_N<Q, true>), row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, out, rp, \
-                                  p.cap);                                                                             \
-  else hipLaunchKernelGGL((k_row_N<Q, false>), row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, out, rp, p.cap)
-  PFC_FOR_NLOC(m, PFC_X)
+  const RowPlan p = row_plan(m, 2);
+  if (lanes_N(m, p)) {
+    const int cap = std::min(m->dev.zmax, PFC_LANES_CAP), rows = PFC_ROW_T / 64 * PFC_LANES_ROWS;
+    const dim3 nb((m->n_slices * 64 + rows - 1) / rows);
+#define PFC_X(Q, L)                                                                                       \
+  hipLaunchKernelGGL((k_lanes_N<Q, L>), nb, dim3(PFC_ROW_T),                                              \
+                     (PFC_ROW_T / 64) * (PFC_LANES_BUF + 64 / L * cap) * sizeof(double), s, m->dev, psi,  \
+                     out, rp, cap, m->d_p2C2t)
+    if (m->nloc == 3) PFC_X(3, 64);
+    else if (m->nloc == 4) PFC_X(4, 64);
+    else if (m->dev.nv_wide && m->nloc == 6) PFC_X(6, 64);
+    else if (m->dev.nv_wide) PFC_X(10, 64);
+    else if (m->nloc == 10) PFC_X(10, 32);
+    else if (few_waves(p)) PFC_X(6, 32);
+    else PFC_X(6, 16);
 #undef PFC_X
+  } else {
+#define PFC_X(Q) hipLaunchKernelGGL(k_row_N<Q>, row_grid(m, p.T), dim3(p.T), p.lds(2), s, m->dev, psi, out, rp, p.cap)
+    PFC_FOR_NLOC(m, PFC_X)
+#undef PFC_X
+  }
   PFC_HIP(hipGetLastError());
   return PFC_OK;
 }
@@ -814,12 +937,12 @@ std::vector<Poly> p2_basis(int m) {
 }
 }  // namespace
 
-// M2 [q*q], D [k*k*q*q], C2 [q*q][c <= d], C3 [q][b <= c <= d] concatenated
+// M2 [q*q], D [k*k*q*q], C2 [q*q][c <= d], C3 [q][b <= c <= d], C2 transposed [c <= d][q*q], concatenated
 static std::vector<double> p2_tables(int m) {
   const std::vector<Poly> B = p2_basis(m);
   const int q = (int)B.size(), k = m + 1;
   const int np = q * (q + 1) / 2, nt = q * (q + 1) * (q + 2) / 6;
-  std::vector<double> t((size_t)q * q + (size_t)k * k * q * q + (size_t)q * q * np + (size_t)q * nt, 0.0);
+  std::vector<double> t((size_t)q * q + (size_t)k * k * q * q + 2 * (size_t)q * q * np + (size_t)q * nt, 0.0);
   double* M2 = t.data();
   double* D = M2 + q * q;
   double* C2 = D + k * k * q * q;
@@ -846,6 +969,9 @@ static std::vector<double> p2_tables(int m) {
         for (int d = c; d < q; ++d, ++p)  // C2 holds each product of c != d twice already
           C3[a * nt + p] = (c == d ? (b == c ? 1.0 : 3.0) : (b == c ? 1.5 : 3.0)) *
                            C2[(a * q + b) * np + c * q - c * (c - 1) / 2 + d - c];
+  double* C2t = C3 + (size_t)q * nt;
+  for (int ab = 0; ab < q * q; ++ab)
+    for (int p = 0; p < np; ++p) C2t[(size_t)p * q * q + ab] = C2[(size_t)ab * np + p];
   return t;
 }
 
@@ -932,6 +1058,7 @@ static int create_lagrange(const char* who, int dim, int degree, int n, int n_el
     m->dev.p2_D = m->d_p2tab + k * k;
     m->dev.p2_C2 = m->dev.p2_D + kv * kv * k * k;
     m->dev.p2_C3 = m->dev.p2_C2 + k * k * (k * (k + 1) / 2);
+    m->d_p2C2t = m->dev.p2_C3 + k * (k * (k + 1) * (k + 2) / 6);
   }
   // element geometry and assembly on the GPU
   double* d_X = nullptr;

@@ -152,3 +152,40 @@ def test_step_time_grows_with_the_simplices(pfc):
             pfc.pfc_instance_destroy(inst)
             pfc.pfc_mesh_destroy(h)
     assert t[1600] <= 16 * t[200], t
+
+
+# N with 16 and 32 lanes of a wave a row (P2, few slices), a thread a row beyond 640 slices, and a last wave that
+# is not full; unstructured P2 triangles with rows of 40 entries and more
+@pytest.mark.parametrize("dim,N", [(2, 3), (2, 11), (2, 102), (3, 3), (3, 5), (2, 0)])
+def test_assemble_N_p2(pfc, dim, N):
+    if N:
+        mesh = wl.p2_mesh(wl.make_mesh(dim, N, jitter=0.1, seed=71))
+    else:
+        mesh = hub(2, 15, degree=2)  # the hub's row: 46 entries
+    M, _ = assembly.mass_stiffness(mesh)
+    psi = -0.3 + 0.3 * np.random.default_rng(71).uniform(-1, 1, mesh.n)
+    h = create(pfc, mesh)
+    try:
+        Nd = dev(np.full(M.nnz, np.nan))
+        pfc.pfc_assemble_N(h, dev(psi), Nd)
+        ref = assembly.N_matrix(mesh, psi)
+        assert np.array_equal(ref.indices, M.indices)
+        assert np.abs(host(Nd) - ref.data).max() <= 1e-13 * np.abs(ref.data).max()
+    finally:
+        pfc.pfc_mesh_destroy(h)
+
+
+def test_assemble_time_grows_with_the_simplices(pfc):
+    """N on a hub of 1600 triangles against one of 200: a walk of all simplices for every 64 entries of the row
+    measured 46 times the time; a walk per simplex takes at most 8 times as long."""
+    t = {}
+    for m in (200, 1600):
+        mesh = hub(2, m)
+        h = create(pfc, mesh)
+        try:
+            psi, N = dev(np.full(mesh.n, -0.3)), dev(np.zeros(7 * m + 1))
+            N = N[:pfc.pfc_mesh_export_csr(h)[1].size]
+            t[m] = _best(lambda: [pfc.pfc_assemble_N(h, psi, N) for _ in range(5)])
+        finally:
+            pfc.pfc_mesh_destroy(h)
+    assert t[1600] <= 14 * t[200], t
