@@ -265,6 +265,7 @@ __device__ __forceinline__ void row_cols(const PatView<L>& pv, int sl, int lane,
     for (int k = 0; k < W; ++k) j[k] = gldo(c, (unsigned)lane * 4u, k * 256u);
   }
 }
+#define PFC_LOOP32 (1 << 22)  // entries of a row whose byte offsets fit 32 bits
 // sum over the entries of the row of (slice, lane), in order: load(k, j) gives what
 // entry k needs of memory (column j), use(v) adds it.  The columns are loaded at
 // once and the entries in chunks of CH, whose loads are issued together: a chunk is
@@ -292,7 +293,11 @@ __device__ __forceinline__ void row_entries(const PatView<L>& pv, int sl, int la
       }
     } else {
       const int w = pv.width(sl), e0 = pv.base(sl) + lane;
-      for (int k = 0; k < w; ++k) use(load(k, pv.at((long long)e0 + 64LL * k, sl * 64 + lane)));
+      if (L == PFC_COL_MEM && w > PFC_LOOP32) {
+        for (long long k = 0; k < w; ++k) use(load(k, pv.at(e0 + 64 * k, sl * 64 + lane)));
+      } else {
+        for (int k = 0; k < w; ++k) use(load(k, pv.at((long long)e0 + 64LL * k, sl * 64 + lane)));
+      }
     }
   });
 }
@@ -972,12 +977,20 @@ __device__ __forceinline__ T opval_g(const PcgOps<T>& o, long long e) {
   return o.C ? gld(o.C + e) : (gld(o.Mv + e) + o.cK * gld(o.Kv + e));
 }
 
-// values of a slice's entries: entry k of the lane's row, W entries a slice
+// values of a slice's entries: entry k of the lane's row.  A step known at compile time
+// goes with the scalar base (no lane's register: nothing spills beside the in-place sums
+// of long rows); in a loop over k it is a 32-bit offset, which a row of at most
+// PFC_LOOP32 entries fits (as a 64-bit scalar step it took 3D P2 10^3 float64 steps from
+// 134.6 to 151.0 ms)
 template <typename T>
 struct SliceVals {
   const T* a;
   unsigned off;
-  __device__ __forceinline__ T operator()(int k) const { return gldo(a, off + (unsigned)k * 64u * (unsigned)sizeof(T)); }
+  __device__ __forceinline__ T operator()(int k) const {
+    if (__builtin_constant_p(k)) return gldo(a + 64LL * k, off);
+    return gldo(a, off + (unsigned)k * 64u * (unsigned)sizeof(T));
+  }
+  __device__ __forceinline__ T operator()(long long k) const { return gldo(a + 64 * k, off); }
 };
 template <typename T>
 __device__ __forceinline__ SliceVals<T> slice_vals(const T* a, int base, int lane) {
@@ -990,10 +1003,10 @@ __device__ __forceinline__ void op_entries(const PcgOps<T>& o, const PatView<L>&
   const int base = pv.base(sl);
   if (o.C) {
     const SliceVals<T> c = slice_vals(o.C, base, lane);
-    row_entries<C>(pv, sl, lane, [&](int k, int j) { return load(c(k), j); }, use);
+    row_entries<C>(pv, sl, lane, [&](auto k, int j) { return load(c(k), j); }, use);
   } else {
     const SliceVals<T> m = slice_vals(o.Mv, base, lane), q = slice_vals(o.Kv, base, lane);
-    row_entries<C>(pv, sl, lane, [&](int k, int j) { return load(m(k) + o.cK * q(k), j); }, use);
+    row_entries<C>(pv, sl, lane, [&](auto k, int j) { return load(m(k) + o.cK * q(k), j); }, use);
   }
 }
 // Chunks of the row loops: as many entries as the kernel's 128 registers hold beside
@@ -1029,7 +1042,7 @@ __device__ __forceinline__ T row_dot(const PatView<L>& pv, int sl, int lane, con
   const SliceVals<T> a = slice_vals(A, pv.base(sl), lane);
   const T* u = uni(v);
   T acc = T(0);
-  row_entries<ChunkDot>(pv, sl, lane, [&](int k, int j) { return DotTerm<T>{a(k), vat(u, j)}; },
+  row_entries<ChunkDot>(pv, sl, lane, [&](auto k, int j) { return DotTerm<T>{a(k), vat(u, j)}; },
                  [&](const DotTerm<T>& t) { acc += t.a * t.v; });
   return acc;
 }
@@ -1207,7 +1220,7 @@ __device__ __forceinline__ void block_row(const InstDev& I, const PatView<L>& pv
     X2 om;
   };
   w0 = w1 = w2 = 0.0;
-  row_entries<ChunkBlock>(pv, sl, lane, [&](int k, int j) {
+  row_entries<ChunkBlock>(pv, sl, lane, [&](auto k, int j) {
     return Term{M(k), K(k), N(k), MOB ? Kp(k) : 0.0, MOB ? Fm(k) : 0.0, vat(mu, j), vat(ps, j), vat(om, j)};
   }, [&](const Term& q) {
     const double qo = (double)q.om;
