@@ -356,9 +356,9 @@ __device__ __forceinline__ double cm_of(int dim) { return dim == 2 ? (1.0 / 360.
 // streams and psi is gathered once per neighbour or once per visit.  Bound by
 // those gathers' latency, so the loads of several visits are issued together;
 // the terms of an entry are added in element order, one at a time.
-// Measured per call, launch and wait (19 us) included: pfc_assemble_N on 3D 64^3
-// 429 -> 67 us, pfc_apply_AR on 2D 512^2 65 -> 31 us, pfc_stage_rhs on 3D 48^3
-// 128 -> 49 us, pfc_load_psi3 on P2 200^2 68 -> 33 us; inside the solver's
+// Measured per call, launch and wait (17 us) included: pfc_assemble_N on 3D 64^3
+// 429 -> 63 us, pfc_apply_AR on 2D 512^2 65 -> 28 us, pfc_stage_rhs on 3D 48^3
+// 128 -> 46 us, pfc_load_psi3 on P2 200^2 68 -> 31 us; inside the solver's
 // launches (psi through the element's nodes, row_matrix) a 3D 64^3 step 25.8 -> 25.3 ms.
 
 // one visit: the simplex, its volume, the node's local index a, psi at the
@@ -1304,7 +1304,9 @@ __device__ __forceinline__ Red3 ph_pch_out(const InstDev& I, const Team& tm) {
 // load an entry instead of four, the address units being what bounds the gathers of
 // the long rows (P2 256^2 mixed stage solve 42.6 -> 36.2 ms, 3D 48^3 mixed step 22.0 ->
 // 20.4).  In float64 each is a vector of its own: side by side the rows would be 24 or 32
-// bytes apart, and measured slower (P2 256^2: 55.0 ms, at 24 bytes 60.3, at 32 59.3).
+// bytes apart, and measured slower (P2 256^2: 55.0 ms, at 24 bytes 60.3, at 32 59.3; both
+// on the grid with its nodes in place, where a solve takes fewer iterations than on
+// the moved nodes of the figures below).
 typedef float Float4 __attribute__((ext_vector_type(4)));
 typedef unsigned UInt4 __attribute__((ext_vector_type(4)));
 template <typename T>
@@ -1362,8 +1364,9 @@ __device__ __forceinline__ Red3 ph_cg_init(const InstDev& I, const State& S, con
 
 // One iteration.  Bound by the round trips of the gathers (four vectors at every
 // neighbour), so the columns of a row are loaded at once and its entries in chunks
-// that the registers hold (5 in float64: 4 + 1 round trips for the 19 entries of a
-// P2 vertex row instead of 14): P2 256^2 float64 solve 80.6 -> 65.4 ms.
+// that the registers hold (ChunkIter; in float64 4 of the 19 entries of a P2 vertex row:
+// 5 + 1 round trips instead of 14; 5 of the 9 of an edge row: 2 + 1): P2 256^2 float64
+// solve, nodes moved by up to 0.2 cells, 80.6 -> 65.4 ms.
 template <typename T, int L>
 __device__ __forceinline__ Red3 ph_cg_iter(const InstDev& I, const State& S, const Team& tm) {
   const int n = I.n;
