@@ -155,13 +155,12 @@ def test_step_time_grows_with_the_simplices(pfc):
 
 
 # N with 16 and 32 lanes of a wave a row (P2, few slices), a thread a row beyond 640 slices, and a last wave that
-# is not full; unstructured P2 triangles with rows of 40 entries and more
-@pytest.mark.parametrize("dim,N", [(2, 3), (2, 11), (2, 102), (3, 3), (3, 5), (2, 0)])
-def test_assemble_N_p2(pfc, dim, N):
-    if N:
-        mesh = wl.p2_mesh(wl.make_mesh(dim, N, jitter=0.1, seed=71))
-    else:
-        mesh = hub(2, 15, degree=2)  # the hub's row: 46 entries
+# is not full; a P2 hub of 46 entries; hub rows of 2048 entries (the most in LDS) and 2049 (in place), also P2
+@pytest.mark.parametrize("mesh", [("grid", 2, 3), ("grid", 2, 11), ("grid", 2, 102), ("grid", 3, 3), ("grid", 3, 5),
+                                  ("hub", 2, 15, 2), ("hub", 2, 2047, 1), ("hub", 2, 2048, 1), ("hub", 2, 700, 2)],
+                         ids=lambda m: "-".join(map(str, m)))
+def test_assemble_N(pfc, mesh):
+    mesh = hub(*mesh[1:]) if mesh[0] == "hub" else wl.p2_mesh(wl.make_mesh(*mesh[1:], jitter=0.1, seed=71))
     M, _ = assembly.mass_stiffness(mesh)
     psi = -0.3 + 0.3 * np.random.default_rng(71).uniform(-1, 1, mesh.n)
     h = create(pfc, mesh)
