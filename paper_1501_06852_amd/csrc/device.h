@@ -981,31 +981,35 @@ __device__ __forceinline__ T opval_g(const PcgOps<T>& o, long long e) {
 // goes with the scalar base (no lane's register: nothing spills beside the in-place sums
 // of long rows); in a loop over k it is a 32-bit offset, which a row of at most
 // PFC_LOOP32 entries fits (as a 64-bit scalar step it took 3D P2 10^3 float64 steps from
-// 134.6 to 151.0 ms)
-template <typename T>
+// 134.6 to 151.0 ms).  S: steps with the scalar base, where registers are short (double,
+// or columns from memory); the float grid kernels lose a little by it (3D 64^3 mixed step
+// 17.00 -> 17.07 ms)
+template <bool S, typename T>
 struct SliceVals {
   const T* a;
   unsigned off;
   __device__ __forceinline__ T operator()(int k) const {
-    if (__builtin_constant_p(k)) return gldo(a + 64LL * k, off);
+    if (S && __builtin_constant_p(k)) return gldo(a + 64LL * k, off);
     return gldo(a, off + (unsigned)k * 64u * (unsigned)sizeof(T));
   }
   __device__ __forceinline__ T operator()(long long k) const { return gldo(a + 64 * k, off); }
 };
-template <typename T>
-__device__ __forceinline__ SliceVals<T> slice_vals(const T* a, int base, int lane) {
-  return SliceVals<T>{uni(a + base), (unsigned)lane * (unsigned)sizeof(T)};
+template <bool S, typename T>
+__device__ __forceinline__ SliceVals<S, T> slice_vals(const T* a, int base, int lane) {
+  return SliceVals<S, T>{uni(a + base), (unsigned)lane * (unsigned)sizeof(T)};
 }
+template <typename T, int L>
+constexpr bool scalar_steps() { return sizeof(T) == 8 || L == PFC_COL_MEM; }
 // row_entries over a row of an operator, stored or M + cK (one choice for the row:
 // a branch per entry would keep its loads apart); load(a, j) with the value a
 template <typename C, typename T, int L, typename LoadF, typename UseF>
 __device__ __forceinline__ void op_entries(const PcgOps<T>& o, const PatView<L>& pv, int sl, int lane, LoadF load, UseF use) {
   const int base = pv.base(sl);
   if (o.C) {
-    const SliceVals<T> c = slice_vals(o.C, base, lane);
+    const auto c = slice_vals<scalar_steps<T, L>()>(o.C, base, lane);
     row_entries<C>(pv, sl, lane, [&](auto k, int j) { return load(c(k), j); }, use);
   } else {
-    const SliceVals<T> m = slice_vals(o.Mv, base, lane), q = slice_vals(o.Kv, base, lane);
+    const auto m = slice_vals<scalar_steps<T, L>()>(o.Mv, base, lane), q = slice_vals<scalar_steps<T, L>()>(o.Kv, base, lane);
     row_entries<C>(pv, sl, lane, [&](auto k, int j) { return load(m(k) + o.cK * q(k), j); }, use);
   }
 }
@@ -1039,7 +1043,7 @@ struct DotTerm {
 };
 template <typename T, int L>
 __device__ __forceinline__ T row_dot(const PatView<L>& pv, int sl, int lane, const T* A, const T* v) {
-  const SliceVals<T> a = slice_vals(A, pv.base(sl), lane);
+  const auto a = slice_vals<scalar_steps<T, L>()>(A, pv.base(sl), lane);
   const T* u = uni(v);
   T acc = T(0);
   row_entries<ChunkDot>(pv, sl, lane, [&](auto k, int j) { return DotTerm<T>{a(k), vat(u, j)}; },
@@ -1210,8 +1214,9 @@ __device__ __forceinline__ void block_row(const InstDev& I, const PatView<L>& pv
                                           BlockVec<X2> y, double& w0, double& w1, double& w2) {
   const double c1 = -(1.0 + I.r);
   const int base = pv.base(sl);
-  const SliceVals<double> M = slice_vals(I.m.M, base, lane), K = slice_vals(I.m.K, base, lane), N = slice_vals((const double*)I.N, base, lane);
-  const SliceVals<double> Kp = slice_vals((const double*)I.Kp, MOB ? base : 0, lane), Fm = slice_vals((const double*)I.Fm, MOB ? base : 0, lane);
+  constexpr bool S = scalar_steps<X2, L>();
+  const auto M = slice_vals<S>(I.m.M, base, lane), K = slice_vals<S>(I.m.K, base, lane), N = slice_vals<S>((const double*)I.N, base, lane);
+  const auto Kp = slice_vals<S>((const double*)I.Kp, MOB ? base : 0, lane), Fm = slice_vals<S>((const double*)I.Fm, MOB ? base : 0, lane);
   const double* mu = uni(y.v);
   const double* ps = uni(y.v + I.n);
   const X2* om = uni(y.om);
