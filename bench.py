@@ -9,9 +9,10 @@ stage solves.  Inputs are synthetic and seeded; everything is resident in HBM
 before the timed region starts.
 
 Prints one JSON line.  `value` is stage solves per second.  `roofline` uses the
-algorithmic bytes of the solver kernel (paper_1501_06852_amd.roofline) per
-launch over the average launch period measured with HIP events on the solver
-stream.  `cpu_baseline` times the float64 oracle on one Rosenbrock step of the
+algorithmic bytes of the solver kernel (paper_1501_06852_amd.roofline: those of
+one PCG iteration at a time, of which launches that run two move about half) per
+launch that advanced the run over the average launch period measured with HIP
+events on the solver stream; `traffic` is what a launch does move.  `cpu_baseline` times the float64 oracle on one Rosenbrock step of the
 same workload on the host (single thread).
 
 Other workloads (`--workload`): 3D 64^3 mixed precision, the P2 / PFC1 / S_D
@@ -36,13 +37,14 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per solver launch from rocprofv3 FETCH_SIZE and WRITE_SIZE runs,
 # each scaled by what the counter reads for a plain device copy of known size
-# (fetch x2.0, write x1.0), averaged over every launch of a profiled
-# `--steps 1 --warmup 0` run (mixed workloads: `--no-precision-check`).  A figure holds only for the kernel sources it
+# (fetch x2.0, write x1.0), averaged over the launches of a profiled
+# `--steps 1 --warmup 0` run that advanced it (mixed workloads: `--no-precision-check`; the launches behind the end,
+# which write nothing and read 0.34 MB, are taken off).  A figure holds only for the kernel sources it
 # was taken on: when their digest differs, `traffic` is reported as null.
 TRAFFIC = {
     # workload: (sha256 of the kernel sources, bytes per launch, algorithmic bytes per launch of the same run)
-    "pfc2d_512_fp64": ("5d5cd65844577a56e2b1a161728419fd8b5c8c648fe81de45ee6a64c1930da38", 45884907.0, 85211856.0),
-    "pfc3d_64_mixed": ("5d5cd65844577a56e2b1a161728419fd8b5c8c648fe81de45ee6a64c1930da38", 37439688.0, 71753338.0),
+    "pfc2d_512_fp64": ("768de3037656096a2a21a09c5215744709320740f0704844272a6dbff2196a03", 49585313.0, 89760531.0),
+    "pfc3d_64_mixed": ("768de3037656096a2a21a09c5215744709320740f0704844272a6dbff2196a03", 43921232.0, 77646124.0),
 }
 
 

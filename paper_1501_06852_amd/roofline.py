@@ -13,8 +13,11 @@ PFC1 (mobility model): the block SpMV also streams K_+ and F values,
 n [z (5*8 + 4) + 4 + 48].  S_D variant: its fixed-count PCG iterations run on
 the second-ring pattern with z_sd entries per row.  Rows of different length
 (P2 meshes) enter through the mean z = nnz / n, which gives the exact total.
-These count every array once per use (no cache reuse), which is what the
-method must move; they are the numerator of the roofline fraction.
+These count every array once per use (no cache reuse), as a method that runs one
+PCG iteration at a time moves them; they are the numerator of the roofline
+fraction.  They are no lower bound: launches that run two iterations read the
+operator once for both (n [z w + 13 w] for two iterations against twice the
+count above) and move about half of what the count credits them with.
 """
 from __future__ import annotations
 
